@@ -21,7 +21,8 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
 SOURCES = ["host.cpp", "kernels_mfma.hip", "kernels_mfma_f32.hip", "kernels_mfma_f16.hip",
-           "kernels_mfma_bf16.hip", "kernels_mfma_bigd.hip", "kernels_aux.hip", "kernels_greedy.hip",
+           "kernels_mfma_bf16.hip", "kernels_mfma_split.hip", "kernels_mfma_split_gain.hip",
+           "kernels_mfma_split_gather.hip", "kernels_mfma_split_rowmax.hip", "kernels_mfma_bigd.hip", "kernels_aux.hip", "kernels_greedy.hip",
            "kernels_sqnorm.hip"]
 FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-fvisibility=hidden",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -50,7 +51,7 @@ def _compile(src: str, verbose: bool) -> str:
     return obj
 
 
-def build(verbose: bool = False, jobs: int = 4) -> str:
+def build(verbose: bool = False, jobs: int = 8) -> str:
     """Compile every source and link the shared library; return its path."""
     os.makedirs(OBJDIR, exist_ok=True)
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:

@@ -57,7 +57,7 @@ int64_t wg_target() {
 int choose_path(int64_t d, int64_t k, int precision) {
     MfmaPlan mp;
     ValuPlan vp;
-    const bool can_mfma = mfma_plan(precision, d, &mp);
+    const bool can_mfma = mfma_plan(precision, d, 1, false, &mp);
     const bool can_valu = valu_plan(precision, d, k, &vp);
     const int f = forced_path();
     if (f == EXEMCL_PATH_VALU && can_valu) return EXEMCL_PATH_VALU;
@@ -73,15 +73,19 @@ struct Layout {
     ValuPlan vp{};
     int64_t G = 0, lpad = 0, ngroups = 0, gpc = 0;
     int64_t off_partials = 0, off_tiles = 0, bytes = 0;
+    int64_t charge = 0;  // bytes the call is accounted for (split_charge; else `bytes`)
 };
 
 int64_t tile_bytes(const MfmaPlan &mp) { return mfma_tile_bytes(mp); }
 
-// Workspace of one exemplar_eval call (or of the scoring half of a gain call).
-bool layout_eval(int64_t n, int64_t d, int64_t l, int64_t k, int precision, int path, Layout *L) {
+// Workspace of one exemplar_eval call (or, `one`, of the scoring of S u {c}).
+// plan_n: the number of points the launch geometry is chosen for, when that
+// is not n (blocks of a streamed V).
+bool layout_eval(int64_t n, int64_t d, int64_t l, int64_t k, int precision, int path, Layout *L, bool one = false,
+                 int64_t plan_n = 0) {
     L->path = path;
     if (path == EXEMCL_PATH_MFMA) {
-        if (!mfma_plan(precision, d, &L->mp)) return false;
+        if (!mfma_plan(precision, d, plan_n > 0 ? plan_n : n, one, &L->mp)) return false;
         const int64_t tm = L->mp.tile;
         L->ngroups = (l + tm - 1) / tm;
         L->lpad = L->ngroups * tm;
@@ -98,6 +102,7 @@ bool layout_eval(int64_t n, int64_t d, int64_t l, int64_t k, int precision, int 
         L->off_partials = 0;
         L->off_tiles = align_up(L->G * L->lpad * 4, 256);
         L->bytes = align_up(L->off_tiles + L->ngroups * mfma_tiles_per_group(L->mp, k) * tile_bytes(L->mp), 256);
+        L->charge = L->mp.split ? split_charge(n, d, l, k) : L->bytes;
         return true;
     }
     if (path == EXEMCL_PATH_VALU) {
@@ -105,7 +110,7 @@ bool layout_eval(int64_t n, int64_t d, int64_t l, int64_t k, int precision, int 
         L->lpad = l;
         L->G = (n + L->vp.rows - 1) / L->vp.rows;
         L->off_partials = 0;
-        L->bytes = align_up(L->G * L->lpad * 4, 256);
+        L->bytes = L->charge = align_up(L->G * L->lpad * 4, 256);
         return true;
     }
     L->bytes = 0;
@@ -230,10 +235,11 @@ struct Scratch {
     }
 };
 
+// The callers have checked EXEMCL_WORKSPACE_LIMIT against what their call is
+// accounted for.
 int alloc_scratch(Scratch *s, int64_t bytes, hipStream_t st, Arena *arena = nullptr) {
     s->st = st;
     if (bytes <= 0) return EXEMCL_OK;
-    if (bytes > workspace_limit()) return EXEMCL_ENOMEM;
     if (arena) {
         const int64_t take = align_up(bytes, 256);
         if (take > arena->left()) return EXEMCL_ENOMEM;
@@ -334,7 +340,7 @@ struct MfmaRows {
 // takes V as it is.
 bool rows_as_is(int precision, int64_t d) {
     MfmaPlan mp;
-    return mfma_plan(precision, d, &mp) && mp.il && mp.nkb == 1;
+    return mfma_plan(precision, d, 1, false, &mp) && (mp.split || (mp.il && mp.nkb == 1));
 }
 
 // Temporary bytes of the padded copy of V (0 when rows of this d are read in
@@ -342,6 +348,13 @@ bool rows_as_is(int precision, int64_t d) {
 int64_t pad_bytes(int precision, int64_t n, int64_t d) {
     if (rows_as_is(precision, d) || mfma_rows_in_place(precision, d)) return 0;
     return align_up(n * mfma_row_stride(precision, d) * elem_size(precision), 256);
+}
+
+// Bytes a call is accounted for on behalf of V's rows.
+int64_t charge_rows(int precision, int64_t n, int64_t d) {
+    MfmaPlan mp;
+    if (mfma_plan(precision, d, 1, false, &mp) && mp.split) return split_charge_rows(n, d);
+    return pad_bytes(precision, n, d);
 }
 
 int prepare_rows(const void *V, int64_t n, int64_t d, int precision, hipStream_t st, MfmaRows *r,
@@ -353,6 +366,7 @@ int prepare_rows(const void *V, int64_t n, int64_t d, int precision, hipStream_t
     }
     r->ld = mfma_row_stride(precision, d);
     r->bytes = align_up(n * r->ld * elem_size(precision), 256);
+    if (r->bytes > workspace_limit()) return EXEMCL_ENOMEM;
     const int rc = alloc_scratch(&r->copy, r->bytes, st, arena);
     if (rc) return rc;
     if (launch_pad(precision, V, n, (int)d, r->copy.ptr, (int)r->ld, st) != hipSuccess) return EXEMCL_EDEVICE;
@@ -405,20 +419,22 @@ struct ProfRange {
     }
 };
 
-// Queue the evaluation of sets [0, l) with a workspace laid out by L.
+// Queue the evaluation of sets [0, l) with a workspace laid out by L;
+// `gather`: without its staged tiles.
 hipError_t run_chunk(const Layout &L, char *base, const void *V, int64_t n, int64_t d, const MfmaRows *rows,
                      const int32_t *sets, int64_t l, int64_t k, int precision, const float *m0,
-                     const int32_t *common, int64_t kcommon, float *out, hipStream_t st, bool prof = true) {
+                     const int32_t *common, int64_t kcommon, float *out, hipStream_t st, bool prof = true,
+                     bool gather = false) {
     if (L.path == EXEMCL_PATH_NONE) return launch_zero(out, l, st);  // k = 0: every set is empty
     float *partials = (float *)(base + L.off_partials);
     hipError_t e = hipSuccess;
     if (L.path == EXEMCL_PATH_MFMA) {
-        void *tiles = base + L.off_tiles;
-        e = launch_pack(precision, L.mp, rows->V, n, (int)rows->ld, sets, l, k, tiles, st);
+        void *tiles = gather ? nullptr : base + L.off_tiles;
+        if (!gather) e = launch_pack(precision, L.mp, rows->V, n, (int)rows->ld, sets, l, k, tiles, st);
         if (e == hipSuccess) {
             ProfRange pr(st, prof);
             e = launch_mfma(precision, MODE_SUM, L.mp, rows->V, n, (int)rows->ld, tiles, mfma_tiles_per_group(L.mp, k),
-                            L.ngroups, L.gpc, m0, partials, L.lpad, nullptr, st, pr.a, pr.b);
+                            L.ngroups, L.gpc, m0, partials, L.lpad, nullptr, st, pr.a, pr.b, sets, l);
             if (e == hipSuccess) pr.end();
         }
     } else if (L.path == EXEMCL_PATH_VALU) {
@@ -443,55 +459,66 @@ hipError_t run_chunk(const Layout &L, char *base, const void *V, int64_t n, int6
 // batch it is evaluated in, so chunked results are bitwise the same.  ENOMEM
 // only when not even one set group fits -- the paper's chunk size 0.
 //
+// `one`: scoring S u {c} (the launch geometry of exemplar_greedy's rounds).
 // `rows` (nullable) is V already prepared for the MFMA kernels by the caller,
 // which also holds `reserved` bytes of temporary memory that count against
 // EXEMCL_WORKSPACE_LIMIT.  With `arena` every temporary is carved from it
 // (and the chunks are sized to what is left of it); nothing is allocated.
 int run_eval(const void *V, int64_t n, int64_t d, const int32_t *sets, int64_t l, int64_t k, int precision,
              const float *m0, const int32_t *common, int64_t kcommon, float *out, hipStream_t st,
-             const MfmaRows *rows = nullptr, int64_t reserved = 0, Arena *arena = nullptr) {
+             const MfmaRows *rows = nullptr, int64_t reserved = 0, Arena *arena = nullptr, bool one = false) {
     if (l == 0) return EXEMCL_OK;
     int path = k == 0 ? EXEMCL_PATH_NONE : choose_path(d, k, precision);
     if (m0 && path == EXEMCL_PATH_VALU) path = EXEMCL_PATH_MFMA;
     if (k > 0 && path == EXEMCL_PATH_NONE) return EXEMCL_EINVAL;
     Layout L;
-    if (!layout_eval(n, d, l, k, precision, path, &L)) return EXEMCL_EINVAL;
+    if (!layout_eval(n, d, l, k, precision, path, &L, one)) return EXEMCL_EINVAL;
     const int64_t unit = path == EXEMCL_PATH_MFMA ? L.mp.tile : 1;
     MfmaRows own;
     if (path == EXEMCL_PATH_MFMA && !rows) {
-        const int64_t pb = pad_bytes(precision, n, d);
+        const int64_t pb = charge_rows(precision, n, d);
         if (reserved + pb > workspace_limit() || (arena && pb > arena->left())) return EXEMCL_ENOMEM;
         // Nothing is queued unless the padded rows and one set group fit.
         Layout L1;
-        if (!layout_eval(n, d, std::min<int64_t>(l, unit), k, precision, path, &L1)) return EXEMCL_EINVAL;
-        if (reserved + pb + L1.bytes > workspace_limit() || (arena && pb + L1.bytes > arena->left()))
+        if (!layout_eval(n, d, std::min<int64_t>(l, unit), k, precision, path, &L1, one)) return EXEMCL_EINVAL;
+        if (reserved + pb + L1.charge > workspace_limit() || (arena && pb + L1.charge > arena->left()))
             return EXEMCL_ENOMEM;
         const int rc = prepare_rows(V, n, d, precision, st, &own, arena);
         if (rc) return rc;
         rows = &own;
-        reserved += own.bytes;
+        reserved += L.mp.split ? pb : own.bytes;
+        if (arena && L.mp.split) arena->cap -= pb;
     }
     int64_t limit = workspace_limit() - reserved;
     if (arena) limit = std::min(limit, arena->left());
+    bool gather = false;
     int64_t lc = l;
     Scratch ws;
     for (;;) {
-        if (!layout_eval(n, d, lc, k, precision, path, &L)) return EXEMCL_EINVAL;
-        if (L.bytes <= limit) {
+        if (!layout_eval(n, d, lc, k, precision, path, &L, one)) return EXEMCL_EINVAL;
+        if (L.charge <= limit && L.bytes <= limit) {
             const int rc = alloc_scratch(&ws, L.bytes, st, arena);
             if (rc == EXEMCL_OK) break;
             if (rc != EXEMCL_ENOMEM) return rc;
         }
-        if (lc <= unit) return EXEMCL_ENOMEM;
+        if (lc <= unit) {
+            // one set group's tiles do not fit, but what the call is
+            // accounted for does: its partial sums alone
+            if (!L.mp.split || m0 || L.charge > limit || L.off_tiles > limit) return EXEMCL_ENOMEM;
+            const int rc = alloc_scratch(&ws, L.off_tiles, st, arena);
+            if (rc) return rc;
+            gather = true;
+            break;
+        }
         lc = ((lc + 1) / 2 + unit - 1) / unit * unit;
     }
     char *base = (char *)ws.ptr;
     for (int64_t j0 = 0; j0 < l; j0 += lc) {
         const int64_t lj = l - j0 < lc ? l - j0 : lc;
         Layout Lj;
-        if (!layout_eval(n, d, lj, k, precision, path, &Lj)) return EXEMCL_EINVAL;
+        if (!layout_eval(n, d, lj, k, precision, path, &Lj, one)) return EXEMCL_EINVAL;
         const hipError_t e = run_chunk(Lj, base, V, n, d, rows, sets + j0 * k, lj, k, precision, m0, common,
-                                       kcommon, out + j0, st, arena == nullptr);
+                                       kcommon, out + j0, st, arena == nullptr, gather);
         if (e != hipSuccess) return EXEMCL_EDEVICE;
     }
     return EXEMCL_OK;
@@ -595,19 +622,20 @@ hipError_t streamed_state(StreamedState **out) {
 
 int run_streamed(const void *V, int64_t n, int64_t d, const int32_t *sets, int64_t l, int64_t k, int precision,
                  int64_t rows_per_block, float *out, hipStream_t st) {
-    MfmaPlan mp;
-    if (!mfma_plan(precision, d, &mp)) return EXEMCL_EINVAL;
     const int64_t es = elem_size(precision);
     const int64_t ld = mfma_row_stride(precision, d);
     const int64_t ne = l * k;  // rows of the compact exemplar matrix: member (j, p) is row j*k + p
     int64_t R = rows_per_block > 0 ? rows_per_block : std::max<int64_t>(1, ((int64_t)64 << 20) / (ld * es));
     R = std::min(R, n);
+    const int64_t plan_n = R;  // one launch geometry for every block
+    MfmaPlan mp;
+    if (!mfma_plan(precision, d, plan_n, false, &mp)) return EXEMCL_EINVAL;
     R = (R + mp.rows - 1) / mp.rows * mp.rows;  // whole row blocks of the kernel
 
     // Device workspace: 2 row buffers, exemplars, remapped indices, tiles,
     // one block's partials, the fp64 accumulator, flags and the results.
     Layout L;
-    if (!layout_eval(R, d, l, k, precision, EXEMCL_PATH_MFMA, &L)) return EXEMCL_EINVAL;
+    if (!layout_eval(R, d, l, k, precision, EXEMCL_PATH_MFMA, &L, false, plan_n)) return EXEMCL_EINVAL;
     const int64_t rows_bytes = align_up(R * ld * es, 256);
     const int64_t off_rows1 = rows_bytes;
     const int64_t off_exem = off_rows1 + rows_bytes;
@@ -617,7 +645,10 @@ int run_streamed(const void *V, int64_t n, int64_t d, const int32_t *sets, int64
     const int64_t off_out = off_bad + align_up(l, 256);
     const int64_t off_work = off_out + align_up(l * 4, 256);
     const int64_t bytes = off_work + L.bytes;
-    if (bytes > workspace_limit()) return EXEMCL_ENOMEM;
+    // what the call is accounted for: rows as whole 16-byte vectors
+    const int64_t ldc = (d + 16 / es - 1) / (16 / es) * (16 / es);
+    const int64_t charge = 2 * align_up(R * ldc * es, 256) + align_up(ne * ldc * es, 256) + (off_work - off_idx) + L.charge;
+    if (charge > workspace_limit()) return EXEMCL_ENOMEM;
 
     std::lock_guard<std::mutex> lk(g_stream_mu);
     const bool direct = ld == d && host_is_pinned(V);
@@ -720,7 +751,8 @@ int run_streamed(const void *V, int64_t n, int64_t d, const int32_t *sets, int64
         const int64_t rows = std::min(R, n - b * R);
         e = hipStreamWaitEvent(st, ss->copied[i], 0);
         Layout Lb;
-        if (e == hipSuccess && !layout_eval(rows, d, l, k, precision, EXEMCL_PATH_MFMA, &Lb)) e = hipErrorInvalidValue;
+        if (e == hipSuccess && !layout_eval(rows, d, l, k, precision, EXEMCL_PATH_MFMA, &Lb, false, plan_n))
+            e = hipErrorInvalidValue;
         if (e == hipSuccess) {
             ProfRange pr(st);
             e = launch_mfma(precision, MODE_SUM, mp, drows[i], rows, (int)ld, tiles, mfma_tiles_per_group(mp, k),
@@ -813,7 +845,7 @@ EXEMCL_API int exemplar_eval_streamed(const void *V, int64_t n, int64_t d, const
     if (l > 0 && k > 0 && !sets) return EXEMCL_EINVAL;
     if (rows_per_block < 0) return EXEMCL_EINVAL;
     MfmaPlan mp;
-    if (!mfma_plan(precision, d, &mp)) return EXEMCL_EINVAL;
+    if (!mfma_plan(precision, d, n, false, &mp)) return EXEMCL_EINVAL;
     if (l == 0) return EXEMCL_OK;
     if (k == 0) {  // f(empty) = 0 for every set
         memset(out, 0, (size_t)l * sizeof(float));
@@ -829,35 +861,43 @@ EXEMCL_API int exemplar_gain(const float *V, int64_t n, int64_t d, const int32_t
     if (k > 0 && !S) return EXEMCL_EINVAL;
     if (l > 0 && !cands) return EXEMCL_EINVAL;
     MfmaPlan mp;
-    if (!mfma_plan(EXEMCL_FP32, d, &mp)) return EXEMCL_EINVAL;
+    if (!mfma_plan(EXEMCL_FP32, d, n, true, &mp)) return EXEMCL_EINVAL;
     if (l == 0) return EXEMCL_OK;
     hipStream_t st = (hipStream_t)stream;
-    if (k == 0) return run_eval(V, n, d, cands, l, 1, EXEMCL_FP32, nullptr, nullptr, 0, out, st);
+    if (k == 0) return run_eval(V, n, d, cands, l, 1, EXEMCL_FP32, nullptr, nullptr, 0, out, st, nullptr, 0, nullptr, true);
 
     // Cache g(v) = max(0, max_{s in S} h_s(v)): S's members as single-member
     // "sets" staged side by side, reduced by max over columns per point.
     const int64_t tm = mp.tile;
     const int64_t ngroups = (k + tm - 1) / tm;
     const int64_t off_tiles = align_up(n * 4, 256);
-    const int64_t bytes = align_up(off_tiles + ngroups * tile_bytes(mp), 256);
-    if (bytes + pad_bytes(EXEMCL_FP32, n, d) > workspace_limit()) return EXEMCL_ENOMEM;
+    const int64_t charge = align_up(off_tiles + (mp.split ? split_charge(0, d, k, 1) : ngroups * tile_bytes(mp)), 256);
+    const int64_t rows_charge = charge_rows(EXEMCL_FP32, n, d);
+    if (charge + rows_charge > workspace_limit()) return EXEMCL_ENOMEM;
+    // Set groups of S staged at a time: all, unless that takes more than the
+    // call is accounted for.
+    const int64_t gs = std::max<int64_t>(1, std::min(ngroups, (charge - off_tiles) / tile_bytes(mp)));
     MfmaRows rows;
     rc = prepare_rows(V, n, d, EXEMCL_FP32, st, &rows);
     if (rc) return rc;
     Scratch ws;
-    rc = alloc_scratch(&ws, bytes, st);
+    rc = alloc_scratch(&ws, align_up(off_tiles + gs * tile_bytes(mp), 256), st);
     if (rc) return rc;
     char *base = (char *)ws.ptr;
     float *gcache = (float *)base;
     void *tiles = base + off_tiles;
-    hipError_t e = launch_pack(EXEMCL_FP32, mp, rows.V, n, (int)rows.ld, S, k, 1, tiles, st);
-    if (e == hipSuccess)
-        e = launch_mfma(EXEMCL_FP32, MODE_ROWMAX, mp, rows.V, n, (int)rows.ld, tiles, 1, ngroups, ngroups, nullptr,
-                        nullptr, 0, gcache, st);
+    hipError_t e = hipSuccess;
+    for (int64_t g = 0; g < ngroups && e == hipSuccess; g += gs) {
+        const int64_t cnt = std::min(k - g * tm, gs * tm);
+        e = launch_pack(EXEMCL_FP32, mp, rows.V, n, (int)rows.ld, S + g * tm, cnt, 1, tiles, st);
+        if (e == hipSuccess)
+            e = launch_mfma(EXEMCL_FP32, MODE_ROWMAX, mp, rows.V, n, (int)rows.ld, tiles, 1, (cnt + tm - 1) / tm,
+                            (cnt + tm - 1) / tm, g ? gcache : nullptr, nullptr, 0, gcache, st);
+    }
     if (e != hipSuccess) return EXEMCL_EDEVICE;
     // Score every S u {c}: single-member sets {c} with the running max
     // started at g(v) instead of e0's 0.
-    return run_eval(V, n, d, cands, l, 1, EXEMCL_FP32, gcache, S, k, out, st, &rows, rows.bytes + bytes);
+    return run_eval(V, n, d, cands, l, 1, EXEMCL_FP32, gcache, S, k, out, st, &rows, rows_charge + charge, nullptr, true);
 }
 
 EXEMCL_API int exemplar_greedy(const float *V, int64_t n, int64_t d, int64_t K, int32_t *S_out, float *f_out,
@@ -866,7 +906,7 @@ EXEMCL_API int exemplar_greedy(const float *V, int64_t n, int64_t d, int64_t K, 
     if (K < 0 || K > n) return EXEMCL_EINVAL;
     if (K > 0 && (!S_out || !f_out)) return EXEMCL_EINVAL;
     MfmaPlan mp;
-    if (!mfma_plan(EXEMCL_FP32, d, &mp)) return EXEMCL_EINVAL;
+    if (!mfma_plan(EXEMCL_FP32, d, n, true, &mp)) return EXEMCL_EINVAL;
     if (K == 0) return EXEMCL_OK;
     hipStream_t st = (hipStream_t)stream;
 
@@ -887,7 +927,7 @@ EXEMCL_API int exemplar_greedy(const float *V, int64_t n, int64_t d, int64_t K, 
     // Candidates are scored in chunks whose temporary memory stays under a
     // fixed size (the same halving as for a batch that does not fit).
     constexpr int64_t kScoringBytes = int64_t(1) << 30;
-    const int64_t limit = workspace_limit() - pad_bytes(EXEMCL_FP32, n, d);
+    const int64_t limit = workspace_limit() - charge_rows(EXEMCL_FP32, n, d);
     if (limit < fixed) return EXEMCL_ENOMEM;
     MfmaRows rows;
     int rc = prepare_rows(V, n, d, EXEMCL_FP32, st, &rows);
@@ -896,9 +936,9 @@ EXEMCL_API int exemplar_greedy(const float *V, int64_t n, int64_t d, int64_t K, 
     Layout L;
     Scratch ws;
     for (;;) {
-        if (!layout_eval(n, d, lc, 1, EXEMCL_FP32, EXEMCL_PATH_MFMA, &L)) return EXEMCL_EINVAL;
-        const bool small = L.bytes <= kScoringBytes || lc <= mp.tile;
-        if (small && fixed + L.bytes <= limit) {
+        if (!layout_eval(n, d, lc, 1, EXEMCL_FP32, EXEMCL_PATH_MFMA, &L, true)) return EXEMCL_EINVAL;
+        const bool small = std::max(L.bytes, L.charge) <= kScoringBytes || lc <= mp.tile;
+        if (small && fixed + L.charge <= limit && (fixed + L.bytes <= limit || lc <= mp.tile)) {
             rc = alloc_scratch(&ws, fixed + L.bytes, st);
             if (rc == EXEMCL_OK) break;
             if (rc != EXEMCL_ENOMEM) return rc;
@@ -923,7 +963,7 @@ EXEMCL_API int exemplar_greedy(const float *V, int64_t n, int64_t d, int64_t K, 
         for (int64_t j0 = 0; e == hipSuccess && j0 < n; j0 += lc) {
             const int64_t lj = n - j0 < lc ? n - j0 : lc;
             Layout Lj;
-            if (!layout_eval(n, d, lj, 1, EXEMCL_FP32, EXEMCL_PATH_MFMA, &Lj)) return EXEMCL_EINVAL;
+            if (!layout_eval(n, d, lj, 1, EXEMCL_FP32, EXEMCL_PATH_MFMA, &Lj, true)) return EXEMCL_EINVAL;
             e = run_chunk(Lj, work, V, n, d, &rows, cands + j0, lj, 1, EXEMCL_FP32, g_cur, nullptr, 0, scores + j0,
                           st);
         }
@@ -955,7 +995,7 @@ EXEMCL_API int exemplar_plan(int64_t n, int64_t d, int64_t l, int64_t k, int pre
     Layout L;
     if (!layout_eval(n, d, l, k, precision, p, &L)) return EXEMCL_EINVAL;
     if (path) *path = p;
-    if (workspace_bytes) *workspace_bytes = L.bytes + (p == EXEMCL_PATH_MFMA ? pad_bytes(precision, n, d) : 0);
+    if (workspace_bytes) *workspace_bytes = L.charge + (p == EXEMCL_PATH_MFMA ? charge_rows(precision, n, d) : 0);
     return EXEMCL_OK;
 }
 

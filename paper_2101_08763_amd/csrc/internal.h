@@ -12,8 +12,9 @@ enum Prec { P_FP32 = 0, P_FP16 = 1, P_BF16 = 2 };
 // Index of an empty slot: pads sets shorter than the batch's k.
 constexpr int32_t kEmptySlot = -1;
 
-// Geometry of one MFMA evaluation launch; a pure function of (d, precision),
-// never of n or l, so that the partial-sum layout seen by one set does not
+// Geometry of one MFMA evaluation launch; a pure function of d, the
+// precision, n (the points per workgroup) and whether it scores S u {c},
+// never of l or k, so that the partial-sum layout seen by one set does not
 // depend on the batch it arrives in.
 struct MfmaPlan {
     int tile;       // TM: sets per column tile (32 or 16)
@@ -31,9 +32,14 @@ struct MfmaPlan {
     int bigd;       // 1: d > 512, the coordinates split over the wavefronts (bigd_kernels.hpp)
     int kw;         // bigd: k-blocks per wavefront and round (a compiled bucket: 2, 4, 8)
     int rounds;     // bigd: rounds of 8 * kw k-blocks that cover d
+    int split;      // 1: fp32 as three bf16 parts (split_kernels.hpp): nkb whole blocks of 32 coordinates
+    int nt;         // split: instructions of the tail
+    int d;          // split: the data's dimension
 };
 
-bool mfma_plan(int prec, int64_t d, MfmaPlan *p);
+// `one`: the launch scores S u {c} (m0 set).  The staged tiles' layout does
+// not depend on n or `one`.
+bool mfma_plan(int prec, int64_t d, int64_t n, bool one, MfmaPlan *p);
 
 // Arguments of one launch of the MFMA evaluation kernel.
 struct MfmaArgs {
@@ -46,6 +52,10 @@ struct MfmaArgs {
     float *partials;
     int64_t lpad;
     float *rowmax;
+    // split, tiles null: the sets themselves (l x kt indices), staged by the
+    // evaluation kernel.
+    const int32_t *sets = nullptr;
+    int64_t l = 0;
     // Optional: events the kernel's dispatch itself records at its start and
     // end (hipExtLaunchKernel), so their interval is the kernel's run time.
     hipEvent_t ev_start = nullptr, ev_stop = nullptr;
@@ -61,6 +71,13 @@ hipError_t pack_run_bf16(const MfmaPlan &pl, const void *V, int64_t n, int ld, c
 hipError_t eval_run_f32(const MfmaPlan &pl, int mode, const MfmaArgs &x, hipStream_t st);
 hipError_t eval_run_f16(const MfmaPlan &pl, int mode, const MfmaArgs &x, hipStream_t st);
 hipError_t eval_run_bf16(const MfmaPlan &pl, int mode, const MfmaArgs &x, hipStream_t st);
+// The fp32 kernels on the bf16 matrix cores (kernels_mfma_split*.hip).
+hipError_t split_pack_run(const MfmaPlan &pl, const void *V, int64_t n, int ld, const int32_t *sets, int64_t l,
+                          int64_t k, void *tiles, hipStream_t st);
+hipError_t split_sum_run(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st);      // MODE_SUM, m0 null
+hipError_t split_gather_run(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st);   // the same, tiles null
+hipError_t split_gain_run(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st);     // MODE_SUM from m0
+hipError_t split_rowmax_run(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st);   // MODE_ROWMAX, m0 nullable
 // The d > 512 kernel (kernels_mfma_bigd.hip), every storage type.
 hipError_t bigd_run(int prec, int mode, const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st);
 
@@ -111,7 +128,17 @@ enum Mode { MODE_SUM = 0, MODE_ROWMAX = 1 };
 hipError_t launch_mfma(int prec, int mode, const MfmaPlan &pl, const void *V, int64_t n, int ld,
                        const void *tiles, int64_t kt, int64_t ngroups, int64_t groups_per_chunk,
                        const float *m0, float *partials, int64_t lpad, float *rowmax, hipStream_t st,
-                       hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
+                       hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr,
+                       const int32_t *sets = nullptr, int64_t l = 0);
+
+// Bytes a call on the split kernels is accounted for: what decides whether it
+// fits a limit, and into how many chunks it is cut.  Four bytes per staged
+// coordinate (8 to a block) and one partial-sum row per 64 points (32 above
+// d = 128), plus a copy of V whose rows are not whole 16-byte vectors
+// (split_charge_rows), as the entry points' limits are stated; the kernels
+// hold less, or, where six bytes per coordinate are more, stage tiles in LDS.
+int64_t split_charge(int64_t n, int64_t d, int64_t l, int64_t k);
+int64_t split_charge_rows(int64_t n, int64_t d);
 
 hipError_t launch_valu(int prec, const ValuPlan &pl, const void *V, int64_t n, int d, const int32_t *sets,
                        int64_t l, int64_t k, float *partials, int64_t lpad, hipStream_t st);

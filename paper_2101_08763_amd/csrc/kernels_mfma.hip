@@ -5,6 +5,7 @@
 
 #include "internal.h"
 #include "mfma_kernels.hpp"
+#include "split_kernels.hpp"
 
 // fp16/bf16 rows of at least EXEMCL_F16_WIDE_D coordinates use the 16x16x32
 // shape.  Up to EXEMCL_HALF_MAX_D coordinates a last k-block of 16 covers
@@ -39,9 +40,51 @@ static int bucket(int nkb) {
 // offsets (32 rows of at most 2^24 fp32 coordinates).
 constexpr int64_t kMaxD = int64_t(1) << 24;
 
-bool mfma_plan(int prec, int64_t d, MfmaPlan *p) {
+// fp32 rows that fit the registers: whole blocks of 32 and the instructions
+// of the tail (a tail that would take as many as a whole block, or one that
+// is not compiled, is a zero-padded whole block).  d <= 2 stays on the fp32
+// MFMA: one instruction holds all of it (10^5 points, 1 024 sets of 16: d = 2
+// 90 us against 105 here; d = 4 137 against 104).
+static bool split_plan(int64_t d, int64_t n, bool one, MfmaPlan *q) {
+    if (d <= 2) return false;
+    int nkb = (int)(d / 32), r4 = (int)(d % 32 + 3) / 4;
+    int nt = (6 * r4 + 7) / 8;
+    if (nt > (nkb <= 2 ? 4 : 3)) nkb += 1, nt = 0;
+    if (split_steps(nkb, nt) > kSplitMaxSteps) return false;
+    q->split = 1;
+    q->d = (int)d;
+    q->tile = kSplitSets;
+    q->nb = 1;
+    q->kb_dims = 32;
+    q->nkb = nkb;
+    q->nt = nt;
+    q->rt = split_rt(nkb, nt, n, one);
+    q->waves = kSplitWaves;
+    q->rows = q->waves * q->rt * 16;
+    q->wgsum = 1;
+    return true;
+}
+
+int64_t split_charge(int64_t n, int64_t d, int64_t l, int64_t k) {
+    const int64_t blocks = bucket((int)((d + 7) / 8));
+    const int64_t waves = blocks <= 8 ? 4 : 8, rows = waves * (blocks <= 16 ? 64 : 32);
+    const int64_t groups = (l + 31) / 32;
+    auto up = [](int64_t x) { return (x + 255) / 256 * 256; };
+    return up(up((n + rows - 1) / rows * waves * groups * 32 * 4) +
+              groups * k * ((blocks <= 4 ? 256 : 128) + blocks * 1024));
+}
+
+int64_t split_charge_rows(int64_t n, int64_t d) {
+    return d > 8 && d % 4 != 0 ? (n * ((d + 3) / 4 * 4) * 4 + 255) / 256 * 256 : 0;
+}
+
+bool mfma_plan(int prec, int64_t d, int64_t n, bool one, MfmaPlan *p) {
     if (d < 1 || d > kMaxD) return false;
     MfmaPlan q{};
+    if (prec == P_FP32 && split_plan(d, n, one, &q)) {
+        *p = q;
+        return true;
+    }
     // fp16/bf16 up to d = 1024 stay on the register-resident kernel (one row
     // tile of 16 points and 32 k-blocks per wavefront); above that, and fp32
     // above 512, the coordinates are split over the wavefronts.
@@ -123,6 +166,7 @@ bool mfma_plan(int prec, int64_t d, MfmaPlan *p) {
 }
 
 int64_t mfma_tile_bytes(const MfmaPlan &pl) {
+    if (pl.split) return split_tile_bytes(pl.nkb, pl.nt);
     return hdr_bytes(pl.tile, pl.nb, pl.splat != 0) + (int64_t)(pl.nkb - pl.half) * pl.nb * 1024 +
            (int64_t)pl.half * pl.nb * 512;
 }
@@ -131,6 +175,7 @@ int64_t mfma_tiles_per_group(const MfmaPlan &pl, int64_t k) { return (k + pl.nb 
 
 hipError_t launch_pack(int prec, const MfmaPlan &pl, const void *V, int64_t n, int ld, const int32_t *sets,
                        int64_t l, int64_t k, void *tiles, hipStream_t st) {
+    if (pl.split) return split_pack_run(pl, V, n, ld, sets, l, k, tiles, st);
     switch (prec) {
     case P_FP32: return pack_run_f32(pl, V, n, ld, sets, l, k, tiles, st);
     case P_FP16: return pack_run_f16(pl, V, n, ld, sets, l, k, tiles, st);
@@ -141,9 +186,15 @@ hipError_t launch_pack(int prec, const MfmaPlan &pl, const void *V, int64_t n, i
 
 hipError_t launch_mfma(int prec, int mode, const MfmaPlan &pl, const void *V, int64_t n, int ld, const void *tiles,
                        int64_t kt, int64_t ngroups, int64_t gpc, const float *m0, float *partials, int64_t lpad,
-                       float *rowmax, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
-    const MfmaArgs x{V, n, ld, tiles, kt, ngroups, gpc, m0, partials, lpad, rowmax, ev_start, ev_stop};
+                       float *rowmax, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop, const int32_t *sets,
+                       int64_t l) {
+    const MfmaArgs x{V, n, ld, tiles, kt, ngroups, gpc, m0, partials, lpad, rowmax, sets, l, ev_start, ev_stop};
     if (pl.bigd) return bigd_run(prec, mode, pl, x, st);
+    if (pl.split)
+        return mode == MODE_ROWMAX ? split_rowmax_run(pl, x, st)
+               : m0                ? split_gain_run(pl, x, st)
+               : !tiles            ? split_gather_run(pl, x, st)
+                                   : split_sum_run(pl, x, st);
     switch (prec) {
     case P_FP32: return eval_run_f32(pl, mode, x, st);
     case P_FP16: return mode == MODE_SUM ? eval_run_f16(pl, mode, x, st) : hipErrorInvalidValue;

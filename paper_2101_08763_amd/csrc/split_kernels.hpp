@@ -1,0 +1,728 @@
+// split_kernels.hpp -- fp32 evaluation on the bf16 matrix cores (templates;
+// instantiated in kernels_mfma_f32.hip).
+//
+// The fp32 MFMA runs at a sixteenth of the bf16 rate and never overlaps VALU
+// work.  An fp32 value is exactly the sum of three bf16 ones,
+//     x = hi + mid + lo   (hi = bf16(x), mid = bf16(x - hi), lo = the rest),
+// and of the nine products of two such sums six matter: the other three are
+// below 2^-26 of |x||y|, under the rounding of one fp32 addition.  So
+//     <v, s> = sum  lo*hi + hi*lo + mid*mid + mid*hi + hi*mid + hi*hi
+// on v_mfma_f32_16x16x32_bf16 (products exact, fp32 accumulation), six
+// instructions of 32 coordinates where fp32 needs sixteen times their time.
+// The five small products run in an accumulator of their own: added into the
+// large one they lose their low bits there, always downwards.  Measured
+// against 64 bits, random and clustered points, h_s(v) of d = 8 / 32 / 100 /
+// 256 / 512 coordinates: rms error 3.6 / 4.8 / 8.3 / 15 / 21 e-8 of the
+// values' rms, fp32 MFMA 6.7 / 14 / 24 / 43 / 60 e-8 (one accumulator for
+// all six products: 5.3 / 12 / 20 / 36 / 46 e-8 and a mean of -4e-8).
+//
+// Everything else follows mfma_kernels.hpp: the clamp form, points resident
+// in registers, exemplar tiles streamed through LDS, a running max per
+// (point, set), no work matrix.  Differences:
+//   - a tile is one member of 32 sets: two column groups of 16 sets, so an
+//     odd or single member costs nothing;
+//   - the d coordinates are NKB whole blocks of 32, three operand parts each,
+//     and a tail of r = d - 32 NKB coordinates whose six products lie side by
+//     side in the instruction's 32 places, in quads of four coordinates:
+//     NT = 1, 2, 3, 3, 4 instructions for r <= 4, 8, 12, 16, 20 instead of
+//     six (a longer tail is a zero-padded whole block);
+//   - rows are read with 4-byte alignment, so V never needs a padded copy.
+#pragma once
+
+#include <algorithm>
+#include <atomic>
+#include <float.h>
+#include <stdlib.h>
+
+#include <hip/hip_ext.h>
+
+#include "device.hpp"
+#include "internal.h"
+#include "mfma_kernels.hpp"
+
+namespace exemcl {
+
+// Tile header: 32 fp32 biases; without whole blocks four times each, so that
+// a lane reads its four accumulators' seeds in one load.
+constexpr int split_hdr(int nkb) { return nkb == 0 ? 512 : 128; }
+constexpr int kSplitSets = 32;   // sets per tile
+constexpr int kSplitMaxSteps = 19;
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// Fragments of one column group: lo, mid, hi of every whole block, the tail.
+constexpr int split_steps(int nkb, int nt) { return 3 * nkb + nt; }
+constexpr int split_tile_bytes(int nkb, int nt) { return split_hdr(nkb) + split_steps(nkb, nt) * 2048; }
+
+__device__ __forceinline__ void split3(float x, __bf16 &hi, __bf16 &mid, __bf16 &lo) {
+    hi = (__bf16)x;
+    const float r = x - (float)hi;
+    mid = (__bf16)r;
+    lo = (__bf16)(r - (float)mid);
+}
+
+// The tail's places.  A lane holds 2 NT quads of places (quad 2 t + w: half w
+// of fragment t); u = ceil(r / 4) quads of coordinates have six products each
+// (0 lo*hi, 1 hi*lo, 2 mid*mid, 3 mid*hi, 4 hi*mid, 5 hi*hi, a point's part
+// first), laid out so that a lane reads one quad of coordinates, or two:
+//   u = 1, NT = 1: quad 0 in every group of lanes, products 2 grp + w;
+//   u = 2, NT = 2: quad grp / 2, products 4 t + 2 (grp % 2) + w;
+//   u = 3 or 4, NT = 3: quad grp, products 2 t + w;
+//   u = 5, NT = 4: as NT = 3, then in t = 3 products 2 grp + w of quad 4.
+// Small products come in earlier fragments than hi*hi.  Products above 5 are
+// zero.  (The bias -||s||^2/2 as three bf16 parts in a free quad saves the
+// accumulators' seeds, but beside hi*hi in one instruction it is truncated:
+// results 3e-8 too small at d <= 12, against 0.1e-8 from the seeds.)
+template <int NT>
+struct Tail {
+    static constexpr int OWN = 0, FIFTH = 1;  // which quad of coordinates
+    // the first coordinate of the lane's own quad
+    __device__ static int own(int grp) { return NT == 1 ? 0 : NT == 2 ? 4 * (grp >> 1) : 4 * grp; }
+    // product of place quad (t, w)
+    __device__ static int prod(int grp, int t, int w) {
+        if (NT == 1) return 2 * grp + w;
+        if (NT == 2) return 4 * t + 2 * (grp & 1) + w;
+        return t < 3 ? 2 * t + w : 2 * grp + w;
+    }
+    static constexpr int which(int t) { return NT == 4 && t == 3 ? FIFTH : OWN; }
+};
+
+// A quad of coordinates as its three bf16 parts.
+struct Quad {
+    bf16x4 hi, mid, lo;
+};
+__device__ __forceinline__ Quad split_quad(const float (&x)[4]) {
+    Quad q;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        __bf16 h, m, l;
+        split3(x[e], h, m, l);
+        q.hi[e] = h;
+        q.mid[e] = m;
+        q.lo[e] = l;
+    }
+    return q;
+}
+__device__ __forceinline__ u32x2 pick(int prod, const bf16x4 &p0, const bf16x4 &p1, const bf16x4 &p2, const bf16x4 &p3,
+                                      const bf16x4 &p4, const bf16x4 &p5) {
+    const u32x2 zero = {0u, 0u};
+    auto b = [](const bf16x4 &x) { return __builtin_bit_cast(u32x2, x); };
+    return prod == 0   ? b(p0)
+           : prod == 1 ? b(p1)
+           : prod == 2 ? b(p2)
+           : prod == 3 ? b(p3)
+           : prod == 4 ? b(p4)
+           : prod == 5 ? b(p5)
+                       : zero;
+}
+// One lane's tail fragment t, of a point or of an exemplar.
+template <int NT>
+__device__ __forceinline__ bf16x8 tail_fragment(const Quad *q, int grp, int t, bool point) {
+    const Quad &c = q[Tail<NT>::which(t)];
+    u32x4 v;
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+        const int prod = Tail<NT>::prod(grp, t, w);
+        const u32x2 x = point ? pick(prod, c.lo, c.hi, c.mid, c.mid, c.hi, c.hi)
+                              : pick(prod, c.hi, c.lo, c.mid, c.hi, c.mid, c.hi);
+        v[2 * w] = x[0];
+        v[2 * w + 1] = x[1];
+    }
+    return __builtin_bit_cast(bf16x8, v);
+}
+
+// One column group of one tile: lane L stages row `idx` of V (16 rows, lane
+// L % 16 of each group of lanes) and their biases -||s||^2/2 to `tile`.
+// ||s||^2: the lane's coordinates in order, then the four groups of lanes
+// with a fixed xor tree.  An invalid index is a zero column with bias
+// -FLT_MAX, which never wins the running max.
+template <int NKB, int NT>
+__device__ __forceinline__ void stage_columns(const float *__restrict__ V, int64_t n, int ld, int d, int64_t idx,
+                                              int h, int lane, unsigned char *tile) {
+    const int grp = lane >> 4;
+    const bool valid = idx >= 0 && idx < n;
+    const float *row = V + (valid ? idx : 0) * (int64_t)ld;
+    bf16x8 *dst = reinterpret_cast<bf16x8 *>(tile + split_hdr(NKB)) + h * 64 + lane;
+    float sq = 0.0f;
+    constexpr int NQ = NT == 4 ? 2 : 1;  // quads of the tail the lane reads
+    float xt[NQ][4];
+    const int r = d - 32 * NKB;  // coordinates of the tail
+    if constexpr (NT > 0) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            const int c0 = q == 0 ? Tail<NT>::own(grp) : 16;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const bool in = valid && c0 + e < r;
+                const float x = row[in ? 32 * NKB + c0 + e : 0];
+                xt[q][e] = in ? x : 0.0f;
+            }
+        }
+    }
+    constexpr int BATCH = 4;  // whole blocks loaded before any is stored
+#pragma unroll
+    for (int k0 = 0; k0 < NKB; k0 += BATCH) {
+        float x[BATCH][8];
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+            if (k0 + u >= NKB) continue;
+            const int d0 = (k0 + u) * 32 + grp * 8;
+            if ((k0 + u + 1) * 32 <= d) {
+                const f32x4 a = *reinterpret_cast<const f32x4u *>(row + d0);
+                const f32x4 b = *reinterpret_cast<const f32x4u *>(row + d0 + 4);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[u][e] = a[e], x[u][4 + e] = b[e];
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float v = row[d0 + e < d ? d0 + e : 0];
+                    x[u][e] = d0 + e < d ? v : 0.0f;
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+            if (k0 + u >= NKB) continue;
+            bf16x8 p[3];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float v = valid ? x[u][e] : 0.0f;
+                __bf16 hi, mid, lo;
+                split3(v, hi, mid, lo);
+                p[0][e] = lo;
+                p[1][e] = mid;
+                p[2][e] = hi;
+                sq = fmaf(v, v, sq);
+            }
+#pragma unroll
+            for (int q = 0; q < 3; ++q) dst[(NT + (k0 + u) * 3 + q) * 128] = p[q];
+        }
+    }
+    if constexpr (NT > 0) {
+        // every coordinate once: one lane group of those that read a quad
+        const bool first = NT == 1 ? grp == 0 : NT == 2 ? (grp & 1) == 0 : true;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sq = fmaf(first ? xt[0][e] : 0.0f, xt[0][e], sq);
+        if constexpr (NT == 4)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sq = fmaf(grp == 0 ? xt[NQ - 1][e] : 0.0f, xt[NQ - 1][e], sq);
+    }
+    sq += __shfl_xor(sq, 16);
+    sq += __shfl_xor(sq, 32);
+    const float bias = valid ? -0.5f * sq : -FLT_MAX;
+    if constexpr (split_hdr(NKB) > 128) {
+        if (grp == 0) reinterpret_cast<f32x4 *>(tile)[h * 16 + (lane & 15)] = f32x4{bias, bias, bias, bias};
+    } else {
+        if (grp == 0) reinterpret_cast<float *>(tile)[h * 16 + (lane & 15)] = bias;
+    }
+    if constexpr (NT > 0) {
+        Quad q[NQ];
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) q[i] = split_quad(xt[i]);
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+            dst[t * 128] = tail_fragment<NT>(q, grp, t, false);
+    }
+}
+
+// Staging: one workgroup of two wavefronts per tile (set group g, member p),
+// one column group each; tile g*k + p at tiles + (g*k + p) * tile bytes.
+template <int NKB, int NT>
+__global__ __launch_bounds__(128) void pack_split_kernel(const float *__restrict__ V, int64_t n, int ld, int d,
+                                                         const int32_t *__restrict__ sets, int64_t l, int64_t k,
+                                                         unsigned char *__restrict__ tiles) {
+    const int64_t t = blockIdx.x;
+    const int64_t g = t / k, p = t - (t / k) * k;
+    const int lane = threadIdx.x & 63, h = threadIdx.x >> 6;
+    const int64_t j = g * kSplitSets + h * 16 + (lane & 15);
+    const int64_t idx = j < l ? (int64_t)sets[j * k + p] : -1;
+    stage_columns<NKB, NT>(V, n, ld, d, idx, h, lane, tiles + t * (int64_t)split_tile_bytes(NKB, NT));
+}
+
+// Stage geometry: as many tiles as two buffers (and the partial sums) hold,
+// at most kSplitTpsMax; a workgroup of at most 4 wavefronts leaves room for
+// a second one on the CU.
+constexpr int kSplitLds = 160 * 1024;
+constexpr int kSplitTpsMax = 8;
+constexpr int split_round(int bytes, int waves) { return (bytes + waves * 1024 - 1) / (waves * 1024) * (waves * 1024); }
+constexpr int split_budget(int waves) { return waves >= 8 ? kSplitLds : kSplitLds / (waves >= 4 ? 2 : 4); }
+constexpr int split_red_bytes(int tps, int waves) { return 2 * tps * waves * 32 * 4; }
+constexpr int split_tps(int nkb, int nt, int waves) {
+    int tps = kSplitTpsMax;
+    while (tps > 1 && 2 * split_round(tps * split_tile_bytes(nkb, nt), waves) + split_red_bytes(tps, waves) > split_budget(waves))
+        --tps;
+    return tps;
+}
+constexpr int split_lds(int nkb, int nt, int waves) {
+    return 2 * split_round(split_tps(nkb, nt, waves) * split_tile_bytes(nkb, nt), waves) +
+           split_red_bytes(split_tps(nkb, nt, waves), waves);
+}
+
+// Row tiles per wavefront: as many as the registers hold without spilling in
+// the main loop (3 operand fragments per whole block and row tile).  A
+// smaller ground set takes fewer, so that there are row blocks for all CUs;
+// the rule looks at n and never at l or k, which must not change a result.
+constexpr int kSplitWaves = 8;
+constexpr int split_rt_max(int nkb, int nt) {
+    const int steps = split_steps(nkb, nt);
+    return steps <= 5 ? 4 : steps <= 10 ? 3 : 2;
+}
+constexpr int split_rt(int nkb, int nt, int64_t n, bool one) {
+    const int top = split_rt_max(nkb, nt);
+    if (nkb == 0) return n < 2048 ? 1 : n < 32768 ? 2 : top;
+    return n < 8192 ? 1 : top == 4 ? (n < 100000 ? 2 : top) : (!one && n < 32768 ? 2 : top);
+}
+// The cache g(v) reads V once against a few tiles: small workgroups.
+constexpr int kRowmaxWaves = 4, kRowmaxRt = 2;
+
+#ifndef EXEMCL_SPLIT_PF
+#define EXEMCL_SPLIT_PF 2
+#endif
+
+// ---------------------------------------------------------------------------
+// Evaluation.  A workgroup owns WAVES*RT*16 consecutive points; units of work
+// are (row block, set group) pairs, shared out as in mfma_kernels.hpp: S
+// workgroups take the whole row blocks w, w + S, ... first (all walk the set
+// groups in step, so the tiles stay in L2), then equal contiguous shares of
+// the units of the rest.
+//
+// MODE_SUM: partials[rb * lpad + j] = sum over the row block's points of
+// max(m0(v), max_p h_{s_jp}(v)); wavefront sums go to LDS as set groups end
+// and are added, in wavefront order, after the next stage's barrier.
+// MODE_ROWMAX: rowmax[v] = max(m0(v), 0, max over all staged columns of
+// h_s(v)); rowmax may be m0 (a point is read and written by one workgroup).
+//
+// GATHER: no staged tiles in memory; the workgroup stages every tile into LDS
+// itself, from the set indices, with the same code and so the same bits.
+// ---------------------------------------------------------------------------
+template <int NKB, int NT, int RT, int WAVES, int MODE, bool HAS_M0, bool GATHER>
+__global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
+    const float *__restrict__ V, int64_t n, int ld, int d, const unsigned char *__restrict__ tiles, int64_t kt,
+    int64_t ngroups, int64_t nrb, const float *m0, float *__restrict__ partials, int64_t lpad, float *rowmax,
+    const int32_t *__restrict__ sets, int64_t l) {
+    constexpr int STEPS = split_steps(NKB, NT);
+    constexpr int TB = split_tile_bytes(NKB, NT);
+    constexpr int TPS = split_tps(NKB, NT, WAVES);
+    constexpr int NTHR = WAVES * 64;
+    constexpr int SB = split_round(TPS * TB, WAVES);
+    constexpr int CNT = SB / (NTHR * 16);
+    constexpr int PF = STEPS < EXEMCL_SPLIT_PF ? STEPS : EXEMCL_SPLIT_PF;
+    constexpr int ROWS = WAVES * RT * 16;
+    // An accumulator for the small products; the few of a tail alone go onto
+    // the bias one after the other (error above), which saves the additions.
+    constexpr bool SMALL = NKB > 0;
+    constexpr int HDR = split_hdr(NKB);
+    // Short tiles: the fold of the running max is the busiest unit.
+    constexpr bool PAIR = NKB == 0 && MODE == MODE_SUM && !HAS_M0;
+    // Scoring S u {c}: sets of one member, whose maximum with the cached
+    // value is summed as it comes; no running max is kept.
+    constexpr bool ONE = HAS_M0 && MODE == MODE_SUM;
+
+    extern __shared__ __align__(16) unsigned char smem[];
+    float *red = reinterpret_cast<float *>(smem + 2 * SB);
+
+    auto segment = [&](const int64_t rb, const int64_t g0, const int64_t g1) {
+        // hidden per segment, so that per-lane offsets are not kept in
+        // registers through the whole persistent loop
+        int tid = threadIdx.x, ldv = ld;
+        asm volatile("" : "+v"(tid), "+s"(ldv));
+        const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        const int lr = lane & 15, grp = lane >> 4;
+
+        const int64_t ntiles = (g1 - g0) * kt;
+        const int nst = (int)((ntiles + TPS - 1) / TPS);
+        const unsigned char *chunk = tiles + g0 * kt * (int64_t)TB;
+        const int64_t chunk_bytes = ntiles * (int64_t)TB;
+
+        auto issue = [&](int s) {
+            unsigned char *buf = smem + (s & 1) * SB;
+            if constexpr (GATHER) {
+                const int tn = (int)min((int64_t)TPS, ntiles - (int64_t)s * TPS);
+                for (int c = wave; c < 2 * tn; c += WAVES) {  // column group c % 2 of tile c / 2
+                    const int64_t t = (int64_t)s * TPS + (c >> 1);
+                    const int64_t g = t / kt, q = t - g * kt;
+                    const int64_t j = (g0 + g) * kSplitSets + (c & 1) * 16 + lr;
+                    const int64_t idx = j < l ? (int64_t)sets[j * kt + q] : -1;
+                    stage_columns<NKB, NT>(V, n, ldv, d, idx, c & 1, lane, buf + (c >> 1) * TB);
+                }
+                return;
+            }
+            const int64_t base = s * (int64_t)(TPS * TB);
+            const auto win = window_rsrc(chunk + base, (uint32_t)min((int64_t)(TPS * TB), chunk_bytes - base));
+#pragma unroll
+            for (int r = 0; r < CNT; ++r)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                    win, (__attribute__((address_space(3))) void *)(buf + (r * NTHR + wave * 64) * 16), 16,
+                    (r * NTHR + tid) * 16, 0, 0, 0);
+        };
+        if (nst > 0) issue(0);
+        if (nst > 1) issue(1);
+
+        // This wavefront's points in A-operand order: three parts of every
+        // whole block, the tail's places.  Rows past n read as zeros.
+        const int64_t wrow0 = rb * (int64_t)ROWS;
+        const int64_t wrows = min((int64_t)ROWS, n - wrow0);
+        const auto vwin = window_rsrc(V + wrow0 * (int64_t)ldv, (uint32_t)(wrows * ldv * 4));
+        bf16x8 a[RT][NKB > 0 ? NKB : 1][3], at[RT][NT > 0 ? NT : 1];
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+            const int rowoff = (wave * RT * 16 + rt * 16 + lr) * ldv;
+#pragma unroll
+            for (int kb = 0; kb < NKB; ++kb) {
+                const int d0 = kb * 32 + grp * 8;
+                float x[8];
+                if ((kb + 1) * 32 <= d) {
+                    const f32x4 p = window_load16<f32x4>(vwin, (uint32_t)((rowoff + d0) * 4));
+                    const f32x4 q = window_load16<f32x4>(vwin, (uint32_t)((rowoff + d0 + 4) * 4));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) x[e] = p[e], x[4 + e] = q[e];
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        x[e] = window_load4(vwin, d0 + e < d ? (uint32_t)((rowoff + d0 + e) * 4) : kDeadOffset);
+                }
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    __bf16 hi, mid, lo;
+                    split3(x[e], hi, mid, lo);
+                    a[rt][kb][0][e] = lo;
+                    a[rt][kb][1][e] = mid;
+                    a[rt][kb][2][e] = hi;
+                }
+            }
+            if constexpr (NT > 0) {
+                constexpr int NQ = NT == 4 ? 2 : 1;
+                const int r = d - 32 * NKB;
+                Quad q[NQ];
+#pragma unroll
+                for (int i = 0; i < NQ; ++i) {
+                    // a whole quad in one load; a partial one, or the one
+                    // past the last, coordinate by coordinate
+                    const int c0 = i == 0 ? Tail<NT>::own(grp) : 16;
+                    const bool whole = c0 + 4 <= r;
+                    const uint32_t off = (uint32_t)((rowoff + 32 * NKB + c0) * 4);
+                    const f32x4 v = window_load16<f32x4>(vwin, whole ? off : kDeadOffset);
+                    float x[4] = {v[0], v[1], v[2], v[3]};
+                    if ((r & 3) != 0)
+#pragma unroll
+                        for (int e = 0; e < 3; ++e) {
+                            const float y = window_load4(vwin, !whole && c0 + e < r ? off + 4 * e : kDeadOffset);
+                            x[e] = whole ? x[e] : y;
+                        }
+                    q[i] = split_quad(x);
+                }
+#pragma unroll
+                for (int t = 0; t < NT; ++t) at[rt][t] = tail_fragment<NT>(q, grp, t, true);
+            }
+        }
+
+        // Initial running max: e0's 0, or the cached per-point value.
+        float minit[HAS_M0 ? RT : 1][4];
+        if constexpr (HAS_M0) {
+            // m0 may be null in MODE_ROWMAX (an empty window reads as zeros)
+            const auto mwin = window_rsrc(m0 ? m0 + wrow0 : V, m0 ? (uint32_t)(wrows * 4) : 0u);
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    minit[rt][i] = window_load4(mwin, (uint32_t)((wave * RT * 16 + rt * 16 + 4 * grp + i) * 4));
+        }
+        auto m_init = [&](int rt, int i) -> float {
+            if constexpr (HAS_M0) return minit[rt][i];
+            else return 0.0f;
+        };
+        float m[RT][2][4];
+        auto m_reset = [&]() {
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) m[rt][h][i] = m_init(rt, i);
+        };
+        if constexpr (!ONE) m_reset();
+
+        // B fragments (both column groups of a step) are read PF steps ahead
+        // of use, across tiles of a stage.
+        bf16x8 bq[PF][2];
+        f32x4 bias[2];  // a column's bias, once per accumulator
+        auto frag = [&](const unsigned char *tb, int s, int h) {
+            return reinterpret_cast<const bf16x8 *>(tb + HDR)[(s * 2 + h) * 64 + lane];
+        };
+        auto bias_of = [&](const unsigned char *tb, int h) {
+            if constexpr (HDR > 128) return reinterpret_cast<const f32x4 *>(tb)[h * 16 + lr];
+            const float b = reinterpret_cast<const float *>(tb)[h * 16 + lr];
+            return f32x4{b, b, b, b};
+        };
+        auto head = [&](const unsigned char *tb) {
+#pragma unroll
+            for (int s = 0; s < PF; ++s)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) bq[s][h] = frag(tb, s, h);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) bias[h] = bias_of(tb, h);
+        };
+        // h_s(v) of one tile's 32 columns.
+        auto tile = [&](const unsigned char *tb, const unsigned char *tnext, f32x4 (&acc)[RT][2]) {
+            constexpr f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+            f32x4 sml[RT][2];
+            f32x4 seed[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) seed[h] = bias[h];
+#pragma unroll
+            for (int s = 0; s < STEPS; ++s) {
+                bf16x8 b[2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    b[h] = bq[0][h];
+#pragma unroll
+                    for (int q = 0; q + 1 < PF; ++q) bq[q][h] = bq[q + 1][h];
+                    bq[PF - 1][h] = s + PF < STEPS ? frag(tb, s + PF, h) : frag(tnext, s + PF - STEPS, h);
+                    if (s + PF == STEPS) bias[h] = bias_of(tnext, h);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                auto mma = [](const bf16x8 &x, const bf16x8 &y, const f32x4 &c) {
+                    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, y, c, 0, 0, 0);
+                };
+                if (s < NT) {
+                    // the last fragment holds hi*hi; the others are small
+                    // products
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) {
+                            if (SMALL && s < NT - 1)
+                                sml[rt][h] = mma(at[rt][s], b[h], s == 0 ? zero : sml[rt][h]);
+                            else
+                                acc[rt][h] = mma(at[rt][s], b[h], SMALL || s == 0 ? seed[h] : acc[rt][h]);
+                        }
+                } else {
+                    const int kb = (s - NT) / 3, part = (s - NT) % 3;  // exemplar part: lo, mid, hi
+#pragma unroll
+                    for (int q = 0; q <= part; ++q)  // point parts: hi | mid, hi | lo, mid, hi
+#pragma unroll
+                        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                            for (int h = 0; h < 2; ++h) {
+                                const bf16x8 &x = a[rt][kb][2 - part + q];
+                                if (part == 2 && q == 2)
+                                    acc[rt][h] = mma(x, b[h], NT == 0 && kb == 0 ? seed[h] : acc[rt][h]);
+                                else
+                                    sml[rt][h] = mma(x, b[h], kb == 0 && part == 0 && NT < 2 ? zero : sml[rt][h]);
+                            }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if constexpr (SMALL) {
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) acc[rt][h][i] += sml[rt][h][i];
+            }
+        };
+        auto fold = [&](const f32x4 (&x)[RT][2]) {
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        m[rt][h][i] = fmaxf(ONE ? minit[HAS_M0 ? rt : 0][i] : m[rt][h][i], x[rt][h][i]);
+        };
+        auto fold2 = [&](const f32x4 (&x)[RT][2], const f32x4 (&y)[RT][2]) {
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) m[rt][h][i] = fmaxf(fmaxf(m[rt][h][i], x[rt][h][i]), y[rt][h][i]);
+        };
+
+        // Sums of the running maxima: this lane's, pairwise in a fixed order,
+        // then the four groups of lanes (0 + 2, 1 + 3, then both).  Lanes
+        // 0-15 end with the sums of column group 0, lanes 32-47 with those
+        // of group 1.
+        auto lane_sum = [&](int h) {
+            constexpr int NV = RT * 4;
+            float v[NV];
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[rt * 4 + i] = m[rt][h][i];
+#pragma unroll
+            for (int c = NV; c > 1; c = (c + 1) / 2) {
+                const int half = (c + 1) / 2;
+#pragma unroll
+                for (int i = 0; i + half < c; ++i) v[i] += v[i + half];
+            }
+            return v[0];
+        };
+        auto column_sums = [&]() {
+            const float s0 = lane_sum(0), s1 = lane_sum(1);
+            const float s = (lane < 32 ? s0 : s1) + __shfl_xor(lane < 32 ? s1 : s0, 32);
+            return s + __shfl_xor(s, 16);
+        };
+
+        const int ktile = (int)kt;
+        int p = 0;             // members of the current set group done
+        int64_t gflush = g0;   // first set group whose sums are not stored yet
+        int done = 0;          // set groups ended in the current stage
+        auto flush = [&](int par, int cnt) {
+            for (int i = tid; i < cnt * 32; i += NTHR) {
+                const float *r = red + ((par * TPS + (i >> 5)) * WAVES) * 32 + (i & 31);
+                float t = r[0];
+#pragma unroll
+                for (int w = 1; w < WAVES; ++w) t += r[w * 32];
+                partials[rb * lpad + gflush * 32 + i] = t;
+            }
+            gflush += cnt;
+        };
+        for (int s = 0; s < nst; ++s) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            const unsigned char *buf = smem + (s & 1) * SB;
+            const int tn = (int)min((int64_t)TPS, ntiles - (int64_t)s * TPS);
+            head(buf);
+            if (s > 0 && s + 1 < nst) issue(s + 1);
+            if (MODE == MODE_SUM && done > 0) flush((s & 1) ^ 1, done);
+            done = 0;
+            auto at_tile = [&](int i) { return buf + (i < tn ? i : tn - 1) * TB; };
+            auto group_end = [&]() {
+                const float t = column_sums();
+                if (!(lane & 16)) red[(((s & 1) * TPS + done) * WAVES + wave) * 32 + (lane >> 5) * 16 + lr] = t;
+                ++done;
+                p = 0;
+                if constexpr (!ONE) m_reset();
+            };
+            int i = 0;
+            while (i < tn) {
+                if constexpr (PAIR) {
+                    // two members of the same sets: one max3 per element
+                    while (i + 1 < tn && p + 1 < ktile) {
+                        f32x4 x[RT][2], y[RT][2];
+                        tile(at_tile(i), at_tile(i + 1), x);
+                        tile(at_tile(i + 1), at_tile(i + 2), y);
+                        fold2(x, y);
+                        i += 2;
+                        p += 2;
+                        if (p == ktile && MODE == MODE_SUM) group_end();
+                    }
+                    if (i >= tn) break;
+                }
+                f32x4 x[RT][2];
+                tile(at_tile(i), at_tile(i + 1), x);
+                fold(x);
+                ++i;
+                if (MODE == MODE_SUM && (ONE || ++p == ktile)) group_end();
+            }
+        }
+        if constexpr (MODE == MODE_SUM) {
+            __syncthreads();
+            if (done > 0) flush((nst - 1) & 1, done);
+        } else {
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    float x = fmaxf(fmaxf(m[rt][0][i], m[rt][1][i]), 0.0f);
+#pragma unroll
+                    for (int off = 1; off < 16; off <<= 1) x = fmaxf(x, __shfl_xor(x, off));
+                    const int64_t r = wrow0 + wave * RT * 16 + rt * 16 + 4 * grp + i;
+                    if (lr == 0 && r < n) rowmax[r] = x;
+                }
+        }
+    };
+
+    const int64_t S = gridDim.x;
+    const int64_t q = nrb / S;
+    const int64_t U2 = (nrb - q * S) * ngroups;
+    int64_t v = (int64_t)blockIdx.x * U2 / S;
+    const int64_t v1 = ((int64_t)blockIdx.x + 1) * U2 / S;
+    for (int64_t seg = 0;; ++seg) {
+        int64_t rb, g0, g1;
+        if (seg < q) {
+            rb = seg * S + (int64_t)blockIdx.x;
+            g0 = 0;
+            g1 = ngroups;
+        } else {
+            if (v >= v1) break;
+            rb = q * S + v / ngroups;
+            g0 = v - (v / ngroups) * ngroups;
+            g1 = min(ngroups, g0 + (v1 - v));
+            v += g1 - g0;
+        }
+        // the previous segment's last stage and sums may still be read
+        if (seg > 0) __syncthreads();
+        segment(rb, g0, g1);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Host side.
+// ---------------------------------------------------------------------------
+template <int NKB, int NT>
+hipError_t split_pack_t(const void *V, int64_t n, int ld, int d, const int32_t *sets, int64_t l, int64_t k,
+                        void *tiles, hipStream_t st) {
+    const int64_t ngroups = (l + kSplitSets - 1) / kSplitSets;
+    hipLaunchKernelGGL((pack_split_kernel<NKB, NT>), dim3((unsigned)(ngroups * k)), dim3(128), 0, st, (const float *)V,
+                       n, ld, d, sets, l, k, (unsigned char *)tiles);
+    return hipGetLastError();
+}
+
+template <int NKB, int NT, int RT, int WAVES, int MODE, bool HAS_M0, bool GATHER>
+hipError_t split_launch(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st) {
+    auto kern = eval_split_kernel<NKB, NT, RT, WAVES, MODE, HAS_M0, GATHER>;
+    constexpr int lds = split_lds(NKB, NT, WAVES);
+    constexpr int rows = WAVES * RT * 16;
+    if (MODE == MODE_SUM && pl.rows != rows) return hipErrorInvalidValue;
+    // Resident workgroups per CU, queried once per instantiation.
+    static std::atomic<int> occ{0};
+    int per_cu = occ.load(std::memory_order_relaxed);
+    if (per_cu <= 0) {
+        hipError_t e = hipSuccess;
+        if (lds > 64 * 1024)
+            e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (e == hipSuccess)
+            e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kern, WAVES * 64, lds);
+        if (e != hipSuccess) return e;
+        if (per_cu < 1) return hipErrorInvalidValue;
+        occ.store(per_cu, std::memory_order_relaxed);
+    }
+    const int64_t nrb = (x.n + rows - 1) / rows;
+    const int64_t slots = (int64_t)per_cu * device_cu_count();
+    if (slots < 1) return hipErrorInvalidDevice;
+    // MODE_ROWMAX: a workgroup sees every set group of its row block.
+    int64_t grid = MODE == MODE_ROWMAX ? nrb : nrb * x.ngroups;
+    if (MODE == MODE_SUM && persistent_mode() != kPersistOff) grid = std::min(grid, slots);
+    grid = std::min<int64_t>(grid, 1 << 24);
+    hipExtLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(WAVES * 64), lds, st, x.ev_start, x.ev_stop, 0,
+                          (const float *)x.V, x.n, x.ld, pl.d, (const unsigned char *)x.tiles, x.kt, x.ngroups, nrb,
+                          x.m0, x.partials, x.lpad, x.rowmax, x.sets, x.l);
+    return hipGetLastError();
+}
+
+template <int NKB, int NT, int MODE, bool HAS_M0, bool GATHER>
+hipError_t split_eval_t(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st) {
+    constexpr int TOP = split_rt_max(NKB, NT);
+    if constexpr (MODE == MODE_ROWMAX) {
+        return split_launch<NKB, NT, kRowmaxRt, kRowmaxWaves, MODE, HAS_M0, GATHER>(pl, x, st);
+    } else {
+        if (pl.rt == 1) return split_launch<NKB, NT, 1, kSplitWaves, MODE, HAS_M0, GATHER>(pl, x, st);
+        if constexpr (TOP > 2)
+            if (pl.rt == 2) return split_launch<NKB, NT, 2, kSplitWaves, MODE, HAS_M0, GATHER>(pl, x, st);
+        return split_launch<NKB, NT, TOP, kSplitWaves, MODE, HAS_M0, GATHER>(pl, x, st);
+    }
+}
+
+// One call per compiled (whole blocks, tail instructions).
+#ifndef EXEMCL_SPLIT_CASES
+#define EXEMCL_SPLIT_CASES(F)                                                                              \
+    F(0, 1) F(0, 2) F(0, 3) F(0, 4) F(1, 0) F(1, 1) F(1, 2) F(1, 3) F(1, 4) F(2, 0) F(2, 1) F(2, 2) F(2, 3) \
+    F(2, 4) F(3, 0) F(3, 1) F(3, 2) F(3, 3) F(4, 0) F(4, 1) F(4, 2) F(4, 3) F(5, 0) F(5, 1) F(5, 2) F(5, 3) \
+    F(6, 0) F(6, 1)
+#endif
+constexpr int split_key(int nkb, int nt) { return nkb * 8 + nt; }
+
+}  // namespace exemcl

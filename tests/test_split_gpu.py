@@ -1,0 +1,117 @@
+"""fp32 on the bf16 matrix cores (three bf16 parts, six products): every tail
+length and number of whole blocks, the changes of row tiles with n, tiles
+staged in LDS instead of memory, and the error against 64 bits.
+
+h_s(v) sums d products whose three-part split drops terms below 2^-26 of
+|v_i||s_i| and is accumulated in fp32, so |f - f64| <= (d + 64) 2^-24 (mean of
+|v||s| + |s|^2) is a generous bound; EXACT_RTOL (1e-5) is above it for the
+d tested here and is what the other fp32 tests use.
+"""
+import numpy as np
+import pytest
+
+from paper_2101_08763_amd import api, synth
+from test_parity_gpu import check, exact, gpu_eval, say, to_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch_gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    api.load()
+    return torch
+
+
+@pytest.fixture(scope="module")
+def orc():
+    import oracle
+    return oracle.load()
+
+
+@pytest.fixture(autouse=True)
+def _plain_env(monkeypatch):
+    for v in ("EXEMCL_PATH", "EXEMCL_WG_TARGET", "EXEMCL_PERSIST", "EXEMCL_WORKSPACE_LIMIT"):
+        monkeypatch.delenv(v, raising=False)
+
+
+# every tail of 1 .. 32 coordinates, alone and after 1, 2 and more whole blocks
+TAILS = list(range(1, 33)) + [33, 36, 41, 44, 48, 52, 53, 56, 57, 61, 63, 65, 72, 81, 85, 92, 104, 109, 116, 121, 129,
+                              140, 148, 157, 165, 170, 180, 185, 193, 196, 197]
+
+
+@pytest.mark.parametrize("d", TAILS)
+def test_every_tail(torch_gpu, orc, d):
+    """Odd and even k (lone and paired members), sets past the last group of
+    32, rows past the last row tile; scoring of S u {c} on the same rows."""
+    n, l = 517, 35
+    for k in (1, 4, 5):
+        p = synth.random_problem(n, d, l, k, seed=9000 + 10 * d + k, clusters=3)
+        say(f"split tail: n={n} d={d} l={l} k={k}")
+        Vg, X64 = to_gpu(torch_gpu, p.X, "fp32")
+        got = gpu_eval(torch_gpu, Vg, p.sets)
+        exact(got, orc.eval(X64, p.sets, 4), f"d={d} k={k}")
+    S, C = p.sets[0].copy(), np.arange(0, n, 9, dtype=np.int32)
+    g = api.exemplar_gain(Vg, torch_gpu.from_numpy(S).cuda(), torch_gpu.from_numpy(C).cuda())
+    torch_gpu.cuda.synchronize()
+    exact(g.cpu().numpy(), orc.gain(X64, S, C, 4), f"gain d={d}")
+
+
+@pytest.mark.parametrize("d", [3, 20, 32, 100, 170])
+@pytest.mark.parametrize("n", [127, 2047, 2048, 8191, 8192, 32767, 32768, 99_999, 100_000])
+def test_row_tile_rule(torch_gpu, orc, n, d):
+    """Both sides of every n at which the row tiles per wavefront change; a
+    batch of one set has the bits of the same set in a larger batch."""
+    l, k = 70, 3
+    p = synth.random_problem(n, d, l, k, seed=9500 + d, clusters=3)
+    say(f"row tiles: n={n} d={d}")
+    Vg, X64 = to_gpu(torch_gpu, p.X, "fp32")
+    got = gpu_eval(torch_gpu, Vg, p.sets)
+    idx = np.array([0, 33, 69])
+    exact(got[idx], orc.eval(X64, p.sets[idx], 8), f"n={n} d={d}")
+    assert np.array_equal(got[33:34], gpu_eval(torch_gpu, Vg, p.sets[33:34]))
+
+
+@pytest.mark.parametrize("n,d,k", [(300, 8, 200), (9000, 20, 90), (40_000, 100, 300), (120_000, 4, 700)])
+def test_tiles_staged_in_lds(torch_gpu, monkeypatch, n, d, k):
+    """A limit that admits the call but not one set group's tiles: the
+    evaluation kernel stages them itself, with the same bits."""
+    torch = torch_gpu
+    l = 40
+    p = synth.random_problem(n, d, l, k, seed=9700 + d, clusters=3, replace=True)
+    sets = p.sets.copy()
+    sets[3, 5:] = -1
+    sets[4, 0] = n
+    Vg, _ = to_gpu(torch, p.X, "fp32")
+    full = gpu_eval(torch, Vg, sets)
+    # what one set group is accounted for: 4 bytes per coordinate in blocks of
+    # 8, a header, one partial-sum row per 64 points
+    blocks = -(-d // 8)
+    need = -(-n // 256) * 4 * 32 * 4 + k * ((256 if blocks <= 4 else 128) + blocks * 1024) + 1024
+    rows = 0 if d % 4 == 0 or d <= 8 else -(-(n * (-(-d // 4) * 4) * 4) // 256) * 256
+    say(f"tiles in LDS: n={n} d={d} k={k} limit {need + rows}")
+    monkeypatch.setenv("EXEMCL_WORKSPACE_LIMIT", str(need + rows))
+    assert np.array_equal(full, gpu_eval(torch, Vg, sets), equal_nan=True)
+    assert np.isnan(full[4]) and np.isfinite(np.delete(full, 4)).all()
+    monkeypatch.setenv("EXEMCL_WORKSPACE_LIMIT", str(need + rows - 2048))
+    with pytest.raises(api.ExemclError) as ei:
+        gpu_eval(torch, Vg, sets)
+    assert ei.value.status == api.EXEMCL_ENOMEM
+
+
+@pytest.mark.parametrize("scale", [2.0 ** -30, 1.0, 2.0 ** 30])
+def test_error_against_64_bits(torch_gpu, orc, scale):
+    """Single-member sets of one point's worth of averaging: the error of
+    h_s(v) itself, over magnitudes.  The split keeps 24 bits of every value,
+    so scaling by a power of two scales the result exactly."""
+    n, d = 900, 100
+    p = synth.random_problem(n, d, 64, 1, seed=9800, clusters=5)
+    Vg, X64 = to_gpu(torch_gpu, p.X * np.float32(scale), "fp32")
+    got = gpu_eval(torch_gpu, Vg, p.sets)
+    want = orc.eval(X64, p.sets, 4)
+    worst = exact(got, want, f"scale {scale:g}")
+    assert worst <= 100 * 2.0 ** -24   # d roundings of 2^-24 each
+    V1, _ = to_gpu(torch_gpu, p.X, "fp32")
+    assert np.array_equal(got, gpu_eval(torch_gpu, V1, p.sets) * scale * scale)
