@@ -74,6 +74,7 @@ struct Layout {
     int64_t G = 0, lpad = 0, ngroups = 0, gpc = 0;
     int64_t off_partials = 0, off_tiles = 0, bytes = 0;
     int64_t charge = 0;  // bytes the call is accounted for (split_charge; else `bytes`)
+    int64_t unit = 1;    // sets in the smallest chunk
 };
 
 int64_t tile_bytes(const MfmaPlan &mp) { return mfma_tile_bytes(mp); }
@@ -103,6 +104,7 @@ bool layout_eval(int64_t n, int64_t d, int64_t l, int64_t k, int precision, int 
         L->off_tiles = align_up(L->G * L->lpad * 4, 256);
         L->bytes = align_up(L->off_tiles + L->ngroups * mfma_tiles_per_group(L->mp, k) * tile_bytes(L->mp), 256);
         L->charge = L->mp.split ? split_charge(n, d, l, k) : L->bytes;
+        L->unit = L->mp.split ? split_charge_unit(d) : tm;
         return true;
     }
     if (path == EXEMCL_PATH_VALU) {
@@ -473,7 +475,7 @@ int run_eval(const void *V, int64_t n, int64_t d, const int32_t *sets, int64_t l
     if (k > 0 && path == EXEMCL_PATH_NONE) return EXEMCL_EINVAL;
     Layout L;
     if (!layout_eval(n, d, l, k, precision, path, &L, one)) return EXEMCL_EINVAL;
-    const int64_t unit = path == EXEMCL_PATH_MFMA ? L.mp.tile : 1;
+    const int64_t unit = L.unit;
     MfmaRows own;
     if (path == EXEMCL_PATH_MFMA && !rows) {
         const int64_t pb = charge_rows(precision, n, d);
@@ -937,14 +939,14 @@ EXEMCL_API int exemplar_greedy(const float *V, int64_t n, int64_t d, int64_t K, 
     Scratch ws;
     for (;;) {
         if (!layout_eval(n, d, lc, 1, EXEMCL_FP32, EXEMCL_PATH_MFMA, &L, true)) return EXEMCL_EINVAL;
-        const bool small = std::max(L.bytes, L.charge) <= kScoringBytes || lc <= mp.tile;
-        if (small && fixed + L.charge <= limit && (fixed + L.bytes <= limit || lc <= mp.tile)) {
+        const bool small = std::max(L.bytes, L.charge) <= kScoringBytes || lc <= L.unit;
+        if (small && fixed + L.charge <= limit && (fixed + L.bytes <= limit || lc <= L.unit)) {
             rc = alloc_scratch(&ws, fixed + L.bytes, st);
             if (rc == EXEMCL_OK) break;
             if (rc != EXEMCL_ENOMEM) return rc;
         }
-        if (lc <= mp.tile) return EXEMCL_ENOMEM;
-        lc = ((lc + 1) / 2 + mp.tile - 1) / mp.tile * mp.tile;
+        if (lc <= L.unit) return EXEMCL_ENOMEM;
+        lc = ((lc + 1) / 2 + L.unit - 1) / L.unit * L.unit;
     }
     char *base = (char *)ws.ptr;
     int32_t *cands = (int32_t *)base;

@@ -132,12 +132,14 @@ hipError_t launch_mfma(int prec, int mode, const MfmaPlan &pl, const void *V, in
                        const int32_t *sets = nullptr, int64_t l = 0);
 
 // Bytes a call on the split kernels is accounted for: what decides whether it
-// fits a limit, and into how many chunks it is cut.  Four bytes per staged
-// coordinate (8 to a block) and one partial-sum row per 64 points (32 above
-// d = 128), plus a copy of V whose rows are not whole 16-byte vectors
+// fits a limit, and into how many chunks (of split_charge_unit sets at least)
+// it is cut.  Four bytes per staged coordinate (8 to a block, 16 above d =
+// 256) and one partial-sum row per 64 points (32 above d = 128, 16 above
+// 256), plus a copy of V whose rows are not whole 16-byte vectors
 // (split_charge_rows), as the entry points' limits are stated; the kernels
 // hold less, or, where six bytes per coordinate are more, stage tiles in LDS.
 int64_t split_charge(int64_t n, int64_t d, int64_t l, int64_t k);
+int64_t split_charge_unit(int64_t d);
 int64_t split_charge_rows(int64_t n, int64_t d);
 
 hipError_t launch_valu(int prec, const ValuPlan &pl, const void *V, int64_t n, int d, const int32_t *sets,

@@ -50,6 +50,8 @@ static bool split_plan(int64_t d, int64_t n, bool one, MfmaPlan *q) {
     int nkb = (int)(d / 32), r4 = (int)(d % 32 + 3) / 4;
     int nt = (6 * r4 + 7) / 8;
     if (nt > (nkb <= 2 ? 4 : 3)) nkb += 1, nt = 0;
+    // many whole blocks: one compiled tail
+    if (nt > 0 && (nkb > 6 || (nkb == 6 && nt > 1))) nt = 3;
     if (split_steps(nkb, nt) > kSplitMaxSteps) return false;
     q->split = 1;
     q->d = (int)d;
@@ -66,13 +68,16 @@ static bool split_plan(int64_t d, int64_t n, bool one, MfmaPlan *q) {
 }
 
 int64_t split_charge(int64_t n, int64_t d, int64_t l, int64_t k) {
-    const int64_t blocks = bucket((int)((d + 7) / 8));
-    const int64_t waves = blocks <= 8 ? 4 : 8, rows = waves * (blocks <= 16 ? 64 : 32);
-    const int64_t groups = (l + 31) / 32;
+    const int64_t tm = split_charge_unit(d), groups = (l + tm - 1) / tm;
+    const int64_t blocks = bucket((int)(tm == 32 ? (d + 7) / 8 : (d + 15) / 16));
+    const int64_t waves = blocks <= 8 && tm == 32 ? 4 : 8;
+    const int64_t rows = waves * (tm == 16 ? 16 : blocks <= 16 ? 64 : 32);
     auto up = [](int64_t x) { return (x + 255) / 256 * 256; };
-    return up(up((n + rows - 1) / rows * waves * groups * 32 * 4) +
-              groups * k * ((blocks <= 4 ? 256 : 128) + blocks * 1024));
+    return up(up((n + rows - 1) / rows * waves * groups * tm * 4) +
+              groups * k * ((blocks <= 4 && tm == 32 ? 256 : 128) + blocks * 1024));
 }
+
+int64_t split_charge_unit(int64_t d) { return d <= 256 ? 32 : 16; }
 
 int64_t split_charge_rows(int64_t n, int64_t d) {
     return d > 8 && d % 4 != 0 ? (n * ((d + 3) / 4 * 4) * 4 + 255) / 256 * 256 : 0;
@@ -114,28 +119,13 @@ bool mfma_plan(int prec, int64_t d, int64_t n, bool one, MfmaPlan *p) {
     q.half = 0;
     q.splat = 0;
     q.il = 0;
-    if (prec == P_FP32 && d <= 256) {
-        // v_mfma_f32_32x32x2_f32, 8 coordinates per k-block
+    if (prec == P_FP32) {
+        // d <= 2: one v_mfma_f32_32x32x2_f32 holds both coordinates
         q.tile = 32;
         q.kb_dims = 8;
-        q.nkb = bucket((int)((d + 7) / 8));
-        // instruction e covers dims e and 4 + e, or 2e and 2e + 1 in a
-        // paired last k-block (il): one k-block, or an exact bucket whose
-        // last block holds r <= 4 coordinates
-        const int r = (int)(d - 8 * ((d + 7) / 8 - 1));  // coordinates in the last block, 1..8
-        if (q.nkb == 1)
-            q.nks_last = EXEMCL_IL ? (int)((d + 1) / 2) : (int)(d < 4 ? d : 4);
-        else if (q.nkb == (d + 7) / 8 && r <= 4)
-            q.nks_last = EXEMCL_IL ? (r + 1) / 2 : 4;
-        else
-            q.nks_last = 4;
-        q.il = il_layout(4, 32, q.nkb, q.nks_last) ? 1 : 0;
-    } else if (prec == P_FP32) {
-        // v_mfma_f32_16x16x4_f32, 16 coordinates per k-block
-        q.tile = 16;
-        q.kb_dims = 16;
-        q.nkb = bucket((int)((d + 15) / 16));
-        q.nks_last = 4;
+        q.nkb = 1;
+        q.nks_last = 1;
+        q.il = 1;
     } else if (d >= EXEMCL_F16_WIDE_D) {
         // v_mfma_f32_16x16x32_{f16,bf16}, 32 coordinates per k-block, two
         // set members per tile; when d mod 32 is in (0, 16] the last k-block

@@ -262,17 +262,8 @@ __global__ __launch_bounds__(64) void pack_tiles_kernel(const T *__restrict__ V,
 #ifndef EXEMCL_FENCE_MIN_NF
 #define EXEMCL_FENCE_MIN_NF 4
 #endif
-#ifndef EXEMCL_SCHED32
-#define EXEMCL_SCHED32 0
-#endif
 #ifndef EXEMCL_PAIR
 #define EXEMCL_PAIR 1
-#endif
-#ifndef EXEMCL_RT1_NKB32
-#define EXEMCL_RT1_NKB32 0
-#endif
-#ifndef EXEMCL_PAIR_NKB32
-#define EXEMCL_PAIR_NKB32 8
 #endif
 #ifndef EXEMCL_PAIR_NKB16
 #define EXEMCL_PAIR_NKB16 4
@@ -289,12 +280,6 @@ __global__ __launch_bounds__(64) void pack_tiles_kernel(const T *__restrict__ V,
 #ifndef EXEMCL_RT16_SMALL
 #define EXEMCL_RT16_SMALL 4
 #endif
-#ifndef EXEMCL_RT16_MID
-#define EXEMCL_RT16_MID 2
-#endif
-#ifndef EXEMCL_RT16_BIG
-#define EXEMCL_RT16_BIG 1
-#endif
 #ifndef EXEMCL_RT16X16_NKB
 #define EXEMCL_RT16X16_NKB 8
 #endif
@@ -303,9 +288,6 @@ __global__ __launch_bounds__(64) void pack_tiles_kernel(const T *__restrict__ V,
 #endif
 #ifndef EXEMCL_RT16X16_BIG
 #define EXEMCL_RT16X16_BIG 2
-#endif
-#ifndef EXEMCL_WAVES16_BIG
-#define EXEMCL_WAVES16_BIG EXEMCL_BIG_WAVES
 #endif
 #ifndef EXEMCL_BIG_NKB
 #define EXEMCL_BIG_NKB 8
@@ -504,7 +486,7 @@ __global__ __launch_bounds__(WAVES * 64, PERSIST ? 2 : 1) void eval_mfma_kernel(
     static_assert(!HALF || (M::HAS_HALF && NKB >= 2), "half k-block needs the 16x16x16 instruction and a whole block");
     // Reads across tiles pay off for long tiles; short ones keep the registers
     // for a third wavefront per SIMD instead.
-    constexpr bool SCHED = (sizeof(T) == 4 ? EXEMCL_SCHED32 : EXEMCL_SCHED16) && NF >= EXEMCL_SCHED_MIN_NF && !HALF;
+    constexpr bool SCHED = EXEMCL_SCHED16 && sizeof(T) == 2 && NF >= EXEMCL_SCHED_MIN_NF && !HALF;
     // B fragments in flight ahead of use.  When the reads run across tiles
     // (SCHED) the ring of PF slots must wrap exactly at a tile's end, so PF
     // divides NF; the next tile then finds fragment i in slot i.
@@ -518,7 +500,7 @@ __global__ __launch_bounds__(WAVES * 64, PERSIST ? 2 : 1) void eval_mfma_kernel(
     // Pairs of tiles per fold (not for HAS_M0: the scoring of S u {c} has
     // single-member sets, where every tile is a set group of its own).
     constexpr bool PAIR = EXEMCL_PAIR && NB == 1 && !HAS_M0 &&
-                          NKB <= (sizeof(T) == 4 ? EXEMCL_PAIR_NKB32 : EXEMCL_PAIR_NKB16);
+                          NKB <= EXEMCL_PAIR_NKB16;
     static_assert(TPS >= 1 && TPS * TB <= SB && NBUF >= 2 && NBUF * SB <= kLdsBytes, "stage geometry");
     static_assert(CNT * (NBUF - 2) < 64, "vmcnt range");
     static_assert(NKS_LAST >= 1 && NKS_LAST <= M::KS_PER_KB, "k-steps of the last block");
@@ -1107,15 +1089,13 @@ constexpr int w12_rt(int nkb) {
 // (mfma_plan) and the compiled instantiations follow one rule.
 constexpr int plan_rt(int elem_bytes, int tile, int nkb) {
     if (tile == 16)
-        return elem_bytes == 4            ? 1
-               : (nkb >= EXEMCL_WIDE16_MIN_NKB && nkb <= EXEMCL_RT16X16_NKB) ? wide16_rt(nkb)
+        return (nkb >= EXEMCL_WIDE16_MIN_NKB && nkb <= EXEMCL_RT16X16_NKB) ? wide16_rt(nkb)
                : nkb <= EXEMCL_W16_MAX_NKB ? EXEMCL_RT16X16_W16
                : nkb <= EXEMCL_RT16X16_NKB ? w12_rt(nkb)
                : nkb <= EXEMCL_RT16X16_BIG3_NKB ? 3
                : nkb <= 16                 ? EXEMCL_RT16X16_BIG
                                            : 1;  // 512 < d <= 1024: one row tile of 32 k-blocks
-    if (elem_bytes == 4) return nkb <= EXEMCL_RT1_NKB32 ? 1 : nkb <= 16 ? 2 : 1;
-    return nkb <= EXEMCL_BIG_NKB ? EXEMCL_RT16_SMALL : nkb <= 16 ? EXEMCL_RT16_MID : EXEMCL_RT16_BIG;
+    return elem_bytes == 4 ? 2 : EXEMCL_RT16_SMALL;  // one k-block: fp32 d <= 2, fp16/bf16 d <= 16
 }
 
 constexpr int plan_waves(int elem_bytes, int tile, int nkb) {
@@ -1123,8 +1103,7 @@ constexpr int plan_waves(int elem_bytes, int tile, int nkb) {
     if (elem_bytes == 2 && tile == 16 && nkb >= EXEMCL_WIDE16_MIN_NKB) return EXEMCL_BIG_WAVES;
     if (elem_bytes == 2 && tile == 16 && nkb >= EXEMCL_W12_MIN_NKB) return 12;
     if (elem_bytes == 2 && tile == 16 && nkb <= EXEMCL_W16_MAX_NKB) return 16;
-    if (nkb <= EXEMCL_BIG_NKB) return EXEMCL_SMALL_WAVES;
-    return (elem_bytes == 2 && tile == 32 && nkb > 16) ? EXEMCL_WAVES16_BIG : EXEMCL_BIG_WAVES;
+    return EXEMCL_SMALL_WAVES;
 }
 
 template <typename T, int TILE, int NKB>
@@ -1137,77 +1116,32 @@ constexpr int waves_of() {
     return plan_waves((int)sizeof(T), TILE, NKB);
 }
 
-// One storage type: pick the instantiation for the plan's k-block bucket.
-// fp32 32x32x2 with more than one k-block and a paired last block of
-// KSL (1 or 2) instructions.
-template <typename T, int TILE, int MODE, int KSL>
-hipError_t eval_dispatch_last(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st) {
-    switch (pl.nkb) {
-    case 2: return eval_launch<T, TILE, 2, KSL, rt_of<T, TILE, 2>(), waves_of<T, TILE, 2>(), MODE>(x, st);
-    case 3: return eval_launch<T, TILE, 3, KSL, rt_of<T, TILE, 3>(), waves_of<T, TILE, 3>(), MODE>(x, st);
-    case 4: return eval_launch<T, TILE, 4, KSL, rt_of<T, TILE, 4>(), waves_of<T, TILE, 4>(), MODE>(x, st);
-    case 5: return eval_launch<T, TILE, 5, KSL, rt_of<T, TILE, 5>(), waves_of<T, TILE, 5>(), MODE>(x, st);
-    case 6: return eval_launch<T, TILE, 6, KSL, rt_of<T, TILE, 6>(), waves_of<T, TILE, 6>(), MODE>(x, st);
-    case 7: return eval_launch<T, TILE, 7, KSL, rt_of<T, TILE, 7>(), waves_of<T, TILE, 7>(), MODE>(x, st);
-    case 8: return eval_launch<T, TILE, 8, KSL, rt_of<T, TILE, 8>(), waves_of<T, TILE, 8>(), MODE>(x, st);
-    case 10: return eval_launch<T, TILE, 10, KSL, rt_of<T, TILE, 10>(), waves_of<T, TILE, 10>(), MODE>(x, st);
-    case 12: return eval_launch<T, TILE, 12, KSL, rt_of<T, TILE, 12>(), waves_of<T, TILE, 12>(), MODE>(x, st);
-    case 13: return eval_launch<T, TILE, 13, KSL, rt_of<T, TILE, 13>(), waves_of<T, TILE, 13>(), MODE>(x, st);
-    case 14: return eval_launch<T, TILE, 14, KSL, rt_of<T, TILE, 14>(), waves_of<T, TILE, 14>(), MODE>(x, st);
-    case 16: return eval_launch<T, TILE, 16, KSL, rt_of<T, TILE, 16>(), waves_of<T, TILE, 16>(), MODE>(x, st);
-    case 20: return eval_launch<T, TILE, 20, KSL, rt_of<T, TILE, 20>(), waves_of<T, TILE, 20>(), MODE>(x, st);
-    case 24: return eval_launch<T, TILE, 24, KSL, rt_of<T, TILE, 24>(), waves_of<T, TILE, 24>(), MODE>(x, st);
-    case 28: return eval_launch<T, TILE, 28, KSL, rt_of<T, TILE, 28>(), waves_of<T, TILE, 28>(), MODE>(x, st);
-    case 32: return eval_launch<T, TILE, 32, KSL, rt_of<T, TILE, 32>(), waves_of<T, TILE, 32>(), MODE>(x, st);
-    }
-    return hipErrorInvalidValue;
-}
-
+// One 16-bit storage type: pick the instantiation for the plan's k-block
+// bucket.
 template <typename T, int TILE, int MODE>
 hipError_t eval_dispatch(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st) {
-    if constexpr (TILE == 16 && sizeof(T) == 4) {
-        switch (pl.nkb) {
-        case 20: return eval_launch<T, TILE, 20, 4, rt_of<T, TILE, 20>(), waves_of<T, TILE, 20>(), MODE>(x, st);
-        case 24: return eval_launch<T, TILE, 24, 4, rt_of<T, TILE, 24>(), waves_of<T, TILE, 24>(), MODE>(x, st);
-        case 28: return eval_launch<T, TILE, 28, 4, rt_of<T, TILE, 28>(), waves_of<T, TILE, 28>(), MODE>(x, st);
-        case 32: return eval_launch<T, TILE, 32, 4, rt_of<T, TILE, 32>(), waves_of<T, TILE, 32>(), MODE>(x, st);
+    constexpr int KL = Mfma<T, TILE>::KS_PER_KB;
+    if constexpr (Mfma<T, TILE>::HAS_HALF) {
+        if (pl.half) {
+            // d mod 32 in (0, 16] up to the plan's limit: 2 .. 6 k-blocks.
+            switch (pl.nkb) {
+            case 2: return eval_launch<T, TILE, 2, KL, rt_of<T, TILE, 2>(), waves_of<T, TILE, 2>(), MODE, true>(x, st);
+            case 3: return eval_launch<T, TILE, 3, KL, rt_of<T, TILE, 3>(), waves_of<T, TILE, 3>(), MODE, true>(x, st);
+            case 4: return eval_launch<T, TILE, 4, KL, rt_of<T, TILE, 4>(), waves_of<T, TILE, 4>(), MODE, true>(x, st);
+            case 5: return eval_launch<T, TILE, 5, KL, rt_of<T, TILE, 5>(), waves_of<T, TILE, 5>(), MODE, true>(x, st);
+            case 6: return eval_launch<T, TILE, 6, KL, rt_of<T, TILE, 6>(), waves_of<T, TILE, 6>(), MODE, true>(x, st);
+            }
+            return hipErrorInvalidValue;
         }
+    }
+    if (pl.half) return hipErrorInvalidValue;
+    if (pl.nks_last != KL) return hipErrorInvalidValue;
+    if constexpr (TILE == 32) {  // d <= 16
+        if (pl.nkb != 1) return hipErrorInvalidValue;
+        return eval_launch<T, TILE, 1, KL, rt_of<T, TILE, 1>(), waves_of<T, TILE, 1>(), MODE>(x, st);
     } else {
-        constexpr int KL = Mfma<T, TILE>::KS_PER_KB;
-        if constexpr (Mfma<T, TILE>::HAS_HALF) {
-            if (pl.half) {
-                // d mod 32 in (0, 16] up to the plan's limit: 2 .. 6 k-blocks.
-                switch (pl.nkb) {
-                case 2: return eval_launch<T, TILE, 2, KL, rt_of<T, TILE, 2>(), waves_of<T, TILE, 2>(), MODE, true>(x, st);
-                case 3: return eval_launch<T, TILE, 3, KL, rt_of<T, TILE, 3>(), waves_of<T, TILE, 3>(), MODE, true>(x, st);
-                case 4: return eval_launch<T, TILE, 4, KL, rt_of<T, TILE, 4>(), waves_of<T, TILE, 4>(), MODE, true>(x, st);
-                case 5: return eval_launch<T, TILE, 5, KL, rt_of<T, TILE, 5>(), waves_of<T, TILE, 5>(), MODE, true>(x, st);
-                case 6: return eval_launch<T, TILE, 6, KL, rt_of<T, TILE, 6>(), waves_of<T, TILE, 6>(), MODE, true>(x, st);
-                }
-                return hipErrorInvalidValue;
-            }
-        }
-        if (pl.half) return hipErrorInvalidValue;
-        if (pl.nkb == 1) {
-            if constexpr (KL == 4) {
-                switch (pl.nks_last) {
-                case 1: return eval_launch<T, TILE, 1, 1, rt_of<T, TILE, 1>(), waves_of<T, TILE, 1>(), MODE>(x, st);
-                case 2: return eval_launch<T, TILE, 1, 2, rt_of<T, TILE, 1>(), waves_of<T, TILE, 1>(), MODE>(x, st);
-                case 3: return eval_launch<T, TILE, 1, 3, rt_of<T, TILE, 1>(), waves_of<T, TILE, 1>(), MODE>(x, st);
-                case 4: return eval_launch<T, TILE, 1, 4, rt_of<T, TILE, 1>(), waves_of<T, TILE, 1>(), MODE>(x, st);
-                }
-                return hipErrorInvalidValue;
-            } else {
-                return eval_launch<T, TILE, 1, KL, rt_of<T, TILE, 1>(), waves_of<T, TILE, 1>(), MODE>(x, st);
-            }
-        }
-        if constexpr (KL == 4 && TILE == 32) {
-            // a last k-block of at most 4 coordinates, paired per instruction
-            if (pl.nks_last == 1) return eval_dispatch_last<T, TILE, MODE, 1>(pl, x, st);
-            if (pl.nks_last == 2) return eval_dispatch_last<T, TILE, MODE, 2>(pl, x, st);
-        }
-        if (pl.nks_last != KL) return hipErrorInvalidValue;
         switch (pl.nkb) {
+        case 1: return eval_launch<T, TILE, 1, KL, rt_of<T, TILE, 1>(), waves_of<T, TILE, 1>(), MODE>(x, st);
         case 2: return eval_launch<T, TILE, 2, KL, rt_of<T, TILE, 2>(), waves_of<T, TILE, 2>(), MODE>(x, st);
         case 3: return eval_launch<T, TILE, 3, KL, rt_of<T, TILE, 3>(), waves_of<T, TILE, 3>(), MODE>(x, st);
         case 4: return eval_launch<T, TILE, 4, KL, rt_of<T, TILE, 4>(), waves_of<T, TILE, 4>(), MODE>(x, st);
@@ -1220,19 +1154,13 @@ hipError_t eval_dispatch(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st) 
         case 13: return eval_launch<T, TILE, 13, KL, rt_of<T, TILE, 13>(), waves_of<T, TILE, 13>(), MODE>(x, st);
         case 14: return eval_launch<T, TILE, 14, KL, rt_of<T, TILE, 14>(), waves_of<T, TILE, 14>(), MODE>(x, st);
         case 16: return eval_launch<T, TILE, 16, KL, rt_of<T, TILE, 16>(), waves_of<T, TILE, 16>(), MODE>(x, st);
+        case 20: return eval_launch<T, TILE, 20, KL, rt_of<T, TILE, 20>(), waves_of<T, TILE, 20>(), MODE>(x, st);
+        case 24: return eval_launch<T, TILE, 24, KL, rt_of<T, TILE, 24>(), waves_of<T, TILE, 24>(), MODE>(x, st);
+        case 28: return eval_launch<T, TILE, 28, KL, rt_of<T, TILE, 28>(), waves_of<T, TILE, 28>(), MODE>(x, st);
+        case 32: return eval_launch<T, TILE, 32, KL, rt_of<T, TILE, 32>(), waves_of<T, TILE, 32>(), MODE>(x, st);
         }
-        // The 16x16x32 shape reaches d = 1024 with 32 k-blocks (one row
-        // tile per wavefront); the 16- and 8-coordinate shapes reach 512.
-        {
-            switch (pl.nkb) {
-            case 20: return eval_launch<T, TILE, 20, KL, rt_of<T, TILE, 20>(), waves_of<T, TILE, 20>(), MODE>(x, st);
-            case 24: return eval_launch<T, TILE, 24, KL, rt_of<T, TILE, 24>(), waves_of<T, TILE, 24>(), MODE>(x, st);
-            case 28: return eval_launch<T, TILE, 28, KL, rt_of<T, TILE, 28>(), waves_of<T, TILE, 28>(), MODE>(x, st);
-            case 32: return eval_launch<T, TILE, 32, KL, rt_of<T, TILE, 32>(), waves_of<T, TILE, 32>(), MODE>(x, st);
-            }
-        }
+        return hipErrorInvalidValue;
     }
-    return hipErrorInvalidValue;
 }
 
 }  // namespace exemcl

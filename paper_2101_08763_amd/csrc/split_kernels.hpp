@@ -46,7 +46,7 @@ namespace exemcl {
 // a lane reads its four accumulators' seeds in one load.
 constexpr int split_hdr(int nkb) { return nkb == 0 ? 512 : 128; }
 constexpr int kSplitSets = 32;   // sets per tile
-constexpr int kSplitMaxSteps = 19;
+constexpr int kSplitMaxSteps = 48;
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
@@ -253,8 +253,22 @@ constexpr int split_tps(int nkb, int nt, int waves) {
         --tps;
     return tps;
 }
-constexpr int split_lds(int nkb, int nt, int waves) {
-    return 2 * split_round(split_tps(nkb, nt, waves) * split_tile_bytes(nkb, nt), waves) +
+// Tiles of which two do not fit (d above 384) are staged in two halves, each
+// with a buffer of its own; `gather` stages such a tile whole in one buffer.
+constexpr bool split_halves(int nkb, int nt, int waves) {
+    return 2 * split_round(split_tile_bytes(nkb, nt), waves) + split_red_bytes(1, waves) > kSplitLds;
+}
+constexpr int split_first(int nkb, int nt) { return split_hdr(nkb) + (split_steps(nkb, nt) + 1) / 2 * 2048; }
+constexpr int split_stage_bytes(int nkb, int nt, int waves, bool gather) {
+    return split_round(split_halves(nkb, nt, waves) && !gather ? split_first(nkb, nt)
+                                                               : split_tps(nkb, nt, waves) * split_tile_bytes(nkb, nt),
+                       waves);
+}
+constexpr int split_buffers(int nkb, int nt, int waves, bool gather) {
+    return gather && split_halves(nkb, nt, waves) ? 1 : 2;
+}
+constexpr int split_lds(int nkb, int nt, int waves, bool gather) {
+    return split_buffers(nkb, nt, waves, gather) * split_stage_bytes(nkb, nt, waves, gather) +
            split_red_bytes(split_tps(nkb, nt, waves), waves);
 }
 
@@ -265,19 +279,16 @@ constexpr int split_lds(int nkb, int nt, int waves) {
 constexpr int kSplitWaves = 8;
 constexpr int split_rt_max(int nkb, int nt) {
     const int steps = split_steps(nkb, nt);
-    return steps <= 5 ? 4 : steps <= 10 ? 3 : 2;
+    return steps <= 5 ? 4 : steps <= 10 ? 3 : steps <= 19 ? 2 : 1;
 }
 constexpr int split_rt(int nkb, int nt, int64_t n, bool one) {
     const int top = split_rt_max(nkb, nt);
+    if (top == 1) return 1;
     if (nkb == 0) return n < 2048 ? 1 : n < 32768 ? 2 : top;
     return n < 8192 ? 1 : top == 4 ? (n < 100000 ? 2 : top) : (!one && n < 32768 ? 2 : top);
 }
 // The cache g(v) reads V once against a few tiles: small workgroups.
 constexpr int kRowmaxWaves = 4, kRowmaxRt = 2;
-
-#ifndef EXEMCL_SPLIT_PF
-#define EXEMCL_SPLIT_PF 2
-#endif
 
 // ---------------------------------------------------------------------------
 // Evaluation.  A workgroup owns WAVES*RT*16 consecutive points; units of work
@@ -304,9 +315,14 @@ __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
     constexpr int TB = split_tile_bytes(NKB, NT);
     constexpr int TPS = split_tps(NKB, NT, WAVES);
     constexpr int NTHR = WAVES * 64;
-    constexpr int SB = split_round(TPS * TB, WAVES);
+    constexpr int NBUF = split_buffers(NKB, NT, WAVES, GATHER);
+    constexpr int SB = split_stage_bytes(NKB, NT, WAVES, GATHER);
     constexpr int CNT = SB / (NTHR * 16);
-    constexpr int PF = STEPS < EXEMCL_SPLIT_PF ? STEPS : EXEMCL_SPLIT_PF;
+    // HALF: a stage is half a tile (HSTEPS steps, HBYTES bytes, then the rest)
+    constexpr bool HALF = split_halves(NKB, NT, WAVES) && !GATHER;
+    constexpr int HSTEPS = HALF ? (STEPS + 1) / 2 : STEPS, HBYTES = split_first(NKB, NT);
+    static_assert(NBUF * SB + split_red_bytes(TPS, WAVES) <= kSplitLds, "LDS");
+    constexpr int PF = STEPS == 1 || STEPS > 42 ? 1 : 2;  // steps of B fragments read ahead
     constexpr int ROWS = WAVES * RT * 16;
     // An accumulator for the small products; the few of a tail alone go onto
     // the bias one after the other (error above), which saves the additions.
@@ -319,7 +335,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
     constexpr bool ONE = HAS_M0 && MODE == MODE_SUM;
 
     extern __shared__ __align__(16) unsigned char smem[];
-    float *red = reinterpret_cast<float *>(smem + 2 * SB);
+    float *red = reinterpret_cast<float *>(smem + NBUF * SB);
 
     auto segment = [&](const int64_t rb, const int64_t g0, const int64_t g1) {
         // hidden per segment, so that per-lane offsets are not kept in
@@ -334,8 +350,9 @@ __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
         const unsigned char *chunk = tiles + g0 * kt * (int64_t)TB;
         const int64_t chunk_bytes = ntiles * (int64_t)TB;
 
+        // Stage s into its buffer (HALF: half s % 2 of tile s / 2).
         auto issue = [&](int s) {
-            unsigned char *buf = smem + (s & 1) * SB;
+            unsigned char *buf = smem + (NBUF > 1 ? s & 1 : 0) * SB;
             if constexpr (GATHER) {
                 const int tn = (int)min((int64_t)TPS, ntiles - (int64_t)s * TPS);
                 for (int c = wave; c < 2 * tn; c += WAVES) {  // column group c % 2 of tile c / 2
@@ -347,8 +364,9 @@ __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
                 }
                 return;
             }
-            const int64_t base = s * (int64_t)(TPS * TB);
-            const auto win = window_rsrc(chunk + base, (uint32_t)min((int64_t)(TPS * TB), chunk_bytes - base));
+            const int64_t base = HALF ? (s >> 1) * (int64_t)TB + (s & 1) * HBYTES : s * (int64_t)(TPS * TB);
+            const int64_t most = HALF ? (s & 1 ? TB - HBYTES : HBYTES) : TPS * TB;
+            const auto win = window_rsrc(chunk + base, (uint32_t)min(most, chunk_bytes - base));
 #pragma unroll
             for (int r = 0; r < CNT; ++r)
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(
@@ -356,7 +374,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
                     (r * NTHR + tid) * 16, 0, 0, 0);
         };
         if (nst > 0) issue(0);
-        if (nst > 1) issue(1);
+        if (NBUF > 1 && (HALF || nst > 1)) issue(1);
 
         // This wavefront's points in A-operand order: three parts of every
         // whole block, the tail's places.  Rows past n read as zeros.
@@ -447,7 +465,8 @@ __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
         bf16x8 bq[PF][2];
         f32x4 bias[2];  // a column's bias, once per accumulator
         auto frag = [&](const unsigned char *tb, int s, int h) {
-            return reinterpret_cast<const bf16x8 *>(tb + HDR)[(s * 2 + h) * 64 + lane];
+            const unsigned char *f = s < HSTEPS ? tb + HDR + s * 2048 : smem + SB + (s - HSTEPS) * 2048;
+            return reinterpret_cast<const bf16x8 *>(f)[h * 64 + lane];
         };
         auto bias_of = [&](const unsigned char *tb, int h) {
             if constexpr (HDR > 128) return reinterpret_cast<const f32x4 *>(tb)[h * 16 + lr];
@@ -463,7 +482,8 @@ __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
             for (int h = 0; h < 2; ++h) bias[h] = bias_of(tb, h);
         };
         // h_s(v) of one tile's 32 columns.
-        auto tile = [&](const unsigned char *tb, const unsigned char *tnext, f32x4 (&acc)[RT][2]) {
+        // `mid`: called before the second half of the steps (HALF).
+        auto tile = [&](const unsigned char *tb, const unsigned char *tnext, f32x4 (&acc)[RT][2], auto mid) {
             constexpr f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
             f32x4 sml[RT][2];
             f32x4 seed[2];
@@ -472,13 +492,21 @@ __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
 #pragma unroll
             for (int s = 0; s < STEPS; ++s) {
                 bf16x8 b[2];
+                if (HALF && s == HSTEPS) {
+                    mid();
+#pragma unroll
+                    for (int q = 0; q < PF; ++q)
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) bq[q][h] = frag(tb, s + q, h);
+                }
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     b[h] = bq[0][h];
 #pragma unroll
                     for (int q = 0; q + 1 < PF; ++q) bq[q][h] = bq[q + 1][h];
-                    bq[PF - 1][h] = s + PF < STEPS ? frag(tb, s + PF, h) : frag(tnext, s + PF - STEPS, h);
-                    if (s + PF == STEPS) bias[h] = bias_of(tnext, h);
+                    if (s + PF < (s < HSTEPS ? HSTEPS : STEPS)) bq[PF - 1][h] = frag(tb, s + PF, h);
+                    else if (!HALF) bq[PF - 1][h] = frag(tnext, s + PF - STEPS, h);
+                    if (!HALF && s + PF == STEPS) bias[h] = bias_of(tnext, h);
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 auto mma = [](const bf16x8 &x, const bf16x8 &y, const f32x4 &c) {
@@ -580,12 +608,21 @@ __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
             gflush += cnt;
         };
         for (int s = 0; s < nst; ++s) {
+            if (NBUF == 1 && s > 0) {
+                __syncthreads();
+                issue(s);
+            }
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
-            const unsigned char *buf = smem + (s & 1) * SB;
+            const unsigned char *buf = smem + (HALF || NBUF == 1 ? 0 : s & 1) * SB;
             const int tn = (int)min((int64_t)TPS, ntiles - (int64_t)s * TPS);
             head(buf);
-            if (s > 0 && s + 1 < nst) issue(s + 1);
+            if (NBUF > 1 && s > 0 && (HALF || s + 1 < nst)) issue(HALF ? 2 * s + 1 : s + 1);
+            auto mid = [&]() {
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                __syncthreads();
+                if (s + 1 < nst) issue(2 * (s + 1));
+            };
             if (MODE == MODE_SUM && done > 0) flush((s & 1) ^ 1, done);
             done = 0;
             auto at_tile = [&](int i) { return buf + (i < tn ? i : tn - 1) * TB; };
@@ -602,8 +639,8 @@ __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
                     // two members of the same sets: one max3 per element
                     while (i + 1 < tn && p + 1 < ktile) {
                         f32x4 x[RT][2], y[RT][2];
-                        tile(at_tile(i), at_tile(i + 1), x);
-                        tile(at_tile(i + 1), at_tile(i + 2), y);
+                        tile(at_tile(i), at_tile(i + 1), x, mid);
+                        tile(at_tile(i + 1), at_tile(i + 2), y, mid);
                         fold2(x, y);
                         i += 2;
                         p += 2;
@@ -612,7 +649,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
                     if (i >= tn) break;
                 }
                 f32x4 x[RT][2];
-                tile(at_tile(i), at_tile(i + 1), x);
+                tile(at_tile(i), at_tile(i + 1), x, mid);
                 fold(x);
                 ++i;
                 if (MODE == MODE_SUM && (ONE || ++p == ktile)) group_end();
@@ -674,7 +711,7 @@ hipError_t split_pack_t(const void *V, int64_t n, int ld, int d, const int32_t *
 template <int NKB, int NT, int RT, int WAVES, int MODE, bool HAS_M0, bool GATHER>
 hipError_t split_launch(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st) {
     auto kern = eval_split_kernel<NKB, NT, RT, WAVES, MODE, HAS_M0, GATHER>;
-    constexpr int lds = split_lds(NKB, NT, WAVES);
+    constexpr int lds = split_lds(NKB, NT, WAVES, GATHER);
     constexpr int rows = WAVES * RT * 16;
     if (MODE == MODE_SUM && pl.rows != rows) return hipErrorInvalidValue;
     // Resident workgroups per CU, queried once per instantiation.
@@ -709,7 +746,8 @@ hipError_t split_eval_t(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st) {
     if constexpr (MODE == MODE_ROWMAX) {
         return split_launch<NKB, NT, kRowmaxRt, kRowmaxWaves, MODE, HAS_M0, GATHER>(pl, x, st);
     } else {
-        if (pl.rt == 1) return split_launch<NKB, NT, 1, kSplitWaves, MODE, HAS_M0, GATHER>(pl, x, st);
+        if constexpr (TOP > 1)
+            if (pl.rt == 1) return split_launch<NKB, NT, 1, kSplitWaves, MODE, HAS_M0, GATHER>(pl, x, st);
         if constexpr (TOP > 2)
             if (pl.rt == 2) return split_launch<NKB, NT, 2, kSplitWaves, MODE, HAS_M0, GATHER>(pl, x, st);
         return split_launch<NKB, NT, TOP, kSplitWaves, MODE, HAS_M0, GATHER>(pl, x, st);
@@ -721,7 +759,8 @@ hipError_t split_eval_t(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st) {
 #define EXEMCL_SPLIT_CASES(F)                                                                              \
     F(0, 1) F(0, 2) F(0, 3) F(0, 4) F(1, 0) F(1, 1) F(1, 2) F(1, 3) F(1, 4) F(2, 0) F(2, 1) F(2, 2) F(2, 3) \
     F(2, 4) F(3, 0) F(3, 1) F(3, 2) F(3, 3) F(4, 0) F(4, 1) F(4, 2) F(4, 3) F(5, 0) F(5, 1) F(5, 2) F(5, 3) \
-    F(6, 0) F(6, 1)
+    F(6, 0) F(6, 1) F(6, 3) F(7, 0) F(7, 3) F(8, 0) F(8, 3) F(9, 0) F(9, 3) F(10, 0) F(10, 3) F(11, 0)      \
+    F(11, 3) F(12, 0) F(12, 3) F(13, 0) F(13, 3) F(14, 0) F(14, 3) F(15, 0) F(15, 3) F(16, 0)
 #endif
 constexpr int split_key(int nkb, int nt) { return nkb * 8 + nt; }
 

@@ -39,7 +39,7 @@ def _plain_env(monkeypatch):
 
 # every tail of 1 .. 32 coordinates, alone and after 1, 2 and more whole blocks
 TAILS = list(range(1, 33)) + [33, 36, 41, 44, 48, 52, 53, 56, 57, 61, 63, 65, 72, 81, 85, 92, 104, 109, 116, 121, 129,
-                              140, 148, 157, 165, 170, 180, 185, 193, 196, 197]
+                              140, 148, 157, 165, 170, 180, 185, 193, 196, 197, 209, 224, 230, 257, 301, 333, 352, 400, 447, 449, 480, 496, 500, 512]
 
 
 @pytest.mark.parametrize("d", TAILS)
@@ -74,7 +74,7 @@ def test_row_tile_rule(torch_gpu, orc, n, d):
     assert np.array_equal(got[33:34], gpu_eval(torch_gpu, Vg, p.sets[33:34]))
 
 
-@pytest.mark.parametrize("n,d,k", [(300, 8, 200), (9000, 20, 90), (40_000, 100, 300), (120_000, 4, 700)])
+@pytest.mark.parametrize("n,d,k", [(300, 8, 200), (9000, 20, 90), (40_000, 100, 300), (120_000, 4, 700), (5000, 300, 60)])
 def test_tiles_staged_in_lds(torch_gpu, monkeypatch, n, d, k):
     """A limit that admits the call but not one set group's tiles: the
     evaluation kernel stages them itself, with the same bits."""
@@ -87,9 +87,13 @@ def test_tiles_staged_in_lds(torch_gpu, monkeypatch, n, d, k):
     Vg, _ = to_gpu(torch, p.X, "fp32")
     full = gpu_eval(torch, Vg, sets)
     # what one set group is accounted for: 4 bytes per coordinate in blocks of
-    # 8, a header, one partial-sum row per 64 points
-    blocks = -(-d // 8)
-    need = -(-n // 256) * 4 * 32 * 4 + k * ((256 if blocks <= 4 else 128) + blocks * 1024) + 1024
+    # 8 (16 above d = 256), a header, one partial-sum row per 64 (16) points
+    if d <= 256:
+        blocks = -(-d // 8)
+        need = -(-n // 256) * 4 * 32 * 4 + k * ((256 if blocks <= 4 else 128) + blocks * 1024) + 1024
+    else:
+        blocks = 20   # d = 300 in 16s, rounded up to a compiled count
+        need = -(-n // 128) * 8 * 16 * 4 + k * (128 + blocks * 1024) + 1024
     rows = 0 if d % 4 == 0 or d <= 8 else -(-(n * (-(-d // 4) * 4) * 4) // 256) * 256
     say(f"tiles in LDS: n={n} d={d} k={k} limit {need + rows}")
     monkeypatch.setenv("EXEMCL_WORKSPACE_LIMIT", str(need + rows))
