@@ -235,10 +235,11 @@ EXEMCL_API int exemplar_gain(const float *V, int64_t n, int64_t d, const int32_t
 /*
  * exemplar_greedy -- the Greedy optimizer of Algorithm 1, run on the device.
  *
- * K rounds; round i scores f(S u {c}) for every point c of V not yet in S
- * (the same computation as exemplar_gain, with the cache g(v) kept on the
- * device and updated as g <- max(g, <v,c*> - ||c*||^2/2) after each round),
- * and adds the best candidate c*.  Ties go to the lowest index (Algorithm 1
+ * K rounds; round i adds the point c* of V not yet in S with the best
+ * f(S u {c}) (the same computation as exemplar_gain, with the cache g(v) kept
+ * on the device and updated as g <- max(g, <v,c*> - ||c*||^2/2) after each
+ * round).  Candidates whose gain in an earlier round already rules them out
+ * (f is submodular, Definition 2) need not be scored again.  Ties go to the lowest index (Algorithm 1
  * leaves the choice open); a NaN score ranks below every number.  The
  * rounds are queued back to back on the stream: no host synchronisation.
  *
@@ -251,8 +252,9 @@ EXEMCL_API int exemplar_gain(const float *V, int64_t n, int64_t d, const int32_t
  *
  * Scores of round i are those exemplar_gain returns for S = S_out[0..i-1]
  * (bitwise), so f_out[i] - f_out[i-1] is the round's discrete derivative
- * (Definition 1).  Temporary memory: about 17 bytes per point plus a scoring
- * workspace kept under 1 GiB by scoring the candidates in chunks.
+ * (Definition 1).  Temporary memory: about 17 bytes per point (25 for large
+ * n^2 d, when a limit leaves room) plus a scoring workspace kept under 1 GiB
+ * by scoring the candidates in chunks.
  * Errors: EINVAL for bad sizes (K > n, d > 2^24) or NULL outputs when K > 0;
  * ENOMEM / EDEVICE as for exemplar_eval.
  */

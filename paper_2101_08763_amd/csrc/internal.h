@@ -56,6 +56,11 @@ struct MfmaArgs {
     // evaluation kernel.
     const int32_t *sets = nullptr;
     int64_t l = 0;
+    // split, m0 set: the number of sets counted on the device (null: all);
+    // this launch's are those from live0 on.
+    const int32_t *live = nullptr;
+    int64_t live0 = 0;
+    int m0_stride = 1;  // split: m0 of point i is m0[i * m0_stride]
     // Optional: events the kernel's dispatch itself records at its start and
     // end (hipExtLaunchKernel), so their interval is the kernel's run time.
     hipEvent_t ev_start = nullptr, ev_stop = nullptr;
@@ -73,7 +78,7 @@ hipError_t eval_run_f16(const MfmaPlan &pl, int mode, const MfmaArgs &x, hipStre
 hipError_t eval_run_bf16(const MfmaPlan &pl, int mode, const MfmaArgs &x, hipStream_t st);
 // The fp32 kernels on the bf16 matrix cores (kernels_mfma_split*.hip).
 hipError_t split_pack_run(const MfmaPlan &pl, const void *V, int64_t n, int ld, const int32_t *sets, int64_t l,
-                          int64_t k, void *tiles, hipStream_t st);
+                          int64_t k, void *tiles, hipStream_t st, const int32_t *live, int64_t live0);
 hipError_t split_sum_run(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st);      // MODE_SUM, m0 null
 hipError_t split_gather_run(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st);   // the same, tiles null
 hipError_t split_gain_run(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st);     // MODE_SUM from m0
@@ -109,7 +114,8 @@ hipError_t launch_pad(int prec, const void *V, int64_t n, int d, void *Vp, int l
 // TM sets as nb column groups: TM*nb biases -||s||^2/2 (-FLT_MAX for padding
 // columns, members past k and invalid indices) and the B lane vectors.
 hipError_t launch_pack(int prec, const MfmaPlan &pl, const void *V, int64_t n, int ld, const int32_t *sets,
-                       int64_t l, int64_t k, void *tiles, hipStream_t st);
+                       int64_t l, int64_t k, void *tiles, hipStream_t st, const int32_t *live = nullptr,
+                       int64_t live0 = 0);
 
 // Bytes of one staged tile (bias header + B lane vectors), and staged tiles
 // per set group of k members.
@@ -129,7 +135,8 @@ hipError_t launch_mfma(int prec, int mode, const MfmaPlan &pl, const void *V, in
                        const void *tiles, int64_t kt, int64_t ngroups, int64_t groups_per_chunk,
                        const float *m0, float *partials, int64_t lpad, float *rowmax, hipStream_t st,
                        hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr,
-                       const int32_t *sets = nullptr, int64_t l = 0);
+                       const int32_t *sets = nullptr, int64_t l = 0, const int32_t *live = nullptr,
+                       int64_t live0 = 0, int m0_stride = 1);
 
 // Bytes a call on the split kernels is accounted for: what decides whether it
 // fits a limit, and into how many chunks (of split_charge_unit sets at least)
@@ -148,9 +155,10 @@ hipError_t launch_valu(int prec, const ValuPlan &pl, const void *V, int64_t n, i
 // out[j] = (2/n) * sum_g partials[g * lpad + j] (fp64, fixed order), or NaN
 // when an index of set j (or of the common list) is outside [0, n) and not
 // the empty slot.
+// `live`: only *live - live0 of the l sets are there.
 hipError_t launch_reduce(const float *partials, int64_t G, int64_t lpad, int64_t l, int64_t n,
                          const int32_t *sets, int64_t kset, const int32_t *common, int64_t kcommon, float *out,
-                         hipStream_t st);
+                         hipStream_t st, const int32_t *live = nullptr, int64_t live0 = 0);
 
 // Out-of-core evaluation: acc[j] (+)= sum_{g < G} partials[g * lpad + j]
 // (fp64, g in order; `first` overwrites), and out[j] = (2/n) * acc[j], or NaN
@@ -170,6 +178,30 @@ hipError_t launch_greedy_init(int32_t *cands, uint8_t *taken, float *g, int64_t 
 
 // Partial-result slots the argmax needs (pval and pidx hold this many).
 int64_t argmax_blocks(int64_t n);
+
+// Lazy rounds.  The gain f(S u {c}) - f(S) never grows with S (Definition 2),
+// so a candidate's gain from an earlier round bounds its gain now, and only
+// candidates whose bound reaches the best score found can be the argmax.
+constexpr int kGreedyProbes = 32;
+struct GreedyState {
+    float tol;      // margin for the rounding of scores
+    int32_t count;  // candidates in the round's list
+};
+// tol from the mean of q[i] = ||v_i||^2; count = 0.
+hipError_t launch_greedy_scale(const float *q, int64_t n, int64_t d, GreedyState *state, hipStream_t st);
+// probes[b] = the untaken candidate of the b-th of kGreedyProbes ranges with
+// the largest estimate (the empty slot when all are taken).
+hipError_t launch_greedy_probe(const float *estimate, const uint8_t *taken, int64_t n, int32_t *probes, hipStream_t st);
+// list = the untaken candidates that are no probes and whose bound *f_prev +
+// gain[c] is not below the best probe score by more than tol (any order).
+hipError_t launch_greedy_filter(const float *gain, const uint8_t *taken, int64_t n, const int32_t *probes,
+                                const float *probe_scores, const float *f_prev, GreedyState *state, int32_t *list,
+                                hipStream_t st);
+// The best of probes and list (largest score, lowest index): S_slot, f_slot,
+// taken; gain[c] = score - *f_prev for every one scored; count = 0.
+hipError_t launch_greedy_pick(const int32_t *probes, const float *probe_scores, const int32_t *list,
+                              const float *list_scores, const float *f_prev, GreedyState *state, float *gain,
+                              uint8_t *taken, int64_t n, int32_t *S_slot, float *f_slot, hipStream_t st);
 
 // Best untaken scores[i] (largest, lowest i on ties, NaN last): writes its
 // index to *S_slot and its score to *f_slot, and sets taken[i] = 1.

@@ -183,11 +183,16 @@ __global__ __launch_bounds__(RJ * RQ) void reduce_sets_kernel(const float *__res
                                                               int64_t lpad, int64_t l, int64_t n,
                                                               const int32_t *__restrict__ sets, int64_t kset,
                                                               const int32_t *__restrict__ common, int64_t kcommon,
-                                                              float *__restrict__ out) {
+                                                              float *__restrict__ out,
+                                                              const int32_t *__restrict__ live, int64_t live0) {
     __shared__ double part[RQ][RJ];
     const int tid = threadIdx.x;
     const int jl = tid % RJ, q = tid / RJ;
     const int64_t j = (int64_t)blockIdx.x * RJ + jl;
+    if (live) {
+        l = min(l, (int64_t)*live - live0);
+        if ((int64_t)blockIdx.x * RJ >= l) return;
+    }
 
     // The first member of each row lane's share is loaded before the
     // partial sums (from an address clamped into the arrays, without a
@@ -233,10 +238,10 @@ __global__ __launch_bounds__(RJ * RQ) void reduce_sets_kernel(const float *__res
 
 hipError_t launch_reduce(const float *partials, int64_t G, int64_t lpad, int64_t l, int64_t n,
                          const int32_t *sets, int64_t kset, const int32_t *common, int64_t kcommon, float *out,
-                         hipStream_t st) {
+                         hipStream_t st, const int32_t *live, int64_t live0) {
     if (l == 0) return hipSuccess;
     hipLaunchKernelGGL(reduce_sets_kernel, dim3((unsigned)((l + RJ - 1) / RJ)), dim3(RJ * RQ), 0, st, partials, G,
-                       lpad, l, n, sets, kset, common, kcommon, out);
+                       lpad, l, n, sets, kset, common, kcommon, out, live, live0);
     return hipGetLastError();
 }
 

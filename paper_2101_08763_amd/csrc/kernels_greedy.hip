@@ -100,7 +100,144 @@ __global__ __launch_bounds__(kThreads) void argmax_final_kernel(const float *__r
     }
 }
 
+// ---------------------------------------------------------------------------
+// Lazy rounds (see internal.h).  Bounds compare fp32 scores, whose error
+// against exact arithmetic is at most the mean over the points of the error
+// of h_s(v) where it is positive -- there |s| <= 2 |v|, so |v||s| + |s|^2/2 <=
+// 4 |v|^2 -- and of the fp32 sums: 2 (4 e + 2^-20) L({e0}) with e the error of
+// a dot product relative to |v||s|.  e = sqrt(d) 2^-24 is the largest one
+// measured for a single dot product (5e-7 = 0.84 sqrt(100) 2^-24 at d = 100);
+// its mean over the points, which is what a score holds, is a hundredth of
+// that.  A bound uses two scores: tol = (16 sqrt(d) + 64) 2^-24 L({e0}).
+// ---------------------------------------------------------------------------
+constexpr int kPickThreads = 1024;
+
+__global__ __launch_bounds__(kPickThreads) void greedy_scale_kernel(const float *__restrict__ q, int64_t n, double c,
+                                                                    GreedyState *__restrict__ state) {
+    __shared__ double part[kPickThreads];
+    double s = 0.0;
+    for (int64_t i = threadIdx.x; i < n; i += kPickThreads) s += (double)q[i];
+    part[threadIdx.x] = s;
+    __syncthreads();
+    for (int w = kPickThreads / 2; w >= 1; w >>= 1) {
+        if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        state->tol = (float)(c * part[0] / (double)n);
+        state->count = 0;
+    }
+}
+
+__global__ __launch_bounds__(kThreads) void greedy_probe_kernel(const float *__restrict__ estimate,
+                                                                const uint8_t *__restrict__ taken, int64_t n,
+                                                                int32_t *__restrict__ probes) {
+    const int64_t lo = blockIdx.x * n / kGreedyProbes, hi = (blockIdx.x + 1) * n / kGreedyProbes;
+    float bv = -INFINITY;
+    int32_t bi = INT32_MAX;
+    for (int64_t i = lo + threadIdx.x; i < hi; i += kThreads) {
+        if (taken[i]) continue;
+        const float v = estimate[i];
+        take(bv, bi, isnan(v) ? -INFINITY : v, (int32_t)i);
+    }
+    block_best(bv, bi);
+    if (threadIdx.x == 0) probes[blockIdx.x] = bi < n ? bi : kEmptySlot;
+}
+
+__global__ __launch_bounds__(kThreads) void greedy_filter_kernel(const float *__restrict__ gain,
+                                                                 const uint8_t *__restrict__ taken, int64_t n,
+                                                                 const int32_t *__restrict__ probes,
+                                                                 const float *__restrict__ probe_scores,
+                                                                 const float *__restrict__ f_prev,
+                                                                 GreedyState *__restrict__ state,
+                                                                 int32_t *__restrict__ list) {
+    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    float best = -INFINITY;
+    bool probed = false;
+    for (int b = 0; b < kGreedyProbes; ++b) {  // uniform addresses
+        const int32_t c = probes[b];
+        if (c >= 0) best = fmaxf(best, probe_scores[b]);
+        probed |= c == i;
+    }
+    // a NaN anywhere keeps the candidate
+    const bool keep = i < n && !probed && !taken[i] && !(gain[i] + *f_prev < best - state->tol);
+    const uint64_t mask = __ballot(keep);
+    if (mask == 0) return;
+    const int lane = threadIdx.x & 63, first = __ffsll((unsigned long long)mask) - 1;
+    int at = 0;
+    if (lane == first) at = atomicAdd(&state->count, __popcll(mask));
+    at = __shfl(at, first);
+    if (keep) list[at + __popcll(mask & ((1ull << lane) - 1))] = (int32_t)i;
+}
+
+__global__ __launch_bounds__(kPickThreads) void greedy_pick_kernel(
+    const int32_t *__restrict__ probes, const float *__restrict__ probe_scores, const int32_t *__restrict__ list,
+    const float *__restrict__ list_scores, const float *__restrict__ f_prev, GreedyState *__restrict__ state,
+    float *__restrict__ gain, uint8_t *__restrict__ taken, int64_t n, int32_t *__restrict__ S_slot,
+    float *__restrict__ f_slot) {
+    __shared__ float sv[kPickThreads];
+    __shared__ int32_t si[kPickThreads];
+    const int count = state->count, tid = threadIdx.x;
+    const float f = *f_prev;
+    float bv = -INFINITY, braw = 0.0f;
+    int32_t bi = INT32_MAX;
+    for (int j = tid - kGreedyProbes; j < count; j += kPickThreads) {
+        const int32_t c = j < 0 ? probes[j + kGreedyProbes] : list[j];
+        if (c < 0) continue;
+        const float s = j < 0 ? probe_scores[j + kGreedyProbes] : list_scores[j];
+        gain[c] = s - f;
+        take(bv, bi, isnan(s) ? -INFINITY : s, c);
+        if (bi == c) braw = s;
+    }
+    sv[tid] = bv;
+    si[tid] = bi;
+    __syncthreads();
+    for (int w = kPickThreads / 2; w >= 1; w >>= 1) {
+        if (tid < w) take(sv[tid], si[tid], sv[tid + w], si[tid + w]);
+        __syncthreads();
+    }
+    if (bi == si[0] && bi < n) {  // the one thread that scored it
+        *S_slot = bi;
+        *f_slot = braw;
+        taken[bi] = 1;
+    }
+    if (tid == 0) {
+        state->count = 0;
+        if (si[0] >= n) {  // nothing left to take (the host never asks for that)
+            *S_slot = kEmptySlot;
+            *f_slot = __builtin_nanf("");
+        }
+    }
+}
+
 }  // namespace
+
+hipError_t launch_greedy_scale(const float *q, int64_t n, int64_t d, GreedyState *state, hipStream_t st) {
+    const double c = (16.0 * sqrt((double)d) + 64.0) * 0x1p-24;
+    hipLaunchKernelGGL(greedy_scale_kernel, dim3(1), dim3(kPickThreads), 0, st, q, n, c, state);
+    return hipGetLastError();
+}
+
+hipError_t launch_greedy_probe(const float *estimate, const uint8_t *taken, int64_t n, int32_t *probes, hipStream_t st) {
+    hipLaunchKernelGGL(greedy_probe_kernel, dim3(kGreedyProbes), dim3(kThreads), 0, st, estimate, taken, n, probes);
+    return hipGetLastError();
+}
+
+hipError_t launch_greedy_filter(const float *gain, const uint8_t *taken, int64_t n, const int32_t *probes,
+                                const float *probe_scores, const float *f_prev, GreedyState *state, int32_t *list,
+                                hipStream_t st) {
+    hipLaunchKernelGGL(greedy_filter_kernel, dim3((unsigned)((n + kThreads - 1) / kThreads)), dim3(kThreads), 0, st,
+                       gain, taken, n, probes, probe_scores, f_prev, state, list);
+    return hipGetLastError();
+}
+
+hipError_t launch_greedy_pick(const int32_t *probes, const float *probe_scores, const int32_t *list,
+                              const float *list_scores, const float *f_prev, GreedyState *state, float *gain,
+                              uint8_t *taken, int64_t n, int32_t *S_slot, float *f_slot, hipStream_t st) {
+    hipLaunchKernelGGL(greedy_pick_kernel, dim3(1), dim3(kPickThreads), 0, st, probes, probe_scores, list, list_scores,
+                       f_prev, state, gain, taken, n, S_slot, f_slot);
+    return hipGetLastError();
+}
 
 int64_t argmax_blocks(int64_t n) {
     int64_t b = (n + kItemsPerBlock - 1) / kItemsPerBlock;

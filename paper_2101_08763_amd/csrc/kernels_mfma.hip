@@ -164,8 +164,9 @@ int64_t mfma_tile_bytes(const MfmaPlan &pl) {
 int64_t mfma_tiles_per_group(const MfmaPlan &pl, int64_t k) { return (k + pl.nb - 1) / pl.nb; }
 
 hipError_t launch_pack(int prec, const MfmaPlan &pl, const void *V, int64_t n, int ld, const int32_t *sets,
-                       int64_t l, int64_t k, void *tiles, hipStream_t st) {
-    if (pl.split) return split_pack_run(pl, V, n, ld, sets, l, k, tiles, st);
+                       int64_t l, int64_t k, void *tiles, hipStream_t st, const int32_t *live, int64_t live0) {
+    if (pl.split) return split_pack_run(pl, V, n, ld, sets, l, k, tiles, st, live, live0);
+    if (live) return hipErrorInvalidValue;
     switch (prec) {
     case P_FP32: return pack_run_f32(pl, V, n, ld, sets, l, k, tiles, st);
     case P_FP16: return pack_run_f16(pl, V, n, ld, sets, l, k, tiles, st);
@@ -177,8 +178,10 @@ hipError_t launch_pack(int prec, const MfmaPlan &pl, const void *V, int64_t n, i
 hipError_t launch_mfma(int prec, int mode, const MfmaPlan &pl, const void *V, int64_t n, int ld, const void *tiles,
                        int64_t kt, int64_t ngroups, int64_t gpc, const float *m0, float *partials, int64_t lpad,
                        float *rowmax, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop, const int32_t *sets,
-                       int64_t l) {
-    const MfmaArgs x{V, n, ld, tiles, kt, ngroups, gpc, m0, partials, lpad, rowmax, sets, l, ev_start, ev_stop};
+                       int64_t l, const int32_t *live, int64_t live0, int m0_stride) {
+    const MfmaArgs x{V,      n,    ld, tiles, kt,    ngroups,   gpc,      m0,     partials, lpad,
+                     rowmax, sets, l,  live,  live0, m0_stride, ev_start, ev_stop};
+    if ((live || m0_stride != 1) && !(pl.split && m0)) return hipErrorInvalidValue;
     if (pl.bigd) return bigd_run(prec, mode, pl, x, st);
     if (pl.split)
         return mode == MODE_ROWMAX ? split_rowmax_run(pl, x, st)

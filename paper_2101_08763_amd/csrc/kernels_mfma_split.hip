@@ -4,11 +4,11 @@
 namespace exemcl {
 
 hipError_t split_pack_run(const MfmaPlan &pl, const void *V, int64_t n, int ld, const int32_t *sets, int64_t l,
-                          int64_t k, void *tiles, hipStream_t st) {
+                          int64_t k, void *tiles, hipStream_t st, const int32_t *live, int64_t live0) {
     if (l < 1 || k < 1) return hipErrorInvalidValue;
     switch (split_key(pl.nkb, pl.nt)) {
 #define EXEMCL_CASE(NKB, NT) \
-    case split_key(NKB, NT): return split_pack_t<NKB, NT>(V, n, ld, pl.d, sets, l, k, tiles, st);
+    case split_key(NKB, NT): return split_pack_t<NKB, NT>(V, n, ld, pl.d, sets, l, k, tiles, st, live, live0);
         EXEMCL_SPLIT_CASES(EXEMCL_CASE)
 #undef EXEMCL_CASE
     }

@@ -227,12 +227,18 @@ __device__ __forceinline__ void stage_columns(const float *__restrict__ V, int64
 
 // Staging: one workgroup of two wavefronts per tile (set group g, member p),
 // one column group each; tile g*k + p at tiles + (g*k + p) * tile bytes.
+// `live`: only *live - live0 of the l sets are there (counted on the device).
 template <int NKB, int NT>
 __global__ __launch_bounds__(128) void pack_split_kernel(const float *__restrict__ V, int64_t n, int ld, int d,
                                                          const int32_t *__restrict__ sets, int64_t l, int64_t k,
-                                                         unsigned char *__restrict__ tiles) {
+                                                         unsigned char *__restrict__ tiles,
+                                                         const int32_t *__restrict__ live, int64_t live0) {
     const int64_t t = blockIdx.x;
     const int64_t g = t / k, p = t - (t / k) * k;
+    if (live) {
+        l = min(l, (int64_t)*live - live0);
+        if (g * kSplitSets >= l) return;
+    }
     const int lane = threadIdx.x & 63, h = threadIdx.x >> 6;
     const int64_t j = g * kSplitSets + h * 16 + (lane & 15);
     const int64_t idx = j < l ? (int64_t)sets[j * k + p] : -1;
@@ -310,7 +316,15 @@ template <int NKB, int NT, int RT, int WAVES, int MODE, bool HAS_M0, bool GATHER
 __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
     const float *__restrict__ V, int64_t n, int ld, int d, const unsigned char *__restrict__ tiles, int64_t kt,
     int64_t ngroups, int64_t nrb, const float *m0, float *__restrict__ partials, int64_t lpad, float *rowmax,
-    const int32_t *__restrict__ sets, int64_t l) {
+    const int32_t *__restrict__ sets, int64_t l, const int32_t *__restrict__ live, int64_t live0, int m0_stride) {
+    if constexpr (HAS_M0 && MODE == MODE_SUM) {
+        // scoring a list whose length was counted on the device
+        if (live) {
+            const int64_t cnt = (int64_t)*live - live0;
+            if (cnt <= 0) return;
+            ngroups = min(ngroups, (cnt + kSplitSets - 1) / kSplitSets);
+        }
+    }
     constexpr int STEPS = split_steps(NKB, NT);
     constexpr int TB = split_tile_bytes(NKB, NT);
     constexpr int TPS = split_tps(NKB, NT, WAVES);
@@ -438,12 +452,13 @@ __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
         float minit[HAS_M0 ? RT : 1][4];
         if constexpr (HAS_M0) {
             // m0 may be null in MODE_ROWMAX (an empty window reads as zeros)
-            const auto mwin = window_rsrc(m0 ? m0 + wrow0 : V, m0 ? (uint32_t)(wrows * 4) : 0u);
+            const auto mwin = window_rsrc(m0 ? m0 + wrow0 * m0_stride : V,
+                                          m0 ? (uint32_t)(((wrows - 1) * m0_stride + 1) * 4) : 0u);
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    minit[rt][i] = window_load4(mwin, (uint32_t)((wave * RT * 16 + rt * 16 + 4 * grp + i) * 4));
+                    minit[rt][i] = window_load4(mwin, (uint32_t)((wave * RT * 16 + rt * 16 + 4 * grp + i) * m0_stride * 4));
         }
         auto m_init = [&](int rt, int i) -> float {
             if constexpr (HAS_M0) return minit[rt][i];
@@ -701,10 +716,10 @@ __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
 // ---------------------------------------------------------------------------
 template <int NKB, int NT>
 hipError_t split_pack_t(const void *V, int64_t n, int ld, int d, const int32_t *sets, int64_t l, int64_t k,
-                        void *tiles, hipStream_t st) {
+                        void *tiles, hipStream_t st, const int32_t *live, int64_t live0) {
     const int64_t ngroups = (l + kSplitSets - 1) / kSplitSets;
     hipLaunchKernelGGL((pack_split_kernel<NKB, NT>), dim3((unsigned)(ngroups * k)), dim3(128), 0, st, (const float *)V,
-                       n, ld, d, sets, l, k, (unsigned char *)tiles);
+                       n, ld, d, sets, l, k, (unsigned char *)tiles, live, live0);
     return hipGetLastError();
 }
 
@@ -736,7 +751,7 @@ hipError_t split_launch(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st) {
     grid = std::min<int64_t>(grid, 1 << 24);
     hipExtLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(WAVES * 64), lds, st, x.ev_start, x.ev_stop, 0,
                           (const float *)x.V, x.n, x.ld, pl.d, (const unsigned char *)x.tiles, x.kt, x.ngroups, nrb,
-                          x.m0, x.partials, x.lpad, x.rowmax, x.sets, x.l);
+                          x.m0, x.partials, x.lpad, x.rowmax, x.sets, x.l, x.live, x.live0, x.m0_stride);
     return hipGetLastError();
 }
 
