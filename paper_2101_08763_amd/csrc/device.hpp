@@ -223,6 +223,12 @@ __device__ __forceinline__ vec_t window_load16(__amdgpu_buffer_rsrc_t rsrc, uint
     return __builtin_bit_cast(vec_t, __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 0, 0));
 }
 
+// The same load straight into LDS: lane L's 16 bytes at `lds` + 16 L (`lds`
+// uniform).
+__device__ __forceinline__ void window_to_lds16(__amdgpu_buffer_rsrc_t rsrc, unsigned char *lds, uint32_t off) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void *)lds, 16, (int)off, 0, 0, 0);
+}
+
 template <typename hvec_t>
 __device__ __forceinline__ hvec_t window_load8(__amdgpu_buffer_rsrc_t rsrc, uint32_t off) {
     return __builtin_bit_cast(hvec_t, __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)off, 0, 0));

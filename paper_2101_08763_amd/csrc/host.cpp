@@ -104,6 +104,8 @@ bool layout_eval(int64_t n, int64_t d, int64_t l, int64_t k, int precision, int 
         L->off_tiles = align_up(L->G * L->lpad * 4, 256);
         L->bytes = align_up(L->off_tiles + L->ngroups * mfma_tiles_per_group(L->mp, k) * tile_bytes(L->mp), 256);
         L->charge = L->mp.split ? split_charge(n, d, l, k) : L->bytes;
+        // long rows are accounted for with a partial-sum row per 4 points
+        if (L->mp.wide) L->charge += align_up(L->G * 8 * L->lpad * 4, 256) - L->off_tiles;
         L->unit = L->mp.split ? split_charge_unit(d) : tm;
         return true;
     }

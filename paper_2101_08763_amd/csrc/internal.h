@@ -32,6 +32,7 @@ struct MfmaPlan {
     int bigd;       // 1: d > 512, the coordinates split over the wavefronts (bigd_kernels.hpp)
     int kw;         // bigd: k-blocks per wavefront and round (a compiled bucket: 2, 4, 8)
     int rounds;     // bigd: rounds of 8 * kw k-blocks that cover d
+    int wide;       // 1: fp16/bf16 rows above the register kernel's d, tiled (wide_kernels.hpp)
     int split;      // 1: fp32 as three bf16 parts (split_kernels.hpp): nkb whole blocks of 32 coordinates
     int nt;         // split: instructions of the tail
     int d;          // split: the data's dimension
@@ -83,6 +84,8 @@ hipError_t split_sum_run(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st);
 hipError_t split_gather_run(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st);   // the same, tiles null
 hipError_t split_gain_run(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st);     // MODE_SUM from m0
 hipError_t split_rowmax_run(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st);   // MODE_ROWMAX, m0 nullable
+// Long fp16/bf16 rows (kernels_mfma_wide.hip).
+hipError_t wide_run(int prec, const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st);
 // The d > 512 kernel (kernels_mfma_bigd.hip), every storage type.
 hipError_t bigd_run(int prec, int mode, const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st);
 

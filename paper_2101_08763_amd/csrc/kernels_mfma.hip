@@ -6,6 +6,7 @@
 #include "internal.h"
 #include "mfma_kernels.hpp"
 #include "split_kernels.hpp"
+#include "wide_kernels.hpp"
 
 // fp16/bf16 rows of at least EXEMCL_F16_WIDE_D coordinates use the 16x16x32
 // shape.  Up to EXEMCL_HALF_MAX_D coordinates a last k-block of 16 covers
@@ -20,6 +21,9 @@
 #endif
 #ifndef EXEMCL_MAIN_MAX_D16
 #define EXEMCL_MAIN_MAX_D16 1024
+#endif
+#ifndef EXEMCL_WIDE_MIN_N
+#define EXEMCL_WIDE_MIN_N 6144
 #endif
 #if EXEMCL_HALF_MAX_D > 192
 #error "half k-blocks are compiled for 2 to 6 k-blocks (d <= 192)"
@@ -111,6 +115,12 @@ bool mfma_plan(int prec, int64_t d, int64_t n, bool one, MfmaPlan *p) {
         q.rt = 2;
         q.waves = 8;
         q.rows = 32;
+        if (prec != P_FP32 && d <= kWideMaxD && n >= EXEMCL_WIDE_MIN_N) {
+            // a tiled product (wide_kernels.hpp): one partial sum per 32 points
+            q.bigd = 0;
+            q.wide = 1;
+            q.wgsum = 1;
+        }
         *p = q;
         return true;
     }
@@ -183,6 +193,7 @@ hipError_t launch_mfma(int prec, int mode, const MfmaPlan &pl, const void *V, in
                      rowmax, sets, l,  live,  live0, m0_stride, ev_start, ev_stop};
     if ((live || m0_stride != 1) && !(pl.split && m0)) return hipErrorInvalidValue;
     if (pl.bigd) return bigd_run(prec, mode, pl, x, st);
+    if (pl.wide) return mode == MODE_SUM ? wide_run(prec, pl, x, st) : hipErrorInvalidValue;
     if (pl.split)
         return mode == MODE_ROWMAX ? split_rowmax_run(pl, x, st)
                : m0                ? split_gain_run(pl, x, st)

@@ -104,11 +104,11 @@ constexpr int tile_bytes_of(int hdr, int nff, int nhalf) { return hdr + nff * 10
 // Padding columns (set >= l), members past k, empty slots and invalid
 // indices become zero vectors with bias -FLT_MAX, which never wins the
 // running max.  Rows are ld elements, zero past the data's d.  One wavefront
-// per tile; ||s||^2 is summed from the lane vectors (fp32, k-blocks then
+// per column group; ||s||^2 is summed from the lane vectors (fp32, k-blocks then
 // elements in order, then the K-groups of the column with a fixed xor tree).
 // ---------------------------------------------------------------------------
 template <typename T, int TILE>
-__global__ __launch_bounds__(64) void pack_tiles_kernel(const T *__restrict__ V, int64_t n, int ld,
+__global__ __launch_bounds__((64 * Mfma<T, TILE>::NB)) void pack_tiles_kernel(const T *__restrict__ V, int64_t n, int ld,
                                                         const int32_t *__restrict__ sets, int64_t l,
                                                         int64_t k, int nkb, int half, int splat, int il,
                                                         unsigned char *__restrict__ tiles) {
@@ -117,26 +117,21 @@ __global__ __launch_bounds__(64) void pack_tiles_kernel(const T *__restrict__ V,
     const int64_t kt = (k + NB - 1) / NB;
     const int64_t t = blockIdx.x;
     const int64_t g = t / kt, q = t - (t / kt) * kt;
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63;
     const int col = lane % M::TM, grp = lane / M::TM;
     const int64_t j = g * M::TM + col;
     const int HDR = hdr_bytes(M::TM, NB, splat != 0);
     const int nfull = nkb - half;  // whole k-blocks; a half one follows when half = 1
     unsigned char *tile = tiles + t * (int64_t)tile_bytes_of(HDR, nfull * NB, half * NB);
     typename M::vec_t *dst = reinterpret_cast<typename M::vec_t *>(tile + HDR);
-    // Member indices of every column group first, from addresses clamped
-    // into the set matrix (l, k >= 1 whenever this kernel runs), so their
-    // loads overlap.
-    int32_t raw[NB];
-#pragma unroll
-    for (int h = 0; h < NB; ++h) {
+    // One wavefront per column group.  The member index is read from an
+    // address clamped into the set matrix (l, k >= 1 whenever this kernel
+    // runs).
+    {
+        const int h = threadIdx.x >> 6;
         const int64_t p = q * NB + h;
-        raw[h] = sets[(j < l ? j : l - 1) * k + (p < k ? p : k - 1)];
-    }
-#pragma unroll
-    for (int h = 0; h < NB; ++h) {
-        const int64_t p = q * NB + h;
-        const int64_t idx = (j < l && p < k) ? (int64_t)raw[h] : -1;
+        const int32_t raw = sets[(j < l ? j : l - 1) * k + (p < k ? p : k - 1)];
+        const int64_t idx = (j < l && p < k) ? (int64_t)raw : -1;
         const bool valid = idx >= 0 && idx < n;
         const int64_t r = valid ? idx : n;  // row n reads as zeros
         float sq = 0.0f;
@@ -981,7 +976,7 @@ hipError_t pack_launch(const MfmaPlan &pl, const void *V, int64_t n, int ld, con
     if (l < 1 || k < 1) return hipErrorInvalidValue;  // the kernel reads sets[0] at least
     const int64_t ngroups = (l + TILE - 1) / TILE;
     const int64_t kt = (k + Mfma<T, TILE>::NB - 1) / Mfma<T, TILE>::NB;
-    hipLaunchKernelGGL((pack_tiles_kernel<T, TILE>), dim3((unsigned)(ngroups * kt)), dim3(64), 0, st,
+    hipLaunchKernelGGL((pack_tiles_kernel<T, TILE>), dim3((unsigned)(ngroups * kt)), dim3(64 * Mfma<T, TILE>::NB), 0, st,
                        (const T *)V, n, ld, sets, l, k, pl.nkb, pl.half, pl.splat, pl.il, (unsigned char *)tiles);
     return hipGetLastError();
 }

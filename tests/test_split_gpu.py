@@ -119,3 +119,24 @@ def test_error_against_64_bits(torch_gpu, orc, scale):
     assert worst <= 100 * 2.0 ** -24   # d roundings of 2^-24 each
     V1, _ = to_gpu(torch_gpu, p.X, "fp32")
     assert np.array_equal(got, gpu_eval(torch_gpu, V1, p.sets) * scale * scale)
+
+
+# ---------------------------------------------------------------------------
+# Long fp16/bf16 rows as a tiled product (wide_kernels.hpp).
+# ---------------------------------------------------------------------------
+@pytest.mark.parametrize("prec", ["fp16", "bf16"])
+@pytest.mark.parametrize("n,d,l,k", [(6144, 1025, 40, 1), (6200, 1056, 17, 2), (9001, 1160, 33, 3), (20_011, 1100, 130, 5),
+                                     (6145, 2000, 300, 4)])
+def test_long_rows_tiled(torch_gpu, orc, prec, n, d, l, k):
+    """Odd and even k-blocks, members and set groups that do not fill a
+    column block, ragged rows; the launch shape (row tiles, streams per set
+    group) follows l and k, the bits must not."""
+    p = synth.random_problem(n, d, l, k, seed=9900 + d, clusters=3)
+    say(f"long rows: {prec} n={n} d={d} l={l} k={k}")
+    Vg, X64 = to_gpu(torch_gpu, p.X, prec)
+    got = gpu_eval(torch_gpu, Vg, p.sets)
+    idx = np.unique(np.linspace(0, l - 1, 9).astype(int))
+    exact(got[idx], orc.eval(X64, p.sets[idx], 8), f"{prec} d={d}")
+    assert np.array_equal(got[5:6], gpu_eval(torch_gpu, Vg, p.sets[5:6])), "batch size 1"
+    pad = np.concatenate([p.sets, np.full((l, 3), -1, np.int32), p.sets[:, :1]], axis=1)
+    assert np.array_equal(got, gpu_eval(torch_gpu, Vg, pad)), "blank and repeated members"
