@@ -171,6 +171,9 @@ hipError_t get_pool(hipMemPool_t *pool) {
 // kept; a failed allocation releases every free kept block and retries.
 constexpr size_t kKeepPerStream = 4;
 constexpr size_t kKeepStreams = 8;
+// Behind its bytes a block holds one int32 that is zero between kernels (the
+// count of workgroups of a launch whose last workgroup writes the results).
+constexpr size_t kBlockTail = 256;
 struct KeptBlock {
     void *p;
     size_t bytes;
@@ -224,6 +227,7 @@ struct Scratch {
     hipStream_t st = nullptr;
     bool kept = false;
     bool borrowed = false;  // carved from an Arena: nothing to release
+    int32_t *counter = nullptr;  // the kept block's zero
     int dev = 0;
     uintptr_t sid = 0;
     ~Scratch() {
@@ -244,6 +248,7 @@ struct Scratch {
 int alloc_scratch(Scratch *s, int64_t bytes, hipStream_t st, Arena *arena = nullptr) {
     s->st = st;
     if (bytes <= 0) return EXEMCL_OK;
+    bytes = align_up(bytes, 256);
     if (arena) {
         const int64_t take = align_up(bytes, 256);
         if (take > arena->left()) return EXEMCL_ENOMEM;
@@ -271,13 +276,14 @@ int alloc_scratch(Scratch *s, int64_t bytes, hipStream_t st, Arena *arena = null
                 best->busy = true;
                 s->ptr = best->p;
                 s->kept = true;
+                s->counter = (int32_t *)((char *)best->p + best->bytes);
                 return EXEMCL_OK;
             }
         }
     }
     hipMemPool_t pool;
     if (get_pool(&pool) != hipSuccess) return EXEMCL_EDEVICE;
-    hipError_t e = hipMallocFromPoolAsync(&s->ptr, (size_t)bytes, pool, st);
+    hipError_t e = hipMallocFromPoolAsync(&s->ptr, (size_t)bytes + kBlockTail, pool, st);
     if (e == hipErrorOutOfMemory) {
         (void)hipGetLastError();
         {
@@ -285,7 +291,7 @@ int alloc_scratch(Scratch *s, int64_t bytes, hipStream_t st, Arena *arena = null
             for (size_t i = g_keep.size(); i-- > 0;)
                 if (g_keep[i].dev == dev) release_free_blocks(i);
         }
-        e = hipMallocFromPoolAsync(&s->ptr, (size_t)bytes, pool, st);
+        e = hipMallocFromPoolAsync(&s->ptr, (size_t)bytes + kBlockTail, pool, st);
     }
     if (e == hipErrorOutOfMemory) {
         (void)hipGetLastError();
@@ -324,6 +330,9 @@ int alloc_scratch(Scratch *s, int64_t bytes, hipStream_t st, Arena *arena = null
     }
     bl.push_back(KeptBlock{s->ptr, (size_t)bytes, true});
     s->kept = true;
+    int32_t *zero = (int32_t *)((char *)s->ptr + bytes);
+    if (launch_zero((float *)zero, 1, st) != hipSuccess) return EXEMCL_EDEVICE;
+    s->counter = zero;
     return EXEMCL_OK;
 }
 
@@ -424,11 +433,13 @@ struct ProfRange {
 };
 
 // Queue the evaluation of sets [0, l) with a workspace laid out by L;
-// `gather`: without its staged tiles; `live`: *live - live0 of the sets.
+// `gather`: without its staged tiles, and with `counter` in one launch;
+// `live`: *live - live0 of the sets.
 hipError_t run_chunk(const Layout &L, char *base, const void *V, int64_t n, int64_t d, const MfmaRows *rows,
                      const int32_t *sets, int64_t l, int64_t k, int precision, const float *m0,
                      const int32_t *common, int64_t kcommon, float *out, hipStream_t st, bool prof = true,
-                     bool gather = false, const int32_t *live = nullptr, int64_t live0 = 0) {
+                     bool gather = false, const int32_t *live = nullptr, int64_t live0 = 0,
+                     int32_t *counter = nullptr) {
     if (L.path == EXEMCL_PATH_NONE) return launch_zero(out, l, st);  // k = 0: every set is empty
     float *partials = (float *)(base + L.off_partials);
     hipError_t e = hipSuccess;
@@ -438,7 +449,8 @@ hipError_t run_chunk(const Layout &L, char *base, const void *V, int64_t n, int6
         if (e == hipSuccess) {
             ProfRange pr(st, prof);
             e = launch_mfma(precision, MODE_SUM, L.mp, rows->V, n, (int)rows->ld, tiles, mfma_tiles_per_group(L.mp, k),
-                            L.ngroups, L.gpc, m0, partials, L.lpad, nullptr, st, pr.a, pr.b, sets, l, live, live0);
+                            L.ngroups, L.gpc, m0, partials, L.lpad, nullptr, st, pr.a, pr.b, sets, l, live, live0, 1,
+                            counter, out);
             if (e == hipSuccess) pr.end();
         }
     } else if (L.path == EXEMCL_PATH_VALU) {
@@ -448,10 +460,12 @@ hipError_t run_chunk(const Layout &L, char *base, const void *V, int64_t n, int6
         pr.record_stop();
         if (e == hipSuccess) pr.end();
     }
-    if (e == hipSuccess)
+    if (e == hipSuccess && !counter)
         e = launch_reduce(partials, L.G, L.lpad, l, n, sets, k, common, kcommon, out, st, live, live0);
     return e;
 }
+
+constexpr int64_t kGatherTiles = 8, kGatherUnits = 256, kGatherSets = 64, kGatherD = 128;
 
 // Queue one evaluation of `l` sets of `k` members (shared by eval and the
 // scoring half of gain).  `m0` (nullable) is the per-point initial max.
@@ -498,7 +512,18 @@ int run_eval(const void *V, int64_t n, int64_t d, const int32_t *sets, int64_t l
     bool gather = false;
     int64_t lc = l;
     Scratch ws;
-    for (;;) {
+    // Few short tiles for few workgroups: each stages its own (a set group's,
+    // at most kGatherTiles of them), which saves the staging launch, about
+    // 4 us.  Long rows are staged by too few wavefronts that way (d = 325:
+    // 31 us against 21).
+    const bool few = L.mp.split && !m0 && d <= kGatherD && k <= kGatherTiles && L.G * L.ngroups <= kGatherUnits &&
+                     L.charge <= limit && L.off_tiles <= limit;
+    if (few) {
+        const int rc = alloc_scratch(&ws, L.off_tiles, st, arena);
+        if (rc) return rc;
+        gather = true;
+    }
+    while (!few) {
         if (!layout_eval(n, d, lc, k, precision, path, &L, one)) return EXEMCL_EINVAL;
         if (L.charge <= limit && L.bytes <= limit) {
             const int rc = alloc_scratch(&ws, L.bytes, st, arena);
@@ -516,13 +541,15 @@ int run_eval(const void *V, int64_t n, int64_t d, const int32_t *sets, int64_t l
         }
         lc = ((lc + 1) / 2 + unit - 1) / unit * unit;
     }
+    // Few sets too: the last workgroup writes the results (one launch in all).
+    int32_t *counter = few && l <= kGatherSets && kcommon == 0 ? ws.counter : nullptr;
     char *base = (char *)ws.ptr;
     for (int64_t j0 = 0; j0 < l; j0 += lc) {
         const int64_t lj = l - j0 < lc ? l - j0 : lc;
         Layout Lj;
         if (!layout_eval(n, d, lj, k, precision, path, &Lj, one)) return EXEMCL_EINVAL;
         const hipError_t e = run_chunk(Lj, base, V, n, d, rows, sets + j0 * k, lj, k, precision, m0, common,
-                                       kcommon, out + j0, st, arena == nullptr, gather);
+                                       kcommon, out + j0, st, arena == nullptr, gather, nullptr, 0, counter);
         if (e != hipSuccess) return EXEMCL_EDEVICE;
     }
     return EXEMCL_OK;

@@ -62,6 +62,10 @@ struct MfmaArgs {
     const int32_t *live = nullptr;
     int64_t live0 = 0;
     int m0_stride = 1;  // split: m0 of point i is m0[i * m0_stride]
+    // split, tiles null: a zero the workgroups count on, so that the last one
+    // writes the results too (null: partial sums only); zero again at the end.
+    int32_t *counter = nullptr;
+    float *out = nullptr;
     // Optional: events the kernel's dispatch itself records at its start and
     // end (hipExtLaunchKernel), so their interval is the kernel's run time.
     hipEvent_t ev_start = nullptr, ev_stop = nullptr;
@@ -139,7 +143,7 @@ hipError_t launch_mfma(int prec, int mode, const MfmaPlan &pl, const void *V, in
                        const float *m0, float *partials, int64_t lpad, float *rowmax, hipStream_t st,
                        hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr,
                        const int32_t *sets = nullptr, int64_t l = 0, const int32_t *live = nullptr,
-                       int64_t live0 = 0, int m0_stride = 1);
+                       int64_t live0 = 0, int m0_stride = 1, int32_t *counter = nullptr, float *out = nullptr);
 
 // Bytes a call on the split kernels is accounted for: what decides whether it
 // fits a limit, and into how many chunks (of split_charge_unit sets at least)

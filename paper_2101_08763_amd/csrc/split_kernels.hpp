@@ -290,11 +290,42 @@ constexpr int split_rt_max(int nkb, int nt) {
 constexpr int split_rt(int nkb, int nt, int64_t n, bool one) {
     const int top = split_rt_max(nkb, nt);
     if (top == 1) return 1;
-    if (nkb == 0) return n < 2048 ? 1 : n < 32768 ? 2 : top;
+    if (nkb == 0) return n < 1024 ? 1 : n < 32768 ? 2 : top;
     return n < 8192 ? 1 : top == 4 ? (n < 100000 ? 2 : top) : (!one && n < 32768 ? 2 : top);
 }
 // The cache g(v) reads V once against a few tiles: small workgroups.
 constexpr int kRowmaxWaves = 4, kRowmaxRt = 2;
+
+// out[j] = (2/n) sum_g partials[g][j] by one workgroup, in the order of
+// reduce_sets_kernel: 64 row lanes add rows q, q + 64, ..., then a pairwise
+// tree, fp64; NaN for a set with an invalid index.  `part`: 64 x 16 doubles.
+template <int NTHR>
+__device__ void finish_sets(const float *partials, int64_t G, int64_t lpad, int64_t l, int64_t n,
+                            const int32_t *__restrict__ sets, int64_t k, float *__restrict__ out, double *part) {
+    const int jl = threadIdx.x & 15, q0 = threadIdx.x >> 4;
+    for (int64_t j0 = 0; j0 < l; j0 += 16) {
+        const int64_t j = j0 + jl;
+        for (int q = q0; q < 64; q += NTHR / 16) {
+            double acc = 0.0;
+            bool bad = false;
+            if (j < l) {
+                for (int64_t g = q; g < G; g += 64) acc += (double)partials[g * lpad + j];
+                for (int64_t p = q; p < k; p += 64) {
+                    const int32_t idx = sets[j * k + p];
+                    bad |= idx != kEmptySlot && (idx < 0 || idx >= n);
+                }
+            }
+            part[q * 16 + jl] = bad ? __builtin_nan("") : acc;
+        }
+        __syncthreads();
+        for (int w = 32; w >= 1; w >>= 1) {
+            for (int q = q0; q < w; q += NTHR / 16) part[q * 16 + jl] += part[(q + w) * 16 + jl];
+            __syncthreads();
+        }
+        if (q0 == 0 && j < l) out[j] = (float)(2.0 * part[jl] / (double)n);
+        __syncthreads();
+    }
+}
 
 // ---------------------------------------------------------------------------
 // Evaluation.  A workgroup owns WAVES*RT*16 consecutive points; units of work
@@ -315,8 +346,9 @@ constexpr int kRowmaxWaves = 4, kRowmaxRt = 2;
 template <int NKB, int NT, int RT, int WAVES, int MODE, bool HAS_M0, bool GATHER>
 __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
     const float *__restrict__ V, int64_t n, int ld, int d, const unsigned char *__restrict__ tiles, int64_t kt,
-    int64_t ngroups, int64_t nrb, const float *m0, float *__restrict__ partials, int64_t lpad, float *rowmax,
-    const int32_t *__restrict__ sets, int64_t l, const int32_t *__restrict__ live, int64_t live0, int m0_stride) {
+    int64_t ngroups, int64_t nrb, const float *m0, float *partials, int64_t lpad, float *rowmax,
+    const int32_t *__restrict__ sets, int64_t l, const int32_t *__restrict__ live, int64_t live0, int m0_stride,
+    int32_t *counter, float *__restrict__ out) {
     if constexpr (HAS_M0 && MODE == MODE_SUM) {
         // scoring a list whose length was counted on the device
         if (live) {
@@ -709,6 +741,23 @@ __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
         if (seg > 0) __syncthreads();
         segment(rb, g0, g1);
     }
+    if constexpr (GATHER) {
+        // `counter`: the workgroup that ends last adds the partial sums, in
+        // the second pass's order (reduce_sets_kernel), and saves its launch.
+        if (counter) {
+            int *last = reinterpret_cast<int *>(red);
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                __threadfence();
+                *last = atomicAdd(counter, 1) == (int)gridDim.x - 1;
+            }
+            __syncthreads();
+            if (!*last) return;
+            __threadfence();
+            finish_sets<WAVES * 64>(partials, nrb, lpad, l, n, sets, kt, out, reinterpret_cast<double *>(smem));
+            if (threadIdx.x == 0) atomicExch(counter, 0);
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -751,7 +800,7 @@ hipError_t split_launch(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st) {
     grid = std::min<int64_t>(grid, 1 << 24);
     hipExtLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(WAVES * 64), lds, st, x.ev_start, x.ev_stop, 0,
                           (const float *)x.V, x.n, x.ld, pl.d, (const unsigned char *)x.tiles, x.kt, x.ngroups, nrb,
-                          x.m0, x.partials, x.lpad, x.rowmax, x.sets, x.l, x.live, x.live0, x.m0_stride);
+                          x.m0, x.partials, x.lpad, x.rowmax, x.sets, x.l, x.live, x.live0, x.m0_stride, x.counter, x.out);
     return hipGetLastError();
 }
 

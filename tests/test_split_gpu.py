@@ -140,3 +140,26 @@ def test_long_rows_tiled(torch_gpu, orc, prec, n, d, l, k):
     assert np.array_equal(got[5:6], gpu_eval(torch_gpu, Vg, p.sets[5:6])), "batch size 1"
     pad = np.concatenate([p.sets, np.full((l, 3), -1, np.int32), p.sets[:, :1]], axis=1)
     assert np.array_equal(got, gpu_eval(torch_gpu, Vg, pad)), "blank and repeated members"
+
+
+# ---------------------------------------------------------------------------
+# Small fp32 calls: tiles staged by the evaluation kernel, results written by
+# the workgroup that ends last.
+# ---------------------------------------------------------------------------
+@pytest.mark.parametrize("n,d,l,k", [(1, 3, 1, 1), (130, 3, 64, 8), (1000, 8, 16, 5), (1000, 8, 65, 5), (1000, 8, 64, 9),
+                                     (8191, 128, 33, 8), (5000, 40, 64, 1), (30_000, 20, 20, 4)])
+def test_one_launch(torch_gpu, orc, n, d, l, k):
+    """Both sides of the rule (k <= 8, l <= 64): the bits of a set do not
+    depend on whether its batch is small enough; calls repeat on one block."""
+    p = synth.random_problem(n, d, 80, k, seed=9950 + d, clusters=0, replace=True)
+    sets = p.sets.copy()
+    sets[3 % l, 0] = n          # invalid: NaN
+    sets[2 % l, 1:] = -1        # blanks
+    Vg, X64 = to_gpu(torch_gpu, p.X, "fp32")
+    full = gpu_eval(torch_gpu, Vg, np.tile(sets, (1, 9)))     # k > 8: staged by a launch of its own
+    say(f"one launch: n={n} d={d} l={l} k={k}")
+    for _ in range(3):
+        got = gpu_eval(torch_gpu, Vg, sets[:l])
+        assert np.array_equal(got, full[:l], equal_nan=True)
+    idx = np.arange(0, l, max(1, l // 5))
+    check(got[idx], orc.eval(X64, sets[idx], 4), orc.loss_e0(X64), "fp32", "one launch")
