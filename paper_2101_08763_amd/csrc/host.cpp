@@ -449,8 +449,8 @@ hipError_t run_chunk(const Layout &L, char *base, const void *V, int64_t n, int6
         if (e == hipSuccess) {
             ProfRange pr(st, prof);
             e = launch_mfma(precision, MODE_SUM, L.mp, rows->V, n, (int)rows->ld, tiles, mfma_tiles_per_group(L.mp, k),
-                            L.ngroups, L.gpc, m0, partials, L.lpad, nullptr, st, pr.a, pr.b, sets, l, live, live0, 1,
-                            counter, out);
+                            L.ngroups, L.gpc, m0, partials, L.lpad, nullptr, st, pr.a, pr.b, sets, l, k, live, live0,
+                            1, counter, out);
             if (e == hipSuccess) pr.end();
         }
     } else if (L.path == EXEMCL_PATH_VALU) {
@@ -465,7 +465,7 @@ hipError_t run_chunk(const Layout &L, char *base, const void *V, int64_t n, int6
     return e;
 }
 
-constexpr int64_t kGatherTiles = 8, kGatherUnits = 256, kGatherSets = 64, kGatherD = 128;
+constexpr int64_t kGatherTiles = 8, kGatherUnits = 256, kGatherSets = 16, kGatherD = 128, kGatherRows = 128;
 
 // Queue one evaluation of `l` sets of `k` members (shared by eval and the
 // scoring half of gain).  `m0` (nullable) is the per-point initial max.
@@ -513,10 +513,12 @@ int run_eval(const void *V, int64_t n, int64_t d, const int32_t *sets, int64_t l
     int64_t lc = l;
     Scratch ws;
     // Few short tiles for few workgroups: each stages its own (a set group's,
-    // at most kGatherTiles of them), which saves the staging launch, about
-    // 4 us.  Long rows are staged by too few wavefronts that way (d = 325:
-    // 31 us against 21).
-    const bool few = L.mp.split && !m0 && d <= kGatherD && k <= kGatherTiles && L.G * L.ngroups <= kGatherUnits &&
+    // at most kGatherTiles of them), which saves the staging launch (bf16,
+    // 10 000 x 64, 48 sets of 8: 14.8 -> 11.8 us).  Longer rows are staged by
+    // too few wavefronts that way (d = 325: 31 us against 21).
+    const bool few = path == EXEMCL_PATH_MFMA && !m0 && d <= kGatherD && mfma_gathers(precision, L.mp) &&
+                     mfma_tiles_per_group(L.mp, k) <= kGatherTiles &&
+                     (n + L.mp.rows - 1) / L.mp.rows * L.ngroups <= kGatherUnits &&
                      L.charge <= limit && L.off_tiles <= limit;
     if (few) {
         const int rc = alloc_scratch(&ws, L.off_tiles, st, arena);
@@ -541,8 +543,12 @@ int run_eval(const void *V, int64_t n, int64_t d, const int32_t *sets, int64_t l
         }
         lc = ((lc + 1) / 2 + unit - 1) / unit * unit;
     }
-    // Few sets too: the last workgroup writes the results (one launch in all).
-    int32_t *counter = few && l <= kGatherSets && kcommon == 0 ? ws.counter : nullptr;
+    // A single pass of sums too: the last workgroup writes the results, one
+    // launch in all (fp32, 1 000 x 8, 16 sets of 5: 9.2 us).  It adds 16 sets
+    // at a time, 64 rows of partial sums apart, each about 1 us behind the
+    // last: with more of either the second launch overlaps better (10 000 x
+    // 64, 48 sets of 8: 16.7 us in one launch, 11.8 in two).
+    int32_t *counter = few && l <= kGatherSets && L.G <= kGatherRows && kcommon == 0 ? ws.counter : nullptr;
     char *base = (char *)ws.ptr;
     for (int64_t j0 = 0; j0 < l; j0 += lc) {
         const int64_t lj = l - j0 < lc ? l - j0 : lc;
@@ -1032,8 +1038,8 @@ EXEMCL_API int exemplar_greedy(const float *V, int64_t n, int64_t d, int64_t K, 
                 e = launch_pack(EXEMCL_FP32, mp, rows.V, n, (int)rows.ld, cands + j0, lj, 1, tiles, st);
                 if (e == hipSuccess)
                     e = launch_mfma(EXEMCL_FP32, MODE_SUM, mp, rows.V, ns, (int)(rows.ld * step), tiles, 1, Ls.ngroups,
-                                    Ls.gpc, g_cur, partials, Ls.lpad, nullptr, st, nullptr, nullptr, nullptr, 0, nullptr,
-                                    0, (int)step);
+                                    Ls.gpc, g_cur, partials, Ls.lpad, nullptr, st, nullptr, nullptr, nullptr, 0, 0,
+                                    nullptr, 0, (int)step);
                 if (e == hipSuccess)
                     e = launch_reduce(partials, Ls.G, Ls.lpad, lj, n, cands + j0, 1, nullptr, 0, lscores + j0, st);
             }

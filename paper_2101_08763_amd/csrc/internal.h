@@ -53,16 +53,16 @@ struct MfmaArgs {
     float *partials;
     int64_t lpad;
     float *rowmax;
-    // split, tiles null: the sets themselves (l x kt indices), staged by the
-    // evaluation kernel.
+    // tiles null (mfma_gathers): the sets themselves (l x k indices), staged
+    // by the evaluation kernel.
     const int32_t *sets = nullptr;
-    int64_t l = 0;
+    int64_t l = 0, k = 0;
     // split, m0 set: the number of sets counted on the device (null: all);
     // this launch's are those from live0 on.
     const int32_t *live = nullptr;
     int64_t live0 = 0;
     int m0_stride = 1;  // split: m0 of point i is m0[i * m0_stride]
-    // split, tiles null: a zero the workgroups count on, so that the last one
+    // tiles null: a zero the workgroups count on, so that the last one
     // writes the results too (null: partial sums only); zero again at the end.
     int32_t *counter = nullptr;
     float *out = nullptr;
@@ -129,6 +129,9 @@ hipError_t launch_pack(int prec, const MfmaPlan &pl, const void *V, int64_t n, i
 int64_t mfma_tile_bytes(const MfmaPlan &pl);
 int64_t mfma_tiles_per_group(const MfmaPlan &pl, int64_t k);
 
+// Whether the evaluation kernel can stage the tiles itself (tiles = null).
+bool mfma_gathers(int prec, const MfmaPlan &pl);
+
 // Mode of the MFMA kernel's epilogue.
 enum Mode { MODE_SUM = 0, MODE_ROWMAX = 1 };
 
@@ -142,7 +145,7 @@ hipError_t launch_mfma(int prec, int mode, const MfmaPlan &pl, const void *V, in
                        const void *tiles, int64_t kt, int64_t ngroups, int64_t groups_per_chunk,
                        const float *m0, float *partials, int64_t lpad, float *rowmax, hipStream_t st,
                        hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr,
-                       const int32_t *sets = nullptr, int64_t l = 0, const int32_t *live = nullptr,
+                       const int32_t *sets = nullptr, int64_t l = 0, int64_t k = 0, const int32_t *live = nullptr,
                        int64_t live0 = 0, int m0_stride = 1, int32_t *counter = nullptr, float *out = nullptr);
 
 // Bytes a call on the split kernels is accounted for: what decides whether it

@@ -171,6 +171,10 @@ int64_t mfma_tile_bytes(const MfmaPlan &pl) {
            (int64_t)pl.half * pl.nb * 512;
 }
 
+bool mfma_gathers(int prec, const MfmaPlan &pl) {
+    return pl.split || (prec != P_FP32 && !pl.bigd && !pl.wide && pl.nkb <= 4);
+}
+
 int64_t mfma_tiles_per_group(const MfmaPlan &pl, int64_t k) { return (k + pl.nb - 1) / pl.nb; }
 
 hipError_t launch_pack(int prec, const MfmaPlan &pl, const void *V, int64_t n, int ld, const int32_t *sets,
@@ -188,10 +192,10 @@ hipError_t launch_pack(int prec, const MfmaPlan &pl, const void *V, int64_t n, i
 hipError_t launch_mfma(int prec, int mode, const MfmaPlan &pl, const void *V, int64_t n, int ld, const void *tiles,
                        int64_t kt, int64_t ngroups, int64_t gpc, const float *m0, float *partials, int64_t lpad,
                        float *rowmax, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop, const int32_t *sets,
-                       int64_t l, const int32_t *live, int64_t live0, int m0_stride, int32_t *counter,
+                       int64_t l, int64_t k, const int32_t *live, int64_t live0, int m0_stride, int32_t *counter,
                        float *out) {
-    const MfmaArgs x{V,      n,    ld, tiles, kt,    ngroups,   gpc,      m0,     partials, lpad,
-                     rowmax, sets, l,  live,  live0, m0_stride, counter, out, ev_start, ev_stop};
+    const MfmaArgs x{V,      n,    ld, tiles, kt, ngroups, gpc,       m0,      partials, lpad,
+                     rowmax, sets, l,  k,     live, live0, m0_stride, counter, out,      ev_start, ev_stop};
     if ((live || m0_stride != 1) && !(pl.split && m0)) return hipErrorInvalidValue;
     if (pl.bigd) return bigd_run(prec, mode, pl, x, st);
     if (pl.wide) return mode == MODE_SUM ? wide_run(prec, pl, x, st) : hipErrorInvalidValue;

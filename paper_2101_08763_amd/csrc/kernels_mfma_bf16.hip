@@ -12,6 +12,7 @@ hipError_t pack_run_bf16(const MfmaPlan &pl, const void *V, int64_t n, int ld, c
 
 hipError_t eval_run_bf16(const MfmaPlan &pl, int mode, const MfmaArgs &x, hipStream_t st) {
     (void)mode;
+    if (!x.tiles) return eval_gather<__bf16>(pl, x, st);
     return pl.tile == 32 ? eval_dispatch<__bf16, 32, MODE_SUM>(pl, x, st)
                          : eval_dispatch<__bf16, 16, MODE_SUM>(pl, x, st);
 }

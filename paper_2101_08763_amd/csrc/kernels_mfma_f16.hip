@@ -12,6 +12,7 @@ hipError_t pack_run_f16(const MfmaPlan &pl, const void *V, int64_t n, int ld, co
 
 hipError_t eval_run_f16(const MfmaPlan &pl, int mode, const MfmaArgs &x, hipStream_t st) {
     (void)mode;
+    if (!x.tiles) return eval_gather<_Float16>(pl, x, st);
     return pl.tile == 32 ? eval_dispatch<_Float16, 32, MODE_SUM>(pl, x, st)
                          : eval_dispatch<_Float16, 16, MODE_SUM>(pl, x, st);
 }

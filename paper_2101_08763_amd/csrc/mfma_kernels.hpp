@@ -107,6 +107,111 @@ constexpr int tile_bytes_of(int hdr, int nff, int nhalf) { return hdr + nff * 10
 // per column group; ||s||^2 is summed from the lane vectors (fp32, k-blocks then
 // elements in order, then the K-groups of the column with a fixed xor tree).
 // ---------------------------------------------------------------------------
+
+// One column group of one tile: a wavefront stages column group h of `tile`
+// (in memory or LDS); `idx` is the row of the lane's column, any value.
+template <typename T, int TILE>
+__device__ __forceinline__ void stage_tile_columns(const T *__restrict__ V, int64_t n, int ld, int64_t idx, int h,
+                                                   int lane, int nkb, int half, int splat, int il,
+                                                   unsigned char *tile) {
+    using M = Mfma<T, TILE>;
+    constexpr int NB = M::NB;
+    const int col = lane % M::TM, grp = lane / M::TM;
+    const int HDR = hdr_bytes(M::TM, NB, splat != 0);
+    const int nfull = nkb - half;  // whole k-blocks; a half one follows when half = 1
+    typename M::vec_t *dst = reinterpret_cast<typename M::vec_t *>(tile + HDR);
+    const bool valid = idx >= 0 && idx < n;
+    const int64_t r = valid ? idx : n;  // row n reads as zeros
+    float sq = 0.0f;
+    // Up to KBATCH k-blocks are loaded before any is stored, so the loads
+    // overlap (indices past the last block re-read it and are not
+    // stored); ||s||^2 still runs over k-blocks and elements in order.
+    // A paired last k-block (fp32) follows the others.
+    const bool paired = sizeof(T) == 4 && il;
+    const int nreg = paired ? nfull - 1 : nfull;
+    constexpr int KBATCH = 8;
+    for (int kb0 = 0; kb0 < nreg; kb0 += KBATCH) {
+        typename M::vec_t vb[KBATCH];
+#pragma unroll
+        for (int u = 0; u < KBATCH; ++u) {
+            const int kb = kb0 + u < nreg ? kb0 + u : nreg - 1;
+            vb[u] = lanevec_raw<M>(V, n, ld, r, kb, grp);
+        }
+#pragma unroll
+        for (int u = 0; u < KBATCH; ++u) {
+            const int kb = kb0 + u;
+            if (kb < nreg) {
+                const typename M::vec_t v = lanevec_keep<M>(vb[u], lanevec_live<M>(n, ld, r, kb, grp));
+                dst[(kb * NB + h) * 64 + lane] = v;
+#pragma unroll
+                for (int e = 0; e < M::VEC; ++e) {
+                    const float x = to_f32(v[e]);
+                    sq = fmaf(x, x, sq);
+                }
+            }
+        }
+    }
+    if (paired) {
+        // last k-block: coordinate kb*8 + 2e + grp, read one at a time
+        // (single-block rows may be unpadded)
+        const int kb = nfull - 1;
+        typename M::vec_t v;
+#pragma unroll
+        for (int e = 0; e < M::VEC; ++e) {
+            const int c = kb * M::KB_DIMS + il_dim(grp, e);
+            v[e] = (r < n && c < ld) ? V[r * (int64_t)ld + c] : (typename M::elem_t)0.0f;
+        }
+        dst[(kb * NB + h) * 64 + lane] = v;
+#pragma unroll
+        for (int e = 0; e < M::VEC; ++e) {
+            const float x = to_f32(v[e]);
+            sq = fmaf(x, x, sq);
+        }
+    }
+    if constexpr (M::HAS_HALF) {
+        if (half) {
+            // Half fragment h: lane L's 8 bytes = coordinates
+            // nfull*32 + (L/TM)*4 + {0..3}, after all whole fragments.
+            using hvec_t = typename M::hvec_t;
+            const int d0 = M::hdim(nfull, grp, 0);
+            const bool live = r < n && d0 < ld;  // ld and d0 are multiples of 4: all 4 in the row
+            hvec_t v = *reinterpret_cast<const hvec_t *>(V + (live ? r : 0) * (int64_t)ld + (live ? d0 : 0));
+#pragma unroll
+            for (int e = 0; e < M::HVEC; ++e) v[e] = live ? v[e] : (typename M::elem_t)0.0f;
+            reinterpret_cast<hvec_t *>(tile + HDR + nfull * NB * 1024)[h * 64 + lane] = v;
+#pragma unroll
+            for (int e = 0; e < M::HVEC; ++e) {
+                const float x = to_f32(v[e]);
+                sq = fmaf(x, x, sq);
+            }
+        }
+    }
+#pragma unroll
+    for (int off = M::TM; off < 64; off <<= 1) sq += __shfl_xor(sq, off);
+    const float b = valid ? -0.5f * sq : -FLT_MAX;
+    if (grp == 0) {
+        if (splat) {
+            // Exact three-way split: hi is b rounded to bf16, mid the
+            // rest rounded again, lo what is left (8 bits at most), so
+            // hi + mid + lo == b.  Clamped to a finite value first, so a
+            // zero operand times any part is 0.
+            const float bc = fmaxf(b, -kBf16Max);
+            const __bf16 hi = (__bf16)bc;
+            const float r1 = bc - (float)hi;
+            const __bf16 mid = (__bf16)r1;
+            const __bf16 lo = (__bf16)(r1 - (float)mid);
+            bf16x4 hv;
+            hv[0] = hi;
+            hv[1] = mid;
+            hv[2] = lo;
+            hv[3] = (__bf16)0.0f;
+            reinterpret_cast<bf16x4 *>(tile)[col] = hv;
+        } else {
+            reinterpret_cast<float *>(tile)[h * M::TM + col] = b;
+        }
+    }
+}
+
 template <typename T, int TILE>
 __global__ __launch_bounds__((64 * Mfma<T, TILE>::NB)) void pack_tiles_kernel(const T *__restrict__ V, int64_t n, int ld,
                                                         const int32_t *__restrict__ sets, int64_t l,
@@ -117,112 +222,14 @@ __global__ __launch_bounds__((64 * Mfma<T, TILE>::NB)) void pack_tiles_kernel(co
     const int64_t kt = (k + NB - 1) / NB;
     const int64_t t = blockIdx.x;
     const int64_t g = t / kt, q = t - (t / kt) * kt;
-    const int lane = threadIdx.x & 63;
-    const int col = lane % M::TM, grp = lane / M::TM;
-    const int64_t j = g * M::TM + col;
-    const int HDR = hdr_bytes(M::TM, NB, splat != 0);
-    const int nfull = nkb - half;  // whole k-blocks; a half one follows when half = 1
-    unsigned char *tile = tiles + t * (int64_t)tile_bytes_of(HDR, nfull * NB, half * NB);
-    typename M::vec_t *dst = reinterpret_cast<typename M::vec_t *>(tile + HDR);
-    // One wavefront per column group.  The member index is read from an
-    // address clamped into the set matrix (l, k >= 1 whenever this kernel
-    // runs).
-    {
-        const int h = threadIdx.x >> 6;
-        const int64_t p = q * NB + h;
-        const int32_t raw = sets[(j < l ? j : l - 1) * k + (p < k ? p : k - 1)];
-        const int64_t idx = (j < l && p < k) ? (int64_t)raw : -1;
-        const bool valid = idx >= 0 && idx < n;
-        const int64_t r = valid ? idx : n;  // row n reads as zeros
-        float sq = 0.0f;
-        // Up to KBATCH k-blocks are loaded before any is stored, so the loads
-        // overlap (indices past the last block re-read it and are not
-        // stored); ||s||^2 still runs over k-blocks and elements in order.
-        // A paired last k-block (fp32) follows the others.
-        const bool paired = sizeof(T) == 4 && il;
-        const int nreg = paired ? nfull - 1 : nfull;
-        constexpr int KBATCH = 8;
-        for (int kb0 = 0; kb0 < nreg; kb0 += KBATCH) {
-            typename M::vec_t vb[KBATCH];
-#pragma unroll
-            for (int u = 0; u < KBATCH; ++u) {
-                const int kb = kb0 + u < nreg ? kb0 + u : nreg - 1;
-                vb[u] = lanevec_raw<M>(V, n, ld, r, kb, grp);
-            }
-#pragma unroll
-            for (int u = 0; u < KBATCH; ++u) {
-                const int kb = kb0 + u;
-                if (kb < nreg) {
-                    const typename M::vec_t v = lanevec_keep<M>(vb[u], lanevec_live<M>(n, ld, r, kb, grp));
-                    dst[(kb * NB + h) * 64 + lane] = v;
-#pragma unroll
-                    for (int e = 0; e < M::VEC; ++e) {
-                        const float x = to_f32(v[e]);
-                        sq = fmaf(x, x, sq);
-                    }
-                }
-            }
-        }
-        if (paired) {
-            // last k-block: coordinate kb*8 + 2e + grp, read one at a time
-            // (single-block rows may be unpadded)
-            const int kb = nfull - 1;
-            typename M::vec_t v;
-#pragma unroll
-            for (int e = 0; e < M::VEC; ++e) {
-                const int c = kb * M::KB_DIMS + il_dim(grp, e);
-                v[e] = (r < n && c < ld) ? V[r * (int64_t)ld + c] : (typename M::elem_t)0.0f;
-            }
-            dst[(kb * NB + h) * 64 + lane] = v;
-#pragma unroll
-            for (int e = 0; e < M::VEC; ++e) {
-                const float x = to_f32(v[e]);
-                sq = fmaf(x, x, sq);
-            }
-        }
-        if constexpr (M::HAS_HALF) {
-            if (half) {
-                // Half fragment h: lane L's 8 bytes = coordinates
-                // nfull*32 + (L/TM)*4 + {0..3}, after all whole fragments.
-                using hvec_t = typename M::hvec_t;
-                const int d0 = M::hdim(nfull, grp, 0);
-                const bool live = r < n && d0 < ld;  // ld and d0 are multiples of 4: all 4 in the row
-                hvec_t v = *reinterpret_cast<const hvec_t *>(V + (live ? r : 0) * (int64_t)ld + (live ? d0 : 0));
-#pragma unroll
-                for (int e = 0; e < M::HVEC; ++e) v[e] = live ? v[e] : (typename M::elem_t)0.0f;
-                reinterpret_cast<hvec_t *>(tile + HDR + nfull * NB * 1024)[h * 64 + lane] = v;
-#pragma unroll
-                for (int e = 0; e < M::HVEC; ++e) {
-                    const float x = to_f32(v[e]);
-                    sq = fmaf(x, x, sq);
-                }
-            }
-        }
-#pragma unroll
-        for (int off = M::TM; off < 64; off <<= 1) sq += __shfl_xor(sq, off);
-        const float b = valid ? -0.5f * sq : -FLT_MAX;
-        if (grp == 0) {
-            if (splat) {
-                // Exact three-way split: hi is b rounded to bf16, mid the
-                // rest rounded again, lo what is left (8 bits at most), so
-                // hi + mid + lo == b.  Clamped to a finite value first, so a
-                // zero operand times any part is 0.
-                const float bc = fmaxf(b, -kBf16Max);
-                const __bf16 hi = (__bf16)bc;
-                const float r1 = bc - (float)hi;
-                const __bf16 mid = (__bf16)r1;
-                const __bf16 lo = (__bf16)(r1 - (float)mid);
-                bf16x4 hv;
-                hv[0] = hi;
-                hv[1] = mid;
-                hv[2] = lo;
-                hv[3] = (__bf16)0.0f;
-                reinterpret_cast<bf16x4 *>(tile)[col] = hv;
-            } else {
-                reinterpret_cast<float *>(tile)[h * M::TM + col] = b;
-            }
-        }
-    }
+    const int lane = threadIdx.x & 63, h = threadIdx.x >> 6;
+    const int64_t j = g * M::TM + lane % M::TM, p = q * NB + h;
+    const int64_t bytes = tile_bytes_of(hdr_bytes(M::TM, NB, splat != 0), (nkb - half) * NB, half * NB);
+    // The member index is read from an address clamped into the set matrix
+    // (l, k >= 1 whenever this kernel runs).
+    const int32_t raw = sets[(j < l ? j : l - 1) * k + (p < k ? p : k - 1)];
+    stage_tile_columns<T, TILE>(V, n, ld, j < l && p < k ? (int64_t)raw : -1, h, lane, nkb, half, splat, il,
+                                tiles + t * bytes);
 }
 
 // Stage geometry, fixed at compile time per k-block bucket.  Workgroups of
@@ -405,6 +412,52 @@ __device__ __forceinline__ void wait_vmcnt() {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
+// Whether this is the last of `count` workgroups to get here; what the others
+// wrote before is visible to it.  `flag`: LDS nobody reads any more.
+__device__ __forceinline__ bool last_workgroup(int32_t *counter, int count, int *flag) {
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __threadfence();
+        *flag = atomicAdd(counter, 1) == count - 1;
+    }
+    __syncthreads();
+    const bool last = *flag != 0;
+    if (last) __threadfence();
+    __syncthreads();
+    return last;
+}
+
+// out[j] = (2/n) sum_g partials[g][j] by one workgroup, in the order of
+// reduce_sets_kernel: 64 row lanes add rows q, q + 64, ..., then a pairwise
+// tree, fp64; NaN for a set with an invalid index.  `part`: 64 x 16 doubles.
+template <int NTHR>
+__device__ void finish_sets(const float *partials, int64_t G, int64_t lpad, int64_t l, int64_t n,
+                            const int32_t *__restrict__ sets, int64_t k, float *__restrict__ out, double *part) {
+    const int jl = threadIdx.x & 15, q0 = threadIdx.x >> 4;
+    for (int64_t j0 = 0; j0 < l; j0 += 16) {
+        const int64_t j = j0 + jl;
+        for (int q = q0; q < 64; q += NTHR / 16) {
+            double acc = 0.0;
+            bool bad = false;
+            if (j < l) {
+                for (int64_t g = q; g < G; g += 64) acc += (double)partials[g * lpad + j];
+                for (int64_t p = q; p < k; p += 64) {
+                    const int32_t idx = sets[j * k + p];
+                    bad |= idx != kEmptySlot && (idx < 0 || idx >= n);
+                }
+            }
+            part[q * 16 + jl] = bad ? __builtin_nan("") : acc;
+        }
+        __syncthreads();
+        for (int w = 32; w >= 1; w >>= 1) {
+            for (int q = q0; q < w; q += NTHR / 16) part[q * 16 + jl] += part[(q + w) * 16 + jl];
+            __syncthreads();
+        }
+        if (q0 == 0 && j < l) out[j] = (float)(2.0 * part[jl] / (double)n);
+        __syncthreads();
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Evaluation kernel.
 //
@@ -437,14 +490,20 @@ __device__ __forceinline__ void wait_vmcnt() {
 // MODE_ROWMAX: rowmax[v] = max(m0(v), 0, max over all staged columns of
 // h_s(v)) (m0 = 0 when null); rowmax must not alias m0.
 // ---------------------------------------------------------------------------
+//
+// GATHER: no staged tiles in memory; the workgroup stages every tile into LDS
+// itself, from the set indices, with the same code and so the same bits.  With
+// `counter` the workgroup that ends last writes the results too.
 template <typename T, int TILE, int NKB, int NKS_LAST, int RT, int WAVES, int MODE, bool HAS_M0, bool HALF,
-          bool PERSIST>
+          bool PERSIST, bool GATHER = false>
 __global__ __launch_bounds__(WAVES * 64, PERSIST ? 2 : 1) void eval_mfma_kernel(const T *__restrict__ V, int64_t n, int ld,
                                                                  const unsigned char *__restrict__ tiles, int64_t kt,
                                                                  int64_t ngroups, int64_t gpc, int64_t nrb,
                                                                  const float *__restrict__ m0,
-                                                                 float *__restrict__ partials, int64_t lpad,
-                                                                 float *__restrict__ rowmax) {
+                                                                 float *partials, int64_t lpad,
+                                                                 float *__restrict__ rowmax,
+                                                                 const int32_t *__restrict__ sets, int64_t l, int64_t k,
+                                                                 int32_t *counter, float *__restrict__ out) {
     using M = Mfma<T, TILE>;
     using vec_t = typename M::vec_t;
     using acc_t = typename M::acc_t;
@@ -532,6 +591,17 @@ __global__ __launch_bounds__(WAVES * 64, PERSIST ? 2 : 1) void eval_mfma_kernel(
     // Queue the direct-to-LDS copy of stage s (CNT 16-byte loads per thread).
     auto issue = [&](int64_t s) {
         unsigned char *buf = smem + (int)(s % NBUF) * SB;
+        if constexpr (GATHER) {
+            const int tn = (int)min((int64_t)TPS, ntiles - s * TPS);
+            for (int c = wave; c < NB * tn; c += WAVES) {  // column group c % NB of tile c / NB
+                const int64_t t = s * TPS + c / NB;
+                const int64_t j = (g0 + t / kt) * TM + lr, p = (t % kt) * NB + c % NB;
+                const int64_t idx = j < l && p < k ? (int64_t)sets[j * k + p] : -1;
+                stage_tile_columns<T, TILE>(V, n, ldv, idx, c % NB, lane, NKB, HALF ? 1 : 0, SPLAT ? 1 : 0, 0,
+                                            buf + c / NB * TB);
+            }
+            return;
+        }
         const int64_t base = s * (int64_t)(TPS * TB);
         // A window over this stage's bytes: loads past the chunk end read zeros.
         const auto win = window_rsrc(chunk + base, (uint32_t)min((int64_t)(TPS * TB), chunk_bytes - base));
@@ -913,6 +983,13 @@ __global__ __launch_bounds__(WAVES * 64, PERSIST ? 2 : 1) void eval_mfma_kernel(
     if constexpr (!PERSIST) {
         const int64_t g0 = (int64_t)blockIdx.y * gpc;
         segment((int64_t)blockIdx.x, g0, min(ngroups, g0 + gpc));
+        if constexpr (GATHER) {
+            if (counter && last_workgroup(counter, (int)(gridDim.x * gridDim.y), reinterpret_cast<int *>(smem))) {
+                finish_sets<NT>(partials, nrb * (WGSUM ? 1 : WAVES), lpad, l, n, sets, k, out,
+                                reinterpret_cast<double *>(smem));
+                if (threadIdx.x == 0) atomicExch(counter, 0);
+            }
+        }
     } else {
         const int64_t S = gridDim.x;
         const int64_t q = nrb / S;
@@ -1036,11 +1113,12 @@ hipError_t eval_launch_t(const MfmaArgs &x, hipStream_t st) {
     if (use_persist) {
         hipExtLaunchKernelGGL(kernp, dim3((unsigned)slots, 1), dim3(WAVES * 64), lds, st, x.ev_start, x.ev_stop, 0,
                               (const T *)x.V, x.n, x.ld, (const unsigned char *)x.tiles, x.kt, x.ngroups, x.gpc, G,
-                              x.m0, x.partials, x.lpad, x.rowmax);
+                              x.m0, x.partials, x.lpad, x.rowmax, nullptr, (int64_t)0, (int64_t)0, nullptr, nullptr);
     } else {
         hipExtLaunchKernelGGL(kern, dim3((unsigned)G, (unsigned)chunks), dim3(WAVES * 64), lds, st, x.ev_start,
                               x.ev_stop, 0, (const T *)x.V, x.n, x.ld, (const unsigned char *)x.tiles, x.kt,
-                              x.ngroups, x.gpc, G, x.m0, x.partials, x.lpad, x.rowmax);
+                              x.ngroups, x.gpc, G, x.m0, x.partials, x.lpad, x.rowmax, nullptr, (int64_t)0, (int64_t)0, nullptr,
+                              nullptr);
     }
     return hipGetLastError();
 }
@@ -1156,6 +1234,52 @@ hipError_t eval_dispatch(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st) 
         }
         return hipErrorInvalidValue;
     }
+}
+
+// Few sets over few points (mfma_gathers): one workgroup per (row block, set
+// group), which stages its own tiles.
+template <typename T, int TILE, int NKB, bool HALF>
+hipError_t eval_gather_t(const MfmaArgs &x, hipStream_t st) {
+    constexpr int NB = Mfma<T, TILE>::NB, RT = rt_of<T, TILE, NKB>(), WAVES = waves_of<T, TILE, NKB>();
+    constexpr int KL = Mfma<T, TILE>::KS_PER_KB;
+    constexpr int NF = NKB * NB;
+    constexpr int TB = tile_bytes_of(hdr_bytes(TILE, NB, splat_bias((int)sizeof(T), TILE, NKB)),
+                                     HALF ? (NKB - 1) * NB : NF, HALF ? NB : 0);
+    constexpr bool FILL = wg_sum(WAVES, NB);
+    constexpr int SB = stage_bytes<TB, NF, WAVES, FILL, NB == 1>();
+    constexpr int NBUF = ring_depth<TB, NF, WAVES, FILL, NB == 1>();
+    auto kern = eval_mfma_kernel<T, TILE, NKB, KL, RT, WAVES, MODE_SUM, false, HALF, false, true>;
+    constexpr int lds = NBUF * SB + (FILL ? kWgSumLds : 0);
+    static_assert(lds >= 64 * 16 * 8, "finish_sets");
+    if (lds > 64 * 1024) {
+        const hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (e != hipSuccess) return e;
+    }
+    const int64_t rows = (int64_t)WAVES * RT * TILE, G = (x.n + rows - 1) / rows;
+    hipExtLaunchKernelGGL(kern, dim3((unsigned)G, (unsigned)x.ngroups), dim3(WAVES * 64), lds, st, x.ev_start, x.ev_stop, 0,
+                          (const T *)x.V, x.n, x.ld, (const unsigned char *)nullptr, x.kt, x.ngroups, (int64_t)1, G,
+                          (const float *)nullptr, x.partials, x.lpad, (float *)nullptr, x.sets, x.l, x.k, x.counter, x.out);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t eval_gather(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st) {
+    if (pl.tile == 32) return pl.nkb == 1 ? eval_gather_t<T, 32, 1, false>(x, st) : hipErrorInvalidValue;
+    if (pl.half) {
+        switch (pl.nkb) {
+        case 2: return eval_gather_t<T, 16, 2, true>(x, st);
+        case 3: return eval_gather_t<T, 16, 3, true>(x, st);
+        case 4: return eval_gather_t<T, 16, 4, true>(x, st);
+        }
+        return hipErrorInvalidValue;
+    }
+    switch (pl.nkb) {
+    case 1: return eval_gather_t<T, 16, 1, false>(x, st);
+    case 2: return eval_gather_t<T, 16, 2, false>(x, st);
+    case 3: return eval_gather_t<T, 16, 3, false>(x, st);
+    case 4: return eval_gather_t<T, 16, 4, false>(x, st);
+    }
+    return hipErrorInvalidValue;
 }
 
 }  // namespace exemcl

@@ -296,37 +296,6 @@ constexpr int split_rt(int nkb, int nt, int64_t n, bool one) {
 // The cache g(v) reads V once against a few tiles: small workgroups.
 constexpr int kRowmaxWaves = 4, kRowmaxRt = 2;
 
-// out[j] = (2/n) sum_g partials[g][j] by one workgroup, in the order of
-// reduce_sets_kernel: 64 row lanes add rows q, q + 64, ..., then a pairwise
-// tree, fp64; NaN for a set with an invalid index.  `part`: 64 x 16 doubles.
-template <int NTHR>
-__device__ void finish_sets(const float *partials, int64_t G, int64_t lpad, int64_t l, int64_t n,
-                            const int32_t *__restrict__ sets, int64_t k, float *__restrict__ out, double *part) {
-    const int jl = threadIdx.x & 15, q0 = threadIdx.x >> 4;
-    for (int64_t j0 = 0; j0 < l; j0 += 16) {
-        const int64_t j = j0 + jl;
-        for (int q = q0; q < 64; q += NTHR / 16) {
-            double acc = 0.0;
-            bool bad = false;
-            if (j < l) {
-                for (int64_t g = q; g < G; g += 64) acc += (double)partials[g * lpad + j];
-                for (int64_t p = q; p < k; p += 64) {
-                    const int32_t idx = sets[j * k + p];
-                    bad |= idx != kEmptySlot && (idx < 0 || idx >= n);
-                }
-            }
-            part[q * 16 + jl] = bad ? __builtin_nan("") : acc;
-        }
-        __syncthreads();
-        for (int w = 32; w >= 1; w >>= 1) {
-            for (int q = q0; q < w; q += NTHR / 16) part[q * 16 + jl] += part[(q + w) * 16 + jl];
-            __syncthreads();
-        }
-        if (q0 == 0 && j < l) out[j] = (float)(2.0 * part[jl] / (double)n);
-        __syncthreads();
-    }
-}
-
 // ---------------------------------------------------------------------------
 // Evaluation.  A workgroup owns WAVES*RT*16 consecutive points; units of work
 // are (row block, set group) pairs, shared out as in mfma_kernels.hpp: S
@@ -744,16 +713,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
     if constexpr (GATHER) {
         // `counter`: the workgroup that ends last adds the partial sums, in
         // the second pass's order (reduce_sets_kernel), and saves its launch.
-        if (counter) {
-            int *last = reinterpret_cast<int *>(red);
-            __syncthreads();
-            if (threadIdx.x == 0) {
-                __threadfence();
-                *last = atomicAdd(counter, 1) == (int)gridDim.x - 1;
-            }
-            __syncthreads();
-            if (!*last) return;
-            __threadfence();
+        if (counter && last_workgroup(counter, (int)gridDim.x, reinterpret_cast<int *>(red))) {
             finish_sets<WAVES * 64>(partials, nrb, lpad, l, n, sets, kt, out, reinterpret_cast<double *>(smem));
             if (threadIdx.x == 0) atomicExch(counter, 0);
         }

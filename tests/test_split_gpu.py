@@ -163,3 +163,23 @@ def test_one_launch(torch_gpu, orc, n, d, l, k):
         assert np.array_equal(got, full[:l], equal_nan=True)
     idx = np.arange(0, l, max(1, l // 5))
     check(got[idx], orc.eval(X64, sets[idx], 4), orc.loss_e0(X64), "fp32", "one launch")
+
+
+@pytest.mark.parametrize("prec", ["fp16", "bf16"])
+@pytest.mark.parametrize("n,d,l,k", [(1, 1, 1, 1), (5000, 16, 64, 8), (5000, 17, 20, 3), (6001, 33, 16, 15), (6001, 64, 17, 16),
+                                     (10_000, 70, 48, 8), (9000, 80, 65, 8), (20_011, 96, 5, 4), (7000, 109, 33, 7), (12_345, 128, 16, 8)])
+def test_one_launch_16_bit(torch_gpu, orc, prec, n, d, l, k):
+    """Every compiled row length (32 x 32 tiles up to d = 16, then 1 .. 4
+    k-blocks, the last one whole or half) of the 16-bit kernels: as above."""
+    p = synth.random_problem(n, d, 80, k, seed=9970 + d, clusters=0, replace=True)
+    sets = p.sets.copy()
+    sets[3 % l, 0] = n
+    sets[2 % l, 1:] = -1
+    Vg, X64 = to_gpu(torch_gpu, p.X, prec)
+    full = gpu_eval(torch_gpu, Vg, np.tile(sets, (1, 17)))   # more than 8 tiles: staged by a launch of its own
+    say(f"one launch: {prec} n={n} d={d} l={l} k={k}")
+    for _ in range(3):
+        got = gpu_eval(torch_gpu, Vg, sets[:l])
+        assert np.array_equal(got, full[:l], equal_nan=True)
+    idx = np.arange(0, l, max(1, l // 5))
+    check(got[idx], orc.eval(X64, sets[idx], 4), orc.loss_e0(X64), prec, "one launch")
