@@ -465,7 +465,7 @@ hipError_t run_chunk(const Layout &L, char *base, const void *V, int64_t n, int6
     return e;
 }
 
-constexpr int64_t kGatherTiles = 8, kGatherUnits = 256, kGatherSets = 16, kGatherD = 128, kGatherRows = 128;
+constexpr int64_t kGatherTiles = 8, kGatherShort = 32, kGatherUnits = 256, kGatherSets = 16, kGatherD = 128, kGatherRows = 128;
 
 // Queue one evaluation of `l` sets of `k` members (shared by eval and the
 // scoring half of gain).  `m0` (nullable) is the per-point initial max.
@@ -486,6 +486,7 @@ int run_eval(const void *V, int64_t n, int64_t d, const int32_t *sets, int64_t l
              const float *m0, const int32_t *common, int64_t kcommon, float *out, hipStream_t st,
              const MfmaRows *rows = nullptr, int64_t reserved = 0, Arena *arena = nullptr, bool one = false) {
     if (l == 0) return EXEMCL_OK;
+    const int64_t ws_limit = workspace_limit();
     int path = k == 0 ? EXEMCL_PATH_NONE : choose_path(d, k, precision);
     if (m0 && path == EXEMCL_PATH_VALU) path = EXEMCL_PATH_MFMA;
     if (k > 0 && path == EXEMCL_PATH_NONE) return EXEMCL_EINVAL;
@@ -495,11 +496,11 @@ int run_eval(const void *V, int64_t n, int64_t d, const int32_t *sets, int64_t l
     MfmaRows own;
     if (path == EXEMCL_PATH_MFMA && !rows) {
         const int64_t pb = charge_rows(precision, n, d);
-        if (reserved + pb > workspace_limit() || (arena && pb > arena->left())) return EXEMCL_ENOMEM;
+        if (reserved + pb > ws_limit || (arena && pb > arena->left())) return EXEMCL_ENOMEM;
         // Nothing is queued unless the padded rows and one set group fit.
         Layout L1;
         if (!layout_eval(n, d, std::min<int64_t>(l, unit), k, precision, path, &L1, one)) return EXEMCL_EINVAL;
-        if (reserved + pb + L1.charge > workspace_limit() || (arena && pb + L1.charge > arena->left()))
+        if (reserved + pb + L1.charge > ws_limit || (arena && pb + L1.charge > arena->left()))
             return EXEMCL_ENOMEM;
         const int rc = prepare_rows(V, n, d, precision, st, &own, arena);
         if (rc) return rc;
@@ -507,17 +508,19 @@ int run_eval(const void *V, int64_t n, int64_t d, const int32_t *sets, int64_t l
         reserved += L.mp.split ? pb : own.bytes;
         if (arena && L.mp.split) arena->cap -= pb;
     }
-    int64_t limit = workspace_limit() - reserved;
+    int64_t limit = ws_limit - reserved;
     if (arena) limit = std::min(limit, arena->left());
     bool gather = false;
     int64_t lc = l;
     Scratch ws;
     // Few short tiles for few workgroups: each stages its own (a set group's,
-    // at most kGatherTiles of them), which saves the staging launch (bf16,
-    // 10 000 x 64, 48 sets of 8: 14.8 -> 11.8 us).  Longer rows are staged by
-    // too few wavefronts that way (d = 325: 31 us against 21).
+    // at most kGatherTiles of them, twice that for short rows), which saves
+    // the staging launch (bf16, 10 000 x 64, 48 sets of 8: 14.8 -> 11.8 us;
+    // 5 000 x 16, 100 sets of 16: 15.7 -> 12).  More or longer rows are staged
+    // by too few wavefronts that way (d = 325, 8 tiles: 31 us against 21;
+    // d = 128, 15 tiles: 26.7 against 26.4).
     const bool few = path == EXEMCL_PATH_MFMA && !m0 && d <= kGatherD && mfma_gathers(precision, L.mp) &&
-                     mfma_tiles_per_group(L.mp, k) <= kGatherTiles &&
+                     mfma_tiles_per_group(L.mp, k) <= (d <= kGatherShort ? 2 : 1) * kGatherTiles &&
                      (n + L.mp.rows - 1) / L.mp.rows * L.ngroups <= kGatherUnits &&
                      L.charge <= limit && L.off_tiles <= limit;
     if (few) {

@@ -147,16 +147,18 @@ def test_long_rows_tiled(torch_gpu, orc, prec, n, d, l, k):
 # the workgroup that ends last.
 # ---------------------------------------------------------------------------
 @pytest.mark.parametrize("n,d,l,k", [(1, 3, 1, 1), (130, 3, 64, 8), (1000, 8, 16, 5), (1000, 8, 65, 5), (1000, 8, 64, 9),
-                                     (8191, 128, 33, 8), (5000, 40, 64, 1), (30_000, 20, 20, 4)])
+                                     (8191, 128, 33, 8), (5000, 40, 64, 1), (30_000, 20, 20, 4),
+                                     (1000, 32, 16, 16), (1000, 32, 16, 17), (1000, 33, 17, 16), (30_000, 8, 16, 3)])
 def test_one_launch(torch_gpu, orc, n, d, l, k):
-    """Both sides of the rule (k <= 8, l <= 64): the bits of a set do not
+    """Both sides of the rules (k <= 8, 16 up to d = 32; one launch up to
+    l = 16): the bits of a set do not
     depend on whether its batch is small enough; calls repeat on one block."""
     p = synth.random_problem(n, d, 80, k, seed=9950 + d, clusters=0, replace=True)
     sets = p.sets.copy()
     sets[3 % l, 0] = n          # invalid: NaN
     sets[2 % l, 1:] = -1        # blanks
     Vg, X64 = to_gpu(torch_gpu, p.X, "fp32")
-    full = gpu_eval(torch_gpu, Vg, np.tile(sets, (1, 9)))     # k > 8: staged by a launch of its own
+    full = gpu_eval(torch_gpu, Vg, np.tile(sets, (1, 17)))    # more than 16 tiles: staged by a launch of its own
     say(f"one launch: n={n} d={d} l={l} k={k}")
     for _ in range(3):
         got = gpu_eval(torch_gpu, Vg, sets[:l])
@@ -166,7 +168,8 @@ def test_one_launch(torch_gpu, orc, n, d, l, k):
 
 
 @pytest.mark.parametrize("prec", ["fp16", "bf16"])
-@pytest.mark.parametrize("n,d,l,k", [(1, 1, 1, 1), (5000, 16, 64, 8), (5000, 17, 20, 3), (6001, 33, 16, 15), (6001, 64, 17, 16),
+@pytest.mark.parametrize("n,d,l,k", [(1, 1, 1, 1), (5000, 16, 64, 8), (5000, 17, 20, 3),
+                                     (6001, 32, 16, 31), (6001, 33, 16, 15), (6001, 64, 17, 16),
                                      (10_000, 70, 48, 8), (9000, 80, 65, 8), (20_011, 96, 5, 4), (7000, 109, 33, 7), (12_345, 128, 16, 8)])
 def test_one_launch_16_bit(torch_gpu, orc, prec, n, d, l, k):
     """Every compiled row length (32 x 32 tiles up to d = 16, then 1 .. 4
@@ -176,7 +179,7 @@ def test_one_launch_16_bit(torch_gpu, orc, prec, n, d, l, k):
     sets[3 % l, 0] = n
     sets[2 % l, 1:] = -1
     Vg, X64 = to_gpu(torch_gpu, p.X, prec)
-    full = gpu_eval(torch_gpu, Vg, np.tile(sets, (1, 17)))   # more than 8 tiles: staged by a launch of its own
+    full = gpu_eval(torch_gpu, Vg, np.tile(sets, (1, 17)))   # more than 16 tiles: staged by a launch of its own
     say(f"one launch: {prec} n={n} d={d} l={l} k={k}")
     for _ in range(3):
         got = gpu_eval(torch_gpu, Vg, sets[:l])
