@@ -413,8 +413,11 @@ __device__ __forceinline__ void wait_vmcnt() {
 }
 
 // Whether this is the last of `count` workgroups to get here; what the others
-// wrote before is visible to it.  `flag`: LDS nobody reads any more.
+// wrote before is visible to it.  `flag`: LDS nobody reads any more.  A
+// barrier alone does not wait for stores to leave the wavefront, and the
+// first thread's fence waits for its own: each wavefront waits for its own.
 __device__ __forceinline__ bool last_workgroup(int32_t *counter, int count, int *flag) {
+    wait_vmcnt<0>();
     __syncthreads();
     if (threadIdx.x == 0) {
         __threadfence();
