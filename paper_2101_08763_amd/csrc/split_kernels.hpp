@@ -76,10 +76,11 @@ __device__ __forceinline__ void split3(float x, __bf16 &hi, __bf16 &mid, __bf16 
 //   u = 2, NT = 2: quad grp / 2, products 4 t + 2 (grp % 2) + w;
 //   u = 3 or 4, NT = 3: quad grp, products 2 t + w;
 //   u = 5, NT = 4: as NT = 3, then in t = 3 products 2 grp + w of quad 4.
-// Small products come in earlier fragments than hi*hi.  Products above 5 are
-// zero.  (The bias -||s||^2/2 as three bf16 parts in a free quad saves the
-// accumulators' seeds, but beside hi*hi in one instruction it is truncated:
-// results 3e-8 too small at d <= 12, against 0.1e-8 from the seeds.)
+// A quad's small products come in earlier fragments than its hi*hi, or in the
+// same one.  Products above 5 are zero.  (The bias -||s||^2/2 as three bf16
+// parts in a free quad saves the accumulators' seeds, but beside hi*hi in one
+// instruction it is truncated: results 3e-8 too small at d <= 12, against
+// 0.1e-8 from the seeds.)
 template <int NT>
 struct Tail {
     static constexpr int OWN = 0, FIFTH = 1;  // which quad of coordinates
@@ -92,6 +93,8 @@ struct Tail {
         return t < 3 ? 2 * t + w : 2 * grp + w;
     }
     static constexpr int which(int t) { return NT == 4 && t == 3 ? FIFTH : OWN; }
+    // the first fragment that holds hi*hi of any quad
+    static constexpr int BIG = NT == 4 ? 2 : NT - 1;
 };
 
 // A quad of coordinates as its three bf16 parts.
@@ -349,6 +352,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
     // An accumulator for the small products; the few of a tail alone go onto
     // the bias one after the other (error above), which saves the additions.
     constexpr bool SMALL = NKB > 0;
+    constexpr int BIG = Tail<NT>::BIG;
     constexpr int HDR = split_hdr(NKB);
     // Short tiles: the fold of the running max is the busiest unit.
     constexpr bool PAIR = NKB == 0 && MODE == MODE_SUM && !HAS_M0;
@@ -536,16 +540,16 @@ __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
                     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, y, c, 0, 0, 0);
                 };
                 if (s < NT) {
-                    // the last fragment holds hi*hi; the others are small
-                    // products
+                    // fragments from BIG on hold hi*hi; the earlier ones
+                    // small products only
 #pragma unroll
                     for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
                         for (int h = 0; h < 2; ++h) {
-                            if (SMALL && s < NT - 1)
+                            if (SMALL && s < BIG)
                                 sml[rt][h] = mma(at[rt][s], b[h], s == 0 ? zero : sml[rt][h]);
                             else
-                                acc[rt][h] = mma(at[rt][s], b[h], SMALL || s == 0 ? seed[h] : acc[rt][h]);
+                                acc[rt][h] = mma(at[rt][s], b[h], s == (SMALL ? BIG : 0) ? seed[h] : acc[rt][h]);
                         }
                 } else {
                     const int kb = (s - NT) / 3, part = (s - NT) % 3;  // exemplar part: lo, mid, hi

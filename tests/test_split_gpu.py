@@ -121,6 +121,32 @@ def test_error_against_64_bits(torch_gpu, orc, scale):
     assert np.array_equal(got, gpu_eval(torch_gpu, V1, p.sets) * scale * scale)
 
 
+@pytest.mark.parametrize("d", [49, 52, 81, 84, 40, 68])
+def test_small_products_stay_apart(torch_gpu, d):
+    """Whole blocks and a tail.  The tail's hi*hi products cancel the bias
+    exactly (points hold half of the exemplar's tail); what is left of h is a
+    whole block's product with a small one, 64 * j / 8 = 8 j, which is gone
+    wherever it is added to the tail's 2^27 (multiples of 16 there).  Every
+    value is exact in fp32 if the accumulators stay apart, so f is too, up to
+    its sums of 512 terms and its own rounding: 12 roundings of 2^-24."""
+    n, r0 = 1001, 32 * (d // 32)
+    rng = np.random.default_rng(d)
+    X = np.zeros((n, d))
+    tail = slice(r0, min(d, r0 + 16))
+    X[0, tail] = 2.0 ** 12
+    X[1:, tail] = 2.0 ** 11
+    X[:, :r0] = 64.0
+    X[1:, 0] += rng.choice([1, 3, 5], n - 1) / 8
+    X = X.astype(np.float32)
+    Vg, X64 = to_gpu(torch_gpu, X, "fp32")
+    s = X64[0]
+    assert np.float32(0.5 * (s * s).sum()) == 0.5 * (s * s).sum()   # the bias is exact
+    want = 2.0 / n * np.maximum(0.0, X64 @ s - 0.5 * (s * s).sum()).sum()
+    got = gpu_eval(torch_gpu, Vg, np.zeros((1, 1), np.int32))[0]
+    say(f"accumulators apart: d={d} rel err {abs(got - want) / want:.2e}")
+    assert abs(got - want) <= 12 * 2.0 ** -24 * want
+
+
 # ---------------------------------------------------------------------------
 # Long fp16/bf16 rows as a tiled product (wide_kernels.hpp).
 # ---------------------------------------------------------------------------
