@@ -147,6 +147,25 @@ def test_small_products_stay_apart(torch_gpu, d):
     assert abs(got - want) <= 12 * 2.0 ** -24 * want
 
 
+@pytest.mark.parametrize("n", [128, 256])
+def test_wavefront_sums_round_once(torch_gpu, n):
+    """Even whole coordinates from 560 to 660: every h is a multiple of 2,
+    about 1.5e6 and exact, and so is a wavefront's sum of 16 of them (below
+    2^24 twos).  What is left to round is a workgroup's sum and the result:
+    2^-24 each (the fp64 sums in between add nothing)."""
+    d, l = 8, 512
+    rng = np.random.default_rng(n)
+    X = (2 * rng.integers(280, 331, (n, d))).astype(np.float32)
+    sets = rng.integers(0, n, (l, 2)).astype(np.int32)
+    Vg, X64 = to_gpu(torch_gpu, X, "fp32")
+    H = X64 @ X64.T - 0.5 * (X64 * X64).sum(1)
+    want = 2.0 / n * np.maximum(0.0, np.maximum(H[:, sets[:, 0]], H[:, sets[:, 1]])).sum(0)
+    got = gpu_eval(torch_gpu, Vg, sets)
+    worst = float((np.abs(got - want) / want).max())
+    say(f"sums round once: n={n} worst {worst / 2.0 ** -24:.2f} x 2^-24")
+    assert worst <= 2 * 2.0 ** -24
+
+
 # ---------------------------------------------------------------------------
 # Long fp16/bf16 rows as a tiled product (wide_kernels.hpp).
 # ---------------------------------------------------------------------------
