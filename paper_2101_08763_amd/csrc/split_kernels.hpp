@@ -143,9 +143,11 @@ __device__ __forceinline__ bf16x8 tail_fragment(const Quad *q, int grp, int t, b
 
 // One column group of one tile: lane L stages row `idx` of V (16 rows, lane
 // L % 16 of each group of lanes) and their biases -||s||^2/2 to `tile`.
-// ||s||^2: the lane's coordinates in order, then the four groups of lanes
-// with a fixed xor tree.  An invalid index is a zero column with bias
-// -FLT_MAX, which never wins the running max.
+// ||s||^2 in fp64 (the lane's blocks and tail in order, then the four groups
+// of lanes with a fixed xor tree), but for a block's eight coordinates where
+// there are many blocks: its error is the same for every point and does not
+// average out in f.  An invalid index is a zero column with bias -FLT_MAX, which never
+// wins the running max.
 template <int NKB, int NT>
 __device__ __forceinline__ void stage_columns(const float *__restrict__ V, int64_t n, int ld, int d, int64_t idx,
                                               int h, int lane, unsigned char *tile) {
@@ -153,7 +155,7 @@ __device__ __forceinline__ void stage_columns(const float *__restrict__ V, int64
     const bool valid = idx >= 0 && idx < n;
     const float *row = V + (valid ? idx : 0) * (int64_t)ld;
     bf16x8 *dst = reinterpret_cast<bf16x8 *>(tile + split_hdr(NKB)) + h * 64 + lane;
-    float sq = 0.0f;
+    double sq = 0.0;
     constexpr int NQ = NT == 4 ? 2 : 1;  // quads of the tail the lane reads
     float xt[NQ][4];
     const int r = d - 32 * NKB;  // coordinates of the tail
@@ -194,6 +196,7 @@ __device__ __forceinline__ void stage_columns(const float *__restrict__ V, int64
         for (int u = 0; u < BATCH; ++u) {
             if (k0 + u >= NKB) continue;
             bf16x8 p[3];
+            float b = 0.0f;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const float v = valid ? x[u][e] : 0.0f;
@@ -202,8 +205,10 @@ __device__ __forceinline__ void stage_columns(const float *__restrict__ V, int64
                 p[0][e] = lo;
                 p[1][e] = mid;
                 p[2][e] = hi;
-                sq = fmaf(v, v, sq);
+                if constexpr (NKB < 4) sq = fma((double)v, (double)v, sq);
+                else b = fmaf(v, v, b);
             }
+            sq += (double)b;
 #pragma unroll
             for (int q = 0; q < 3; ++q) dst[(NT + (k0 + u) * 3 + q) * 128] = p[q];
         }
@@ -212,14 +217,15 @@ __device__ __forceinline__ void stage_columns(const float *__restrict__ V, int64
         // every coordinate once: one lane group of those that read a quad
         const bool first = NT == 1 ? grp == 0 : NT == 2 ? (grp & 1) == 0 : true;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) sq = fmaf(first ? xt[0][e] : 0.0f, xt[0][e], sq);
+        for (int e = 0; e < 4; ++e) sq = fma((double)(first ? xt[0][e] : 0.0f), (double)xt[0][e], sq);
         if constexpr (NT == 4)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) sq = fmaf(grp == 0 ? xt[NQ - 1][e] : 0.0f, xt[NQ - 1][e], sq);
+            for (int e = 0; e < 4; ++e)
+                sq = fma((double)(grp == 0 ? xt[NQ - 1][e] : 0.0f), (double)xt[NQ - 1][e], sq);
     }
     sq += __shfl_xor(sq, 16);
     sq += __shfl_xor(sq, 32);
-    const float bias = valid ? -0.5f * sq : -FLT_MAX;
+    const float bias = valid ? (float)(-0.5 * sq) : -FLT_MAX;
     if constexpr (split_hdr(NKB) > 128) {
         if (grp == 0) reinterpret_cast<f32x4 *>(tile)[h * 16 + (lane & 15)] = f32x4{bias, bias, bias, bias};
     } else {

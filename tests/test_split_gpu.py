@@ -166,6 +166,42 @@ def test_wavefront_sums_round_once(torch_gpu, n):
     assert worst <= 2 * 2.0 ** -24
 
 
+def norm_errors(torch, prec, n, d, seed):
+    """The error of the bias -|s|^2 / 2 in units of its last place, for 16
+    exemplars: points with one coordinate M at a place where |s_0| is a power
+    of two, so <v, s> = M s_0 is exact, just above |s|^2 / 2, and h is their
+    difference without rounding."""
+    rng = np.random.default_rng(seed)
+    worst = 0.0
+    for rep in range(16):
+        s = rng.standard_normal(d)
+        s = s * np.sqrt(d / (s * s).sum())
+        s[0] = 2.0 ** -4
+        X = np.zeros((n, d))
+        X[0] = s
+        Xs, X64 = synth.rounded(X.astype(np.float32), prec)
+        B = 0.5 * (X64[0] ** 2).sum()
+        m = np.exp2(np.ceil(np.log2(B * 16)) - 8)                 # eight bits of M: exact in every storage type
+        X64[1:, 0] = np.ceil(B * 16 * 1.02 / m) * m
+        V, X64 = to_gpu(torch, X64.astype(np.float32), prec)
+        got = gpu_eval(torch, V, np.zeros((1, 1), np.int32))[0]
+        h = X64[1, 0] * X64[0, 0]                                # exact; h - B > 0
+        want = 2.0 / n * ((n - 1) * (h - B) + B)
+        ulp = np.exp2(np.floor(np.log2(B)) - 23)
+        worst = max(worst, abs(got - want) * n / 2 / n / ulp)
+    return worst
+
+
+@pytest.mark.parametrize("d", [4, 8, 20, 33, 100, 301, 512])
+def test_norms_round_once(torch_gpu, d):
+    """Half a unit for the bias, f's own sums (a few percent of a unit: h is
+    2 % of B), and above d = 127 the fp32 sums of eight squares, each below a
+    tenth of a unit: 0.63 in all when evaluated for these exemplars."""
+    worst = norm_errors(torch_gpu, "fp32", 4096, d, 31 + d)
+    say(f"norms: d={d} worst {worst:.2f} units")
+    assert worst <= 0.75
+
+
 # ---------------------------------------------------------------------------
 # Long fp16/bf16 rows as a tiled product (wide_kernels.hpp).
 # ---------------------------------------------------------------------------
