@@ -122,7 +122,15 @@ __device__ __forceinline__ void stage_tile_columns(const T *__restrict__ V, int6
     typename M::vec_t *dst = reinterpret_cast<typename M::vec_t *>(tile + HDR);
     const bool valid = idx >= 0 && idx < n;
     const int64_t r = valid ? idx : n;  // row n reads as zeros
+    // ||s||^2 of long 16-bit rows in fp64: a chain of hundreds of fp32 sums
+    // is up to 12 units of the last place off, the same for every point.
     float sq = 0.0f;
+    double sq64 = 0.0;
+    const bool long_row = sizeof(T) == 2 && nkb > 32;
+    auto add = [&](float x) {
+        if (long_row) sq64 = fma((double)x, (double)x, sq64);
+        else sq = fmaf(x, x, sq);
+    };
     // Up to KBATCH k-blocks are loaded before any is stored, so the loads
     // overlap (indices past the last block re-read it and are not
     // stored); ||s||^2 still runs over k-blocks and elements in order.
@@ -144,10 +152,7 @@ __device__ __forceinline__ void stage_tile_columns(const T *__restrict__ V, int6
                 const typename M::vec_t v = lanevec_keep<M>(vb[u], lanevec_live<M>(n, ld, r, kb, grp));
                 dst[(kb * NB + h) * 64 + lane] = v;
 #pragma unroll
-                for (int e = 0; e < M::VEC; ++e) {
-                    const float x = to_f32(v[e]);
-                    sq = fmaf(x, x, sq);
-                }
+                for (int e = 0; e < M::VEC; ++e) add(to_f32(v[e]));
             }
         }
     }
@@ -187,8 +192,11 @@ __device__ __forceinline__ void stage_tile_columns(const T *__restrict__ V, int6
         }
     }
 #pragma unroll
-    for (int off = M::TM; off < 64; off <<= 1) sq += __shfl_xor(sq, off);
-    const float b = valid ? -0.5f * sq : -FLT_MAX;
+    for (int off = M::TM; off < 64; off <<= 1) {
+        sq += __shfl_xor(sq, off);
+        if (long_row) sq64 += __shfl_xor(sq64, off);
+    }
+    const float b = !valid ? -FLT_MAX : long_row ? (float)(-0.5 * sq64) : -0.5f * sq;
     if (grp == 0) {
         if (splat) {
             // Exact three-way split: hi is b rounded to bf16, mid the

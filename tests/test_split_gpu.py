@@ -223,6 +223,34 @@ def test_long_rows_tiled(torch_gpu, orc, prec, n, d, l, k):
     assert np.array_equal(got, gpu_eval(torch_gpu, Vg, pad)), "blank and repeated members"
 
 
+@pytest.mark.parametrize("prec", ["fp16", "bf16"])
+@pytest.mark.parametrize("n,d", [(6144, 1025), (6300, 1100)])
+def test_long_rows_bias_seeds(torch_gpu, prec, n, d):
+    """1 024 coordinates whose product with the exemplar is exactly
+    |s|^2 / 2 = 2^25, and a last one that adds 3: exact when the accumulator
+    starts at the bias, a multiple of 4 when the bias comes last.  f sums
+    h = 3 over all points but the exemplar (2^25, exact): 12 roundings of
+    2^-24, and the last coordinate's share of |s|^2 / 2, 2^-25 in h."""
+    X = np.zeros((n, d))
+    X[0, :1024], X[1:, :1024] = 256.0, 128.0
+    X[0, d - 1], X[1:, d - 1] = 2.0 ** -12, 3 * 2.0 ** 12
+    Vg, X64 = to_gpu(torch_gpu, X.astype(np.float32), prec)
+    assert np.array_equal(X64, X)
+    want = 2.0 / n * np.maximum(0.0, X64 @ X64[0] - 0.5 * (X64[0] ** 2).sum()).sum()
+    got = gpu_eval(torch_gpu, Vg, np.zeros((1, 1), np.int32))[0]
+    say(f"long rows, bias: {prec} n={n} d={d} rel err {abs(got - want) / want:.2e}")
+    assert abs(got - want) <= 13 * 2.0 ** -24 * want
+
+
+@pytest.mark.parametrize("prec", ["fp16", "bf16"])
+@pytest.mark.parametrize("n,d", [(4096, 1025), (6144, 1025), (6144, 1536)])
+def test_long_norms_round_once(torch_gpu, prec, n, d):
+    """Long rows' biases, on both kernels: half a unit, and f's own sums."""
+    worst = norm_errors(torch_gpu, prec, n, d, 31 + d)
+    say(f"norms: {prec} n={n} d={d} worst {worst:.2f} units")
+    assert worst <= 0.6
+
+
 # ---------------------------------------------------------------------------
 # Small fp32 calls: tiles staged by the evaluation kernel, results written by
 # the workgroup that ends last.
