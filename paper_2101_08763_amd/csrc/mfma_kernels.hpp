@@ -441,6 +441,10 @@ __device__ __forceinline__ bool last_workgroup(int32_t *counter, int count, int 
 // out[j] = (2/n) sum_g partials[g][j] by one workgroup, in the order of
 // reduce_sets_kernel: 64 row lanes add rows q, q + 64, ..., then a pairwise
 // tree, fp64; NaN for a set with an invalid index.  `part`: 64 x 16 doubles.
+// The kernels' files are compiled without NaN semantics, so no NaN goes
+// through the arithmetic: sums are never negative, a row lane that finds an
+// invalid index holds -infinity, and the result's bits are stored as integers.
+typedef uint32_t bits32 __attribute__((may_alias));
 template <int NTHR>
 __device__ void finish_sets(const float *partials, int64_t G, int64_t lpad, int64_t l, int64_t n,
                             const int32_t *__restrict__ sets, int64_t k, float *__restrict__ out, double *part) {
@@ -457,14 +461,17 @@ __device__ void finish_sets(const float *partials, int64_t G, int64_t lpad, int6
                     bad |= idx != kEmptySlot && (idx < 0 || idx >= n);
                 }
             }
-            part[q * 16 + jl] = bad ? __builtin_nan("") : acc;
+            part[q * 16 + jl] = bad ? -__builtin_inf() : acc;
         }
         __syncthreads();
         for (int w = 32; w >= 1; w >>= 1) {
             for (int q = q0; q < w; q += NTHR / 16) part[q * 16 + jl] += part[(q + w) * 16 + jl];
             __syncthreads();
         }
-        if (q0 == 0 && j < l) out[j] = (float)(2.0 * part[jl] / (double)n);
+        if (q0 == 0 && j < l) {
+            const float f = (float)(2.0 * part[jl] / (double)n);
+            reinterpret_cast<bits32 *>(out)[j] = part[jl] < 0.0 ? 0x7fc00000u : __builtin_bit_cast(uint32_t, f);
+        }
         __syncthreads();
     }
 }
