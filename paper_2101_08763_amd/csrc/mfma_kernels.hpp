@@ -108,6 +108,9 @@ constexpr int tile_bytes_of(int hdr, int nff, int nhalf) { return hdr + nff * 10
 // elements in order, then the K-groups of the column with a fixed xor tree).
 // ---------------------------------------------------------------------------
 
+// The workgroup's number in a flat_grid.
+__device__ __forceinline__ int64_t flat_block() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
+
 // One column group of one tile: a wavefront stages column group h of `tile`
 // (in memory or LDS); `idx` is the row of the lane's column, any value.
 template <typename T, int TILE>
@@ -228,7 +231,8 @@ __global__ __launch_bounds__((64 * Mfma<T, TILE>::NB)) void pack_tiles_kernel(co
     using M = Mfma<T, TILE>;
     constexpr int NB = M::NB;
     const int64_t kt = (k + NB - 1) / NB;
-    const int64_t t = blockIdx.x;
+    const int64_t t = flat_block();
+    if (t >= (l + M::TM - 1) / M::TM * kt) return;
     const int64_t g = t / kt, q = t - (t / kt) * kt;
     const int lane = threadIdx.x & 63, h = threadIdx.x >> 6;
     const int64_t j = g * M::TM + lane % M::TM, p = q * NB + h;
@@ -1062,6 +1066,16 @@ inline int64_t device_cu_count() {
     }
     return c;
 }
+
+// `blocks` workgroups of `threads` as a grid (flat_block() numbers them): an
+// extent holds 32 bits of work-items, so larger counts take several rows, of
+// whole multiples of the 8 XCDs.  The last row may reach past `blocks`.
+inline dim3 flat_grid(int64_t blocks, int threads) {
+    const int64_t most = UINT32_MAX / threads / 8 * 8;
+    const int64_t rows = (blocks + most - 1) / most;
+    return rows <= 1 ? dim3((unsigned)blocks) : dim3((unsigned)(((blocks + rows - 1) / rows + 7) / 8 * 8), (unsigned)rows);
+}
+
 template <typename T, int TILE>
 hipError_t pack_launch(const MfmaPlan &pl, const void *V, int64_t n, int ld, const int32_t *sets, int64_t l,
                        int64_t k, void *tiles, hipStream_t st) {
@@ -1071,7 +1085,8 @@ hipError_t pack_launch(const MfmaPlan &pl, const void *V, int64_t n, int ld, con
     if (l < 1 || k < 1) return hipErrorInvalidValue;  // the kernel reads sets[0] at least
     const int64_t ngroups = (l + TILE - 1) / TILE;
     const int64_t kt = (k + Mfma<T, TILE>::NB - 1) / Mfma<T, TILE>::NB;
-    hipLaunchKernelGGL((pack_tiles_kernel<T, TILE>), dim3((unsigned)(ngroups * kt)), dim3(64 * Mfma<T, TILE>::NB), 0, st,
+    constexpr int threads = 64 * Mfma<T, TILE>::NB;
+    hipLaunchKernelGGL((pack_tiles_kernel<T, TILE>), flat_grid(ngroups * kt, threads), dim3(threads), 0, st,
                        (const T *)V, n, ld, sets, l, k, pl.nkb, pl.half, pl.splat, pl.il, (unsigned char *)tiles);
     return hipGetLastError();
 }

@@ -249,8 +249,9 @@ __global__ __launch_bounds__(128) void pack_split_kernel(const float *__restrict
                                                          const int32_t *__restrict__ sets, int64_t l, int64_t k,
                                                          unsigned char *__restrict__ tiles,
                                                          const int32_t *__restrict__ live, int64_t live0) {
-    const int64_t t = blockIdx.x;
+    const int64_t t = flat_block();
     const int64_t g = t / k, p = t - (t / k) * k;
+    if (g * kSplitSets >= l) return;
     if (live) {
         l = min(l, (int64_t)*live - live0);
         if (g * kSplitSets >= l) return;
@@ -746,7 +747,7 @@ template <int NKB, int NT>
 hipError_t split_pack_t(const void *V, int64_t n, int ld, int d, const int32_t *sets, int64_t l, int64_t k,
                         void *tiles, hipStream_t st, const int32_t *live, int64_t live0) {
     const int64_t ngroups = (l + kSplitSets - 1) / kSplitSets;
-    hipLaunchKernelGGL((pack_split_kernel<NKB, NT>), dim3((unsigned)(ngroups * k)), dim3(128), 0, st, (const float *)V,
+    hipLaunchKernelGGL((pack_split_kernel<NKB, NT>), flat_grid(ngroups * k, 128), dim3(128), 0, st, (const float *)V,
                        n, ld, d, sets, l, k, (unsigned char *)tiles, live, live0);
     return hipGetLastError();
 }
@@ -776,7 +777,7 @@ hipError_t split_launch(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st) {
     // MODE_ROWMAX: a workgroup sees every set group of its row block.
     int64_t grid = MODE == MODE_ROWMAX ? nrb : nrb * x.ngroups;
     if (MODE == MODE_SUM && persistent_mode() != kPersistOff) grid = std::min(grid, slots);
-    grid = std::min<int64_t>(grid, 1 << 24);
+    grid = std::min<int64_t>(grid, UINT32_MAX / (WAVES * 64));  // the workgroups share out what there is
     hipExtLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(WAVES * 64), lds, st, x.ev_start, x.ev_stop, 0,
                           (const float *)x.V, x.n, x.ld, pl.d, (const unsigned char *)x.tiles, x.kt, x.ngroups, nrb,
                           x.m0, x.partials, x.lpad, x.rowmax, x.sets, x.l, x.live, x.live0, x.m0_stride, x.counter, x.out);

@@ -66,7 +66,7 @@ __global__ __launch_bounds__(kWideWaves * 64, 2) void eval_wide_kernel(const T *
     const int ncb = (ngroups + GPB - 1) / GPB;
     const int units = nrb * ncb;
     const int per = (units + 7) / 8;
-    const int pos = (int)(blockIdx.x >> 3), u = (int)(blockIdx.x & 7) * per + pos;
+    const int b = (int)flat_block(), pos = b >> 3, u = (b & 7) * per + pos;
     if (pos >= per || u >= units) return;
     const int strip = u / (nrb * 8), width = min(8, ncb - strip * 8);
     const int in = u - strip * nrb * 8;
@@ -217,9 +217,9 @@ hipError_t wide_launch(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st) {
     }
     const int64_t nrb = (x.n + 2 * RT * 16 - 1) / (2 * RT * 16);
     const int64_t gpb = kWideStreams / PARTS, units = nrb * ((x.ngroups + gpb - 1) / gpb);
-    if (units > (1 << 27) || x.ngroups > INT32_MAX || x.kt > INT32_MAX) return hipErrorInvalidValue;
-    hipExtLaunchKernelGGL(kern, dim3((unsigned)((units + 7) / 8 * 8)), dim3(kWideWaves * 64), lds, st, x.ev_start, x.ev_stop,
-                          0, (const T *)x.V, x.n, x.ld, pl.nkb, (const unsigned char *)x.tiles, (int)x.kt, (int)x.ngroups,
+    if (units > (1 << 30) || x.ngroups > INT32_MAX || x.kt > INT32_MAX) return hipErrorInvalidValue;
+    hipExtLaunchKernelGGL(kern, flat_grid((units + 7) / 8 * 8, kWideWaves * 64), dim3(kWideWaves * 64), lds, st, x.ev_start,
+                          x.ev_stop, 0, (const T *)x.V, x.n, x.ld, pl.nkb, (const unsigned char *)x.tiles, (int)x.kt, (int)x.ngroups,
                           (int)nrb, x.partials, x.lpad);
     return hipGetLastError();
 }

@@ -1,0 +1,200 @@
+// The library's host code over a HIP runtime that launches nothing: every
+// runtime call the library makes is defined here and recorded, so that what
+// it allocates, announces and launches can be checked for any size on a
+// machine without a GPU (tests/test_host_runtime.py).  Usage: driver CHECK;
+// exit status 0 = every expectation of that check held.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+
+#include <map>
+#include <set>
+#include <string>
+#include <utility>
+#include <vector>
+
+#include "exemcl.h"
+
+// ---------------------------------------------------------------------------
+// The runtime.
+// ---------------------------------------------------------------------------
+namespace fake {
+struct Launch {
+    std::string name;
+    dim3 grid, block;
+    size_t lds;
+};
+std::vector<Launch> launches;
+std::vector<size_t> allocs;                      // sizes asked of the pool
+std::map<const void *, std::string> &kernels() {  // host stub -> device name (filled before main)
+    static std::map<const void *, std::string> m;
+    return m;
+}
+hipError_t last = hipSuccess;                    // until hipGetLastError
+std::set<std::pair<int, const void *>> announced;  // (device, kernel) with more than 64 KiB of LDS
+int device = 0;
+std::string fail_kernel;                         // launches of kernels with this in their name fail
+uintptr_t next_ptr = uintptr_t(1) << 40;
+size_t pool_left = SIZE_MAX;
+
+hipError_t check(const std::string &name, const void *f, dim3 g, dim3 b, size_t lds) {
+    if (!fail_kernel.empty() && name.find(fail_kernel) != std::string::npos) return hipErrorLaunchFailure;
+    // a grid's extents are 32 bits of work-items; y and z 16 bits of workgroups
+    if ((uint64_t)g.x * b.x > UINT32_MAX || g.x < 1 || g.y < 1 || g.y > 65535 || g.z != 1) return hipErrorInvalidConfiguration;
+    if ((uint64_t)b.x * b.y * b.z > 1024 || lds > 160 * 1024) return hipErrorInvalidConfiguration;
+    if (lds > 64 * 1024 && !announced.count({device, f})) return hipErrorInvalidValue;
+    return hipSuccess;
+}
+hipError_t launch(const void *f, dim3 g, dim3 b, size_t lds) {
+    const std::string name = kernels().count(f) ? kernels()[f] : "?";
+    launches.push_back({name, g, b, lds});
+    const hipError_t e = check(name, f, g, b, lds);
+    if (e != hipSuccess) last = e;
+    return e;
+}
+}  // namespace fake
+
+extern "C" {
+void **__hipRegisterFatBinary(const void *) {
+    static void *h;
+    return &h;
+}
+void __hipUnregisterFatBinary(void **) {}
+void __hipRegisterFunction(void **, const void *f, char *, const char *name, unsigned, void *, void *, void *, void *, int *) {
+    fake::kernels()[f] = name;
+}
+void __hipRegisterVar(void **, void *, char *, char *, int, size_t, int, int) {}
+static dim3 cfg_grid, cfg_block;
+static size_t cfg_lds;
+static hipStream_t cfg_stream;
+hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t lds, hipStream_t st) {
+    cfg_grid = g, cfg_block = b, cfg_lds = lds, cfg_stream = st;
+    return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *lds, hipStream_t *st) {
+    *g = cfg_grid, *b = cfg_block, *lds = cfg_lds, *st = cfg_stream;
+    return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **, size_t lds, hipStream_t) {
+    return fake::launch(f, g, b, lds);
+}
+hipError_t hipExtLaunchKernel(const void *f, dim3 g, dim3 b, void **, size_t lds, hipStream_t, hipEvent_t, hipEvent_t, int) {
+    return fake::launch(f, g, b, lds);
+}
+hipError_t hipFuncSetAttribute(const void *f, hipFuncAttribute, int) {
+    fake::announced.insert({fake::device, f});
+    return hipSuccess;
+}
+hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *, int, size_t lds) {
+    *n = lds > 80 * 1024 ? 1 : 2;
+    return hipSuccess;
+}
+hipError_t hipGetDevice(int *d) {
+    *d = fake::device;
+    return hipSuccess;
+}
+hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) {
+    *v = 256;  // compute units
+    return hipSuccess;
+}
+hipError_t hipMemPoolCreate(hipMemPool_t *p, const hipMemPoolProps *) {
+    *p = (hipMemPool_t)0x10;
+    return hipSuccess;
+}
+hipError_t hipMemPoolSetAttribute(hipMemPool_t, hipMemPoolAttr, void *) { return hipSuccess; }
+hipError_t hipMallocFromPoolAsync(void **p, size_t bytes, hipMemPool_t, hipStream_t) {
+    if (bytes > fake::pool_left) return hipErrorOutOfMemory;
+    fake::allocs.push_back(bytes);
+    *p = (void *)fake::next_ptr;
+    fake::next_ptr += (bytes + 4095) / 4096 * 4096;
+    return hipSuccess;
+}
+hipError_t hipFreeAsync(void *, hipStream_t) { return hipSuccess; }
+hipError_t hipFree(void *) { return hipSuccess; }
+hipError_t hipDeviceSynchronize() { return hipSuccess; }
+hipError_t hipGetLastError() {
+    const hipError_t e = fake::last;
+    fake::last = hipSuccess;
+    return e;
+}
+hipError_t hipHostMalloc(void **p, size_t bytes, unsigned) {
+    *p = malloc(bytes);
+    return hipSuccess;
+}
+hipError_t hipHostFree(void *p) {
+    free(p);
+    return hipSuccess;
+}
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t *, const void *) { return hipErrorInvalidValue; }
+hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) {
+    *s = (hipStream_t)0x20;
+    return hipSuccess;
+}
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) {
+    *e = (hipEvent_t)0x30;
+    return hipSuccess;
+}
+hipError_t hipEventCreate(hipEvent_t *e) { return hipEventCreateWithFlags(e, 0); }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) {
+    *ms = 0.0f;
+    return hipSuccess;
+}
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipMemcpyAsync(void *, const void *, size_t, hipMemcpyKind, hipStream_t) { return hipSuccess; }
+hipError_t hipGetSymbolAddress(void **p, const void *) {
+    *p = (void *)(uintptr_t(1) << 45);
+    return hipSuccess;
+}
+}
+
+// ---------------------------------------------------------------------------
+// The checks.
+// ---------------------------------------------------------------------------
+static int failures = 0;
+static void expect(bool ok, const char *what, const std::string &at = "") {
+    if (ok) return;
+    if (++failures <= 20) fprintf(stderr, "FAILED: %s %s\n", what, at.c_str());
+}
+
+static void *const kV = (void *)0x1000;
+static int32_t *const kI = (int32_t *)0x2000;
+static float *const kF = (float *)0x3000;
+
+// A stream of its own for every call: no block kept from another one.
+static void *fresh_stream() {
+    static uintptr_t s = 0x100000;
+    return (void *)(s += 0x100);
+}
+
+// Launch sizes.  Calls whose staging or evaluation takes more workgroups than
+// a grid's 32 bits of work-items hold in one extent.
+static void check_grids() {
+    struct Call { int64_t n, d, l, k; int prec; const char *what; };
+    const Call calls[] = {
+        {1000000, 1536, 275000, 2, EXEMCL_BF16, "2^23 workgroups of 512: long rows"},
+        {1000, 20, 40000000, 32, EXEMCL_FP16, "2^25 tiles of two wavefronts, 16 bits"},
+        {1000, 3, 36000000, 32, EXEMCL_FP32, "2^25 tiles of two wavefronts, fp32"},
+        {1000, 3, 40, 40000000, EXEMCL_FP32, "one set group's tiles"},
+    };
+    for (const Call &c : calls)
+        expect(exemplar_eval(kV, c.n, c.d, kI, c.l, c.k, c.prec, kF, fresh_stream()) == EXEMCL_OK, c.what);
+    setenv("EXEMCL_PERSIST", "0", 1);
+    expect(exemplar_eval(kV, 40000000, 300, kI, 4000, 1, EXEMCL_FP32, kF, fresh_stream()) == EXEMCL_OK, "plain grid");
+    unsetenv("EXEMCL_PERSIST");
+    expect(exemplar_gain((float *)kV, INT32_MAX, 3, kI, 2, kI, 2, kF, fresh_stream()) == EXEMCL_OK, "cache of 2^31 points");
+}
+
+int main(int argc, char **argv) {
+    const std::string what = argc > 1 ? argv[1] : "";
+    if (what == "grids") check_grids();
+    else expect(false, "no such check", what);
+    if (failures) fprintf(stderr, "%d checks failed\n", failures);
+    else printf("%s: checks passed\n", what.c_str());
+    return failures ? 1 : 0;
+}
