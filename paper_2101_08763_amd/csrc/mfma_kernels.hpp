@@ -1054,11 +1054,18 @@ inline int persistent_mode() {
     return EXEMCL_PERSIST_DEFAULT ? kPersistAuto : kPersistOff;
 }
 
+// The current device's index, for what is kept per device; -1: none.
+constexpr int kMaxDevices = 64;
+inline int current_device() {
+    int dev = 0;
+    return hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices ? dev : -1;
+}
+
 // Compute units of the current device (cached per device index).
 inline int64_t device_cu_count() {
-    static std::atomic<int> cus[64];  // 0 = not queried yet
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
+    static std::atomic<int> cus[kMaxDevices];  // 0 = not queried yet
+    const int dev = current_device();
+    if (dev < 0) return 0;
     int c = cus[dev].load(std::memory_order_relaxed);
     if (c == 0) {
         if (hipDeviceGetAttribute(&c, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;

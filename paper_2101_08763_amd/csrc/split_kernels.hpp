@@ -758,9 +758,12 @@ hipError_t split_launch(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st) {
     constexpr int lds = split_lds(NKB, NT, WAVES, GATHER);
     constexpr int rows = WAVES * RT * 16;
     if (MODE == MODE_SUM && pl.rows != rows) return hipErrorInvalidValue;
-    // Resident workgroups per CU, queried once per instantiation.
-    static std::atomic<int> occ{0};
-    int per_cu = occ.load(std::memory_order_relaxed);
+    // Resident workgroups per CU, queried once per instantiation and device
+    // (the LDS attribute holds for one device).
+    static std::atomic<int> occ[kMaxDevices];
+    const int dev = current_device();
+    if (dev < 0) return hipErrorInvalidDevice;
+    int per_cu = occ[dev].load(std::memory_order_relaxed);
     if (per_cu <= 0) {
         hipError_t e = hipSuccess;
         if (lds > 64 * 1024)
@@ -769,7 +772,7 @@ hipError_t split_launch(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st) {
             e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kern, WAVES * 64, lds);
         if (e != hipSuccess) return e;
         if (per_cu < 1) return hipErrorInvalidValue;
-        occ.store(per_cu, std::memory_order_relaxed);
+        occ[dev].store(per_cu, std::memory_order_relaxed);
     }
     const int64_t nrb = (x.n + rows - 1) / rows;
     const int64_t slots = (int64_t)per_cu * device_cu_count();

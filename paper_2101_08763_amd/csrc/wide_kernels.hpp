@@ -209,11 +209,13 @@ template <typename T, int RT, int PARTS>
 hipError_t wide_launch(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st) {
     auto kern = eval_wide_kernel<T, RT, PARTS>;
     constexpr int lds = 2 * wide_stage(RT);
-    static std::atomic<bool> ready{false};
-    if (!ready.load(std::memory_order_acquire)) {
+    static std::atomic<bool> ready[kMaxDevices];  // the attribute holds for one device
+    const int dev = current_device();
+    if (dev < 0) return hipErrorInvalidDevice;
+    if (!ready[dev].load(std::memory_order_acquire)) {
         const hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
-        ready.store(true, std::memory_order_release);
+        ready[dev].store(true, std::memory_order_release);
     }
     const int64_t nrb = (x.n + 2 * RT * 16 - 1) / (2 * RT * 16);
     const int64_t gpb = kWideStreams / PARTS, units = nrb * ((x.ngroups + gpb - 1) / gpb);

@@ -190,9 +190,28 @@ static void check_grids() {
     expect(exemplar_gain((float *)kV, INT32_MAX, 3, kI, 2, kI, 2, kF, fresh_stream()) == EXEMCL_OK, "cache of 2^31 points");
 }
 
+// Every device is told of a kernel's LDS before the kernel's first launch on it.
+static void check_devices() {
+    for (int dev : {0, 1, 0, 5}) {
+        fake::device = dev;
+        for (int64_t d : {3, 40, 100, 300, 512, 600, 1000, 1536})
+            for (int prec : {EXEMCL_FP32, EXEMCL_FP16, EXEMCL_BF16})
+                for (int64_t n : {900, 7000, 150000})
+                    for (int64_t l : {5, 3000})
+                        expect(exemplar_eval(kV, n, d, kI, l, 3, prec, kF, fresh_stream()) == EXEMCL_OK, "eval on device",
+                               std::to_string(dev) + " d " + std::to_string(d) + " precision " + std::to_string(prec));
+        for (int64_t d : {3, 100, 512, 600}) {
+            const std::string at = std::to_string(dev) + " d " + std::to_string(d);
+            expect(exemplar_gain((float *)kV, 7000, d, kI, 40, kI, 50, kF, fresh_stream()) == EXEMCL_OK, "gain on device", at);
+            expect(exemplar_greedy((float *)kV, 20000, d, 3, kI, kF, fresh_stream()) == EXEMCL_OK, "greedy on device", at);
+        }
+    }
+}
+
 int main(int argc, char **argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "grids") check_grids();
+    else if (what == "devices") check_devices();
     else expect(false, "no such check", what);
     if (failures) fprintf(stderr, "%d checks failed\n", failures);
     else printf("%s: checks passed\n", what.c_str());
