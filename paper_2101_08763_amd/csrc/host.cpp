@@ -302,7 +302,10 @@ int alloc_scratch(Scratch *s, int64_t bytes, hipStream_t st, Arena *arena = null
         s->ptr = nullptr;
         return EXEMCL_EDEVICE;
     }
-    // Keep the new block for this stream.
+    // Keep the new block for this stream, but never one whose count could not
+    // be cleared (the call fails, and gives the block back).
+    int32_t *zero = (int32_t *)((char *)s->ptr + bytes);
+    if (launch_zero((float *)zero, 1, st) != hipSuccess) return EXEMCL_EDEVICE;
     std::lock_guard<std::mutex> lk(g_keep_mu);
     StreamBlocks *entry = kept_for(dev, sid);
     if (!entry) {
@@ -330,8 +333,6 @@ int alloc_scratch(Scratch *s, int64_t bytes, hipStream_t st, Arena *arena = null
     }
     bl.push_back(KeptBlock{s->ptr, (size_t)bytes, true});
     s->kept = true;
-    int32_t *zero = (int32_t *)((char *)s->ptr + bytes);
-    if (launch_zero((float *)zero, 1, st) != hipSuccess) return EXEMCL_EDEVICE;
     s->counter = zero;
     return EXEMCL_OK;
 }

@@ -208,10 +208,29 @@ static void check_devices() {
     }
 }
 
+// A block whose count of workgroups could not be cleared is no block for a
+// later call on its stream.
+static void check_counter() {
+    void *st = fresh_stream();
+    fake::fail_kernel = "zero_kernel";
+    expect(exemplar_eval(kV, 1000, 8, kI, 16, 5, EXEMCL_FP32, kF, st) == EXEMCL_EDEVICE, "the failed launch is reported");
+    fake::fail_kernel = "";
+    fake::launches.clear();
+    const size_t before = fake::allocs.size();
+    expect(exemplar_eval(kV, 1000, 8, kI, 16, 5, EXEMCL_FP32, kF, st) == EXEMCL_OK, "the next call");
+    expect(fake::allocs.size() == before + 1, "a block of its own");
+    expect(fake::launches.size() == 2 && fake::launches[0].name.find("zero_kernel") != std::string::npos,
+           "its count cleared, then one launch");
+    fake::launches.clear();
+    expect(exemplar_eval(kV, 1000, 8, kI, 16, 5, EXEMCL_FP32, kF, st) == EXEMCL_OK, "a third call");
+    expect(fake::allocs.size() == before + 1 && fake::launches.size() == 1, "the kept block, one launch");
+}
+
 int main(int argc, char **argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "grids") check_grids();
     else if (what == "devices") check_devices();
+    else if (what == "counter") check_counter();
     else expect(false, "no such check", what);
     if (failures) fprintf(stderr, "%d checks failed\n", failures);
     else printf("%s: checks passed\n", what.c_str());
