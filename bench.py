@@ -150,8 +150,8 @@ KERNEL_FILES = {
     "eval_mfma_kernel": ["device.hpp", "internal.h", "kernels_mfma.hip", "kernels_mfma_bf16.hip",
                          "kernels_mfma_f16.hip", "kernels_mfma_f32.hip", "mfma_kernels.hpp"],
     "eval_split_kernel": ["device.hpp", "internal.h", "kernels_mfma.hip", "kernels_mfma_split.hip",
-                          "kernels_mfma_split_gain.hip", "kernels_mfma_split_gather.hip",
-                          "kernels_mfma_split_rowmax.hip", "mfma_kernels.hpp", "split_kernels.hpp"],
+                          "kernels_mfma_split_gain.hip", "kernels_mfma_split_gain_gather.hip",
+                          "kernels_mfma_split_gather.hip", "kernels_mfma_split_rowmax.hip", "mfma_kernels.hpp", "split_kernels.hpp"],
     "eval_wide_kernel": ["device.hpp", "internal.h", "kernels_mfma.hip", "kernels_mfma_wide.hip", "mfma_kernels.hpp",
                          "wide_kernels.hpp"],
     "eval_bigd_kernel": ["bigd_kernels.hpp", "device.hpp", "internal.h", "kernels_mfma.hip", "kernels_mfma_bigd.hip"],

@@ -22,7 +22,8 @@ ARCH = "gfx950"
 
 SOURCES = ["host.cpp", "kernels_mfma.hip", "kernels_mfma_f32.hip", "kernels_mfma_f16.hip",
            "kernels_mfma_bf16.hip", "kernels_mfma_split.hip", "kernels_mfma_split_gain.hip",
-           "kernels_mfma_split_gather.hip", "kernels_mfma_split_rowmax.hip", "kernels_mfma_wide.hip", "kernels_mfma_bigd.hip", "kernels_aux.hip", "kernels_greedy.hip",
+           "kernels_mfma_split_gather.hip", "kernels_mfma_split_gain_gather.hip", "kernels_mfma_split_rowmax.hip",
+           "kernels_mfma_wide.hip", "kernels_mfma_bigd.hip", "kernels_aux.hip", "kernels_greedy.hip",
            "kernels_sqnorm.hip"]
 FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-fvisibility=hidden",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

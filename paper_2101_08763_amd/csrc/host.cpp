@@ -468,6 +468,18 @@ hipError_t run_chunk(const Layout &L, char *base, const void *V, int64_t n, int6
 
 constexpr int64_t kGatherTiles = 8, kGatherShort = 32, kGatherUnits = 256, kGatherSets = 16, kGatherD = 128, kGatherRows = 128;
 
+// Few short tiles for few workgroups: each stages its own (a set group's, at
+// most kGatherTiles of them, twice that for short rows), which saves the
+// staging launch (bf16, 10 000 x 64, 48 sets of 8: 14.8 -> 11.8 us; 5 000 x
+// 16, 100 sets of 16: 15.7 -> 12).  More or longer rows are staged by too few
+// wavefronts that way (d = 325, 8 tiles: 31 us against 21; d = 128, 15 tiles:
+// 26.7 against 26.4).
+bool gathers_few(const Layout &L, int precision, int64_t n, int64_t d, int64_t k) {
+    return L.path == EXEMCL_PATH_MFMA && d <= kGatherD && mfma_gathers(precision, L.mp) &&
+           mfma_tiles_per_group(L.mp, k) <= (d <= kGatherShort ? 2 : 1) * kGatherTiles &&
+           (n + L.mp.rows - 1) / L.mp.rows * L.ngroups <= kGatherUnits;
+}
+
 // Queue one evaluation of `l` sets of `k` members (shared by eval and the
 // scoring half of gain).  `m0` (nullable) is the per-point initial max.
 //
@@ -514,16 +526,7 @@ int run_eval(const void *V, int64_t n, int64_t d, const int32_t *sets, int64_t l
     bool gather = false;
     int64_t lc = l;
     Scratch ws;
-    // Few short tiles for few workgroups: each stages its own (a set group's,
-    // at most kGatherTiles of them, twice that for short rows), which saves
-    // the staging launch (bf16, 10 000 x 64, 48 sets of 8: 14.8 -> 11.8 us;
-    // 5 000 x 16, 100 sets of 16: 15.7 -> 12).  More or longer rows are staged
-    // by too few wavefronts that way (d = 325, 8 tiles: 31 us against 21;
-    // d = 128, 15 tiles: 26.7 against 26.4).
-    const bool few = path == EXEMCL_PATH_MFMA && !m0 && d <= kGatherD && mfma_gathers(precision, L.mp) &&
-                     mfma_tiles_per_group(L.mp, k) <= (d <= kGatherShort ? 2 : 1) * kGatherTiles &&
-                     (n + L.mp.rows - 1) / L.mp.rows * L.ngroups <= kGatherUnits &&
-                     L.charge <= limit && L.off_tiles <= limit;
+    const bool few = !m0 && gathers_few(L, precision, n, d, k) && L.charge <= limit && L.off_tiles <= limit;
     if (few) {
         const int rc = alloc_scratch(&ws, L.off_tiles, st, arena);
         if (rc) return rc;
@@ -539,7 +542,7 @@ int run_eval(const void *V, int64_t n, int64_t d, const int32_t *sets, int64_t l
         if (lc <= unit) {
             // one set group's tiles do not fit, but what the call is
             // accounted for does: its partial sums alone
-            if (!L.mp.split || m0 || L.charge > limit || L.off_tiles > limit) return EXEMCL_ENOMEM;
+            if (!L.mp.split || L.charge > limit || L.off_tiles > limit) return EXEMCL_ENOMEM;
             const int rc = alloc_scratch(&ws, L.off_tiles, st, arena);
             if (rc) return rc;
             gather = true;
@@ -666,30 +669,34 @@ int run_streamed(const void *V, int64_t n, int64_t d, const int32_t *sets, int64
     const int64_t es = elem_size(precision);
     const int64_t ld = mfma_row_stride(precision, d);
     const int64_t ne = l * k;  // rows of the compact exemplar matrix: member (j, p) is row j*k + p
-    int64_t R = rows_per_block > 0 ? rows_per_block : std::max<int64_t>(1, ((int64_t)64 << 20) / (ld * es));
-    R = std::min(R, n);
-    const int64_t plan_n = R;  // one launch geometry for every block
-    MfmaPlan mp;
-    if (!mfma_plan(precision, d, plan_n, false, &mp)) return EXEMCL_EINVAL;
-    R = (R + mp.rows - 1) / mp.rows * mp.rows;  // whole row blocks of the kernel
+    int64_t R0 = rows_per_block > 0 ? rows_per_block : std::max<int64_t>(1, ((int64_t)64 << 20) / (ld * es));
+    R0 = std::min(R0, n);
 
-    // Device workspace: 2 row buffers, exemplars, remapped indices, tiles,
-    // one block's partials, the fp64 accumulator, flags and the results.
+    // Device workspace: 2 row buffers, exemplars, remapped indices, the fp64
+    // accumulator, flags, the results, one block's partials and the tiles.
+    // One launch geometry for every block.  Where that does not fit the
+    // limit, the smallest row blocks and, if the kernel can, no tiles (every
+    // workgroup stages them itself).
+    int64_t plan_n = R0, R = 0, bytes = 0, off_exem = 0, off_idx = 0, off_acc = 0, off_bad = 0, off_out = 0, off_work = 0;
+    bool gather = false;
+    MfmaPlan mp;
     Layout L;
-    if (!layout_eval(R, d, l, k, precision, EXEMCL_PATH_MFMA, &L, false, plan_n)) return EXEMCL_EINVAL;
-    const int64_t rows_bytes = align_up(R * ld * es, 256);
-    const int64_t off_rows1 = rows_bytes;
-    const int64_t off_exem = off_rows1 + rows_bytes;
-    const int64_t off_idx = off_exem + align_up(ne * ld * es, 256);
-    const int64_t off_acc = off_idx + align_up(ne * 4, 256);
-    const int64_t off_bad = off_acc + align_up(l * 8, 256);
-    const int64_t off_out = off_bad + align_up(l, 256);
-    const int64_t off_work = off_out + align_up(l * 4, 256);
-    const int64_t bytes = off_work + L.bytes;
-    // what the call is accounted for: rows as whole 16-byte vectors
-    const int64_t ldc = (d + 16 / es - 1) / (16 / es) * (16 / es);
-    const int64_t charge = 2 * align_up(R * ldc * es, 256) + align_up(ne * ldc * es, 256) + (off_work - off_idx) + L.charge;
-    if (charge > workspace_limit()) return EXEMCL_ENOMEM;
+    for (;;) {
+        if (!mfma_plan(precision, d, plan_n, false, &mp)) return EXEMCL_EINVAL;
+        R = (R0 + mp.rows - 1) / mp.rows * mp.rows;  // whole row blocks of the kernel
+        if (!layout_eval(R, d, l, k, precision, EXEMCL_PATH_MFMA, &L, false, plan_n)) return EXEMCL_EINVAL;
+        off_exem = 2 * align_up(R * ld * es, 256);
+        off_idx = off_exem + align_up(ne * ld * es, 256);
+        off_acc = off_idx + align_up(ne * 4, 256);
+        off_bad = off_acc + align_up(l * 8, 256);
+        off_out = off_bad + align_up(l, 256);
+        off_work = off_out + align_up(l * 4, 256);
+        bytes = off_work + (gather ? L.off_tiles : L.bytes);
+        if (bytes <= workspace_limit()) break;
+        if (gather || !mp.split) return EXEMCL_ENOMEM;
+        gather = true;
+        plan_n = 1;
+    }
 
     std::lock_guard<std::mutex> lk(g_stream_mu);
     const bool direct = ld == d && host_is_pinned(V);
@@ -706,7 +713,7 @@ int run_streamed(const void *V, int64_t n, int64_t d, const int32_t *sets, int64
     int rc = alloc_scratch(&ws, bytes, st);
     if (rc) return rc;
     char *base = (char *)ws.ptr;
-    void *drows[2] = {base, base + off_rows1};
+    void *drows[2] = {base, base + off_exem / 2};
     void *dexem = base + off_exem;
     int32_t *didx = (int32_t *)(base + off_idx);
     double *acc = (double *)(base + off_acc);
@@ -714,7 +721,7 @@ int run_streamed(const void *V, int64_t n, int64_t d, const int32_t *sets, int64
     float *dout = (float *)(base + off_out);
     char *work = base + off_work;
     float *partials = (float *)(work + L.off_partials);
-    void *tiles = work + L.off_tiles;
+    void *tiles = gather ? nullptr : work + L.off_tiles;
 
     StreamedState *ss = nullptr;
     if (streamed_state(&ss) != hipSuccess) return EXEMCL_EDEVICE;
@@ -752,7 +759,7 @@ int run_streamed(const void *V, int64_t n, int64_t d, const int32_t *sets, int64
     char *E = (char *)g_pin_exem.p;
     int32_t *ridx = (int32_t *)g_pin_idx.p;
     uint8_t *bad = (uint8_t *)g_pin_bad.p;
-    auto gather = [&](int64_t j0, int64_t j1) {
+    auto gather_rows = [&](int64_t j0, int64_t j1) {
         for (int64_t j = j0; j < j1; ++j) {
             bad[j] = 0;
             for (int64_t p = 0; p < k; ++p) {
@@ -775,10 +782,10 @@ int run_streamed(const void *V, int64_t n, int64_t d, const int32_t *sets, int64
         const unsigned hw = std::max(1u, std::thread::hardware_concurrency());
         const int64_t nt = std::min<int64_t>(std::min<int64_t>(16, hw), std::max<int64_t>(1, ne / 2048));
         if (nt <= 1) {
-            gather(0, l);
+            gather_rows(0, l);
         } else {
             std::vector<std::thread> th;
-            for (int64_t t = 0; t < nt; ++t) th.emplace_back(gather, l * t / nt, l * (t + 1) / nt);
+            for (int64_t t = 0; t < nt; ++t) th.emplace_back(gather_rows, l * t / nt, l * (t + 1) / nt);
             for (auto &x : th) x.join();
         }
     }
@@ -786,7 +793,8 @@ int run_streamed(const void *V, int64_t n, int64_t d, const int32_t *sets, int64
     if (e == hipSuccess) e = hipMemcpyAsync(dexem, E, (size_t)(ne * ld * es), hipMemcpyHostToDevice, st);
     if (e == hipSuccess) e = hipMemcpyAsync(didx, ridx, (size_t)(ne * 4), hipMemcpyHostToDevice, st);
     if (e == hipSuccess) e = hipMemcpyAsync(dbad, bad, (size_t)l, hipMemcpyHostToDevice, st);
-    if (e == hipSuccess) e = launch_pack(precision, mp, dexem, std::max<int64_t>(ne, 1), (int)ld, didx, l, k, tiles, st);
+    if (e == hipSuccess && tiles)
+        e = launch_pack(precision, mp, dexem, std::max<int64_t>(ne, 1), (int)ld, didx, l, k, tiles, st);
     for (int64_t b = 0; b < nblocks && e == hipSuccess; ++b) {
         const int i = (int)(b & 1);
         const int64_t rows = std::min(R, n - b * R);
@@ -797,7 +805,8 @@ int run_streamed(const void *V, int64_t n, int64_t d, const int32_t *sets, int64
         if (e == hipSuccess) {
             ProfRange pr(st);
             e = launch_mfma(precision, MODE_SUM, mp, drows[i], rows, (int)ld, tiles, mfma_tiles_per_group(mp, k),
-                            Lb.ngroups, Lb.gpc, nullptr, partials, Lb.lpad, nullptr, st, pr.a, pr.b);
+                            Lb.ngroups, Lb.gpc, nullptr, partials, Lb.lpad, nullptr, st, pr.a, pr.b, didx, l, k, nullptr,
+                            0, 1, nullptr, nullptr, dexem, ne);
             if (e == hipSuccess) pr.end();
         }
         if (e == hipSuccess) e = launch_accum(partials, Lb.G, Lb.lpad, l, b == 0, acc, st);
@@ -914,31 +923,41 @@ EXEMCL_API int exemplar_gain(const float *V, int64_t n, int64_t d, const int32_t
     const int64_t off_tiles = align_up(n * 4, 256);
     const int64_t charge = align_up(off_tiles + (mp.split ? split_charge(0, d, k, 1) : ngroups * tile_bytes(mp)), 256);
     const int64_t rows_charge = charge_rows(EXEMCL_FP32, n, d);
-    if (charge + rows_charge > workspace_limit()) return EXEMCL_ENOMEM;
-    // Set groups of S staged at a time: all, unless that takes more than the
-    // call is accounted for.
-    const int64_t gs = std::max<int64_t>(1, std::min(ngroups, (charge - off_tiles) / tile_bytes(mp)));
+    const int64_t limit = workspace_limit() - rows_charge;
+    Layout L1;
+    if (!layout_eval(n, d, 1, 1, EXEMCL_FP32, EXEMCL_PATH_MFMA, &L1, true)) return EXEMCL_EINVAL;
+    // Nothing is queued unless the cache, S and the scoring of one set group
+    // fit.
+    if (charge + L1.charge > limit) return EXEMCL_ENOMEM;
+    // Set groups of S staged at a time: all, unless that takes more than a
+    // limit leaves beside the scoring; none, if not even one fits (the kernel
+    // then stages them itself).
+    int64_t gs = std::min(ngroups, (limit - off_tiles - L1.charge) / tile_bytes(mp));
     MfmaRows rows;
     rc = prepare_rows(V, n, d, EXEMCL_FP32, st, &rows);
     if (rc) return rc;
     Scratch ws;
-    rc = alloc_scratch(&ws, align_up(off_tiles + gs * tile_bytes(mp), 256), st);
-    if (rc) return rc;
+    for (;; gs /= 2) {
+        rc = alloc_scratch(&ws, off_tiles + gs * tile_bytes(mp), st);
+        if (rc == EXEMCL_OK) break;
+        if (rc != EXEMCL_ENOMEM || !mp.split || gs == 0) return rc;
+    }
+    const int64_t held = rows_charge + align_up(off_tiles + gs * tile_bytes(mp), 256);
     char *base = (char *)ws.ptr;
     float *gcache = (float *)base;
-    void *tiles = base + off_tiles;
+    void *tiles = gs > 0 ? base + off_tiles : nullptr;
     hipError_t e = hipSuccess;
-    for (int64_t g = 0; g < ngroups && e == hipSuccess; g += gs) {
-        const int64_t cnt = std::min(k - g * tm, gs * tm);
-        e = launch_pack(EXEMCL_FP32, mp, rows.V, n, (int)rows.ld, S + g * tm, cnt, 1, tiles, st);
+    for (int64_t g = 0, step = gs > 0 ? gs : ngroups; g < ngroups && e == hipSuccess; g += step) {
+        const int64_t cnt = std::min(k - g * tm, step * tm), groups = (cnt + tm - 1) / tm;
+        if (tiles) e = launch_pack(EXEMCL_FP32, mp, rows.V, n, (int)rows.ld, S + g * tm, cnt, 1, tiles, st);
         if (e == hipSuccess)
-            e = launch_mfma(EXEMCL_FP32, MODE_ROWMAX, mp, rows.V, n, (int)rows.ld, tiles, 1, (cnt + tm - 1) / tm,
-                            (cnt + tm - 1) / tm, g ? gcache : nullptr, nullptr, 0, gcache, st);
+            e = launch_mfma(EXEMCL_FP32, MODE_ROWMAX, mp, rows.V, n, (int)rows.ld, tiles, 1, groups, groups,
+                            g ? gcache : nullptr, nullptr, 0, gcache, st, nullptr, nullptr, S + g * tm, cnt, 1);
     }
     if (e != hipSuccess) return EXEMCL_EDEVICE;
     // Score every S u {c}: single-member sets {c} with the running max
     // started at g(v) instead of e0's 0.
-    return run_eval(V, n, d, cands, l, 1, EXEMCL_FP32, gcache, S, k, out, st, &rows, rows_charge + charge, nullptr, true);
+    return run_eval(V, n, d, cands, l, 1, EXEMCL_FP32, gcache, S, k, out, st, &rows, held, nullptr, true);
 }
 
 EXEMCL_API int exemplar_greedy(const float *V, int64_t n, int64_t d, int64_t K, int32_t *S_out, float *f_out,
@@ -953,15 +972,14 @@ EXEMCL_API int exemplar_greedy(const float *V, int64_t n, int64_t d, int64_t K, 
 
     // State kept on the device across rounds: the candidate list V (all of
     // it; taken ones are skipped by the argmax), the taken flags, the cache
-    // g(v) double-buffered, the round's scores and one staged tile for the
-    // element just added.
+    // g(v) double-buffered and the round's scores.  The tile of the element
+    // just added is staged over the scoring's, which are done by then.
     const int64_t nb = argmax_blocks(n);
     const int64_t off_taken = align_up(n * 4, 256);
     const int64_t off_g0 = align_up(off_taken + n, 256);
     const int64_t off_g1 = align_up(off_g0 + n * 4, 256);
     const int64_t off_scores = align_up(off_g1 + n * 4, 256);
-    const int64_t off_ctile = align_up(off_scores + n * 4, 256);
-    const int64_t off_pval = align_up(off_ctile + tile_bytes(mp), 256);
+    const int64_t off_pval = align_up(off_scores + n * 4, 256);
     const int64_t off_pidx = align_up(off_pval + nb * 4, 256);
     const int64_t plain = align_up(off_pidx + nb * 4, 256);
     // Lazy rounds keep the scores as gains, and a list of the candidates that
@@ -980,13 +998,17 @@ EXEMCL_API int exemplar_greedy(const float *V, int64_t n, int64_t d, int64_t K, 
     // Candidates are scored in chunks whose temporary memory stays under a
     // fixed size (the same halving as for a batch that does not fit).
     constexpr int64_t kScoringBytes = int64_t(1) << 30;
+    // The call is accounted for with a tile of its own for that element.
+    const int64_t charge = plain + align_up(mp.split ? split_charge(0, d, 1, 1) : tile_bytes(mp), 256);
     const int64_t limit = workspace_limit() - charge_rows(EXEMCL_FP32, n, d);
-    if (limit < plain) return EXEMCL_ENOMEM;
+    Layout L;
+    if (!layout_eval(n, d, 1, 1, EXEMCL_FP32, EXEMCL_PATH_MFMA, &L, true)) return EXEMCL_EINVAL;
+    if (charge + L.charge > limit) return EXEMCL_ENOMEM;
     MfmaRows rows;
     int rc = prepare_rows(V, n, d, EXEMCL_FP32, st, &rows);
     if (rc) return rc;
     int64_t lc = n;
-    Layout L;
+    bool gather = false;  // not even one set group's tiles fit: staged by the kernels
     Scratch ws;
     for (;;) {
         if (!layout_eval(n, d, lc, 1, EXEMCL_FP32, EXEMCL_PATH_MFMA, &L, true)) return EXEMCL_EINVAL;
@@ -995,8 +1017,8 @@ EXEMCL_API int exemplar_greedy(const float *V, int64_t n, int64_t d, int64_t K, 
             lazy = false;
             fixed = plain;
         }
-        if (small && fixed + L.charge <= limit && (fixed + L.bytes <= limit || lc <= L.unit)) {
-            rc = alloc_scratch(&ws, fixed + L.bytes, st);
+        if (small && charge + L.charge <= limit) {
+            rc = fixed + L.bytes <= limit ? alloc_scratch(&ws, fixed + L.bytes, st) : EXEMCL_ENOMEM;
             if (rc == EXEMCL_OK) break;
             if (rc != EXEMCL_ENOMEM) return rc;
             if (lazy) {
@@ -1005,7 +1027,13 @@ EXEMCL_API int exemplar_greedy(const float *V, int64_t n, int64_t d, int64_t K, 
                 continue;
             }
         }
-        if (lc <= L.unit) return EXEMCL_ENOMEM;
+        if (lc <= L.unit) {
+            if (!mp.split || plain + L.off_tiles > limit) return EXEMCL_ENOMEM;
+            rc = alloc_scratch(&ws, plain + L.off_tiles, st);
+            if (rc) return rc;
+            gather = true;
+            break;
+        }
         lc = ((lc + 1) / 2 + L.unit - 1) / L.unit * L.unit;
     }
     lazy = lazy && lc >= kGreedyProbes;
@@ -1014,10 +1042,10 @@ EXEMCL_API int exemplar_greedy(const float *V, int64_t n, int64_t d, int64_t K, 
     uint8_t *taken = (uint8_t *)(base + off_taken);
     float *g_cur = (float *)(base + off_g0), *g_next = (float *)(base + off_g1);
     float *scores = (float *)(base + off_scores);
-    void *ctile = base + off_ctile;
     float *pval = (float *)(base + off_pval);
     int32_t *pidx = (int32_t *)(base + off_pidx);
     char *work = base + fixed;
+    void *ctile = gather ? nullptr : work + L.off_tiles;
 
     int32_t *list = (int32_t *)(base + off_list), *probes = (int32_t *)(base + off_probes);
     float *lscores = (float *)(base + off_lscores), *pscores = (float *)(base + off_pscores);
@@ -1067,7 +1095,7 @@ EXEMCL_API int exemplar_greedy(const float *V, int64_t n, int64_t d, int64_t K, 
                               st, true, false, &state->count, j0);
             else
                 e = run_chunk(Lj, work, V, n, d, &rows, cands + j0, lj, 1, EXEMCL_FP32, g_cur, nullptr, 0,
-                              scores + j0, st);
+                              scores + j0, st, true, gather);
         }
         if (e == hipSuccess)
             e = lazy && i > 0 ? launch_greedy_pick(probes, pscores, list, lscores, f_out + i - 1, state, scores, taken, n,
@@ -1075,10 +1103,11 @@ EXEMCL_API int exemplar_greedy(const float *V, int64_t n, int64_t d, int64_t K, 
                               : launch_argmax(scores, taken, n, pval, pidx, S_out + i, f_out + i, st);
         if (i + 1 == K) break;
         // g <- max(g, h_{c*}) with c* read from S_out[i] on the device.
-        if (e == hipSuccess) e = launch_pack(EXEMCL_FP32, mp, rows.V, n, (int)rows.ld, S_out + i, 1, 1, ctile, st);
+        if (e == hipSuccess && ctile)
+            e = launch_pack(EXEMCL_FP32, mp, rows.V, n, (int)rows.ld, S_out + i, 1, 1, ctile, st);
         if (e == hipSuccess)
             e = launch_mfma(EXEMCL_FP32, MODE_ROWMAX, mp, rows.V, n, (int)rows.ld, ctile, 1, 1, 1, g_cur, nullptr, 0,
-                            g_next, st);
+                            g_next, st, nullptr, nullptr, S_out + i, 1, 1);
         std::swap(g_cur, g_next);
     }
     return status_of(e);
@@ -1100,7 +1129,9 @@ EXEMCL_API int exemplar_plan(int64_t n, int64_t d, int64_t l, int64_t k, int pre
     Layout L;
     if (!layout_eval(n, d, l, k, precision, p, &L)) return EXEMCL_EINVAL;
     if (path) *path = p;
-    if (workspace_bytes) *workspace_bytes = L.charge + (p == EXEMCL_PATH_MFMA ? charge_rows(precision, n, d) : 0);
+    if (workspace_bytes)
+        *workspace_bytes = std::max(L.charge, gathers_few(L, precision, n, d, k) ? L.off_tiles : L.bytes) +
+                           (p == EXEMCL_PATH_MFMA ? charge_rows(precision, n, d) : 0);
     return EXEMCL_OK;
 }
 

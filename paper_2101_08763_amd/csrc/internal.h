@@ -57,7 +57,9 @@ struct MfmaArgs {
     // by the evaluation kernel.
     const int32_t *sets = nullptr;
     int64_t l = 0, k = 0;
-    // split, m0 set: the number of sets counted on the device (null: all);
+    const void *E = nullptr;  // split, tiles null: the ne rows the sets address (null: V's)
+    int64_t ne = 0;
+    // split, m0 set, tiles not null: the number of sets counted on the device (null: all);
     // this launch's are those from live0 on.
     const int32_t *live = nullptr;
     int64_t live0 = 0;
@@ -85,9 +87,11 @@ hipError_t eval_run_bf16(const MfmaPlan &pl, int mode, const MfmaArgs &x, hipStr
 hipError_t split_pack_run(const MfmaPlan &pl, const void *V, int64_t n, int ld, const int32_t *sets, int64_t l,
                           int64_t k, void *tiles, hipStream_t st, const int32_t *live, int64_t live0);
 hipError_t split_sum_run(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st);      // MODE_SUM, m0 null
-hipError_t split_gather_run(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st);   // the same, tiles null
 hipError_t split_gain_run(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st);     // MODE_SUM from m0
 hipError_t split_rowmax_run(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st);   // MODE_ROWMAX, m0 nullable
+hipError_t split_gather_run(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st);         // the three with tiles null
+hipError_t split_gain_gather_run(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st);
+hipError_t split_rowmax_gather_run(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st);
 // Long fp16/bf16 rows (kernels_mfma_wide.hip).
 hipError_t wide_run(int prec, const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st);
 // The d > 512 kernel (kernels_mfma_bigd.hip), every storage type.
@@ -140,13 +144,14 @@ enum Mode { MODE_SUM = 0, MODE_ROWMAX = 1 };
 // of row block rb of max(m0(v), max_p (<v, s_jp> - ||s_jp||^2 / 2)); m0 = 0
 // when null (fp32 only otherwise).  MODE_ROWMAX (fp32, groups_per_chunk =
 // ngroups) instead writes rowmax[v] = max(m0(v), 0, max over all staged
-// columns); rowmax must not alias m0.
+// columns); rowmax must not alias m0, but for plans with `split` may be m0.
 hipError_t launch_mfma(int prec, int mode, const MfmaPlan &pl, const void *V, int64_t n, int ld,
                        const void *tiles, int64_t kt, int64_t ngroups, int64_t groups_per_chunk,
                        const float *m0, float *partials, int64_t lpad, float *rowmax, hipStream_t st,
                        hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr,
                        const int32_t *sets = nullptr, int64_t l = 0, int64_t k = 0, const int32_t *live = nullptr,
-                       int64_t live0 = 0, int m0_stride = 1, int32_t *counter = nullptr, float *out = nullptr);
+                       int64_t live0 = 0, int m0_stride = 1, int32_t *counter = nullptr, float *out = nullptr,
+                       const void *E = nullptr, int64_t ne = 0);
 
 // Bytes a call on the split kernels is accounted for: what decides whether it
 // fits a limit, and into how many chunks (of split_charge_unit sets at least)

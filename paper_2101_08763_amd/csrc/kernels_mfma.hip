@@ -198,17 +198,17 @@ hipError_t launch_mfma(int prec, int mode, const MfmaPlan &pl, const void *V, in
                        int64_t kt, int64_t ngroups, int64_t gpc, const float *m0, float *partials, int64_t lpad,
                        float *rowmax, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop, const int32_t *sets,
                        int64_t l, int64_t k, const int32_t *live, int64_t live0, int m0_stride, int32_t *counter,
-                       float *out) {
-    const MfmaArgs x{V,      n,    ld, tiles, kt, ngroups, gpc,       m0,      partials, lpad,
-                     rowmax, sets, l,  k,     live, live0, m0_stride, counter, out,      ev_start, ev_stop};
-    if ((live || m0_stride != 1) && !(pl.split && m0)) return hipErrorInvalidValue;
+                       float *out, const void *E, int64_t ne) {
+    const MfmaArgs x{V,    n, ld, tiles, kt, ngroups, gpc,   m0,        partials, lpad, rowmax,
+                     sets, l, k,  E,     ne, live,    live0, m0_stride, counter,  out,  ev_start, ev_stop};
+    if ((live || m0_stride != 1) && !(pl.split && m0 && tiles)) return hipErrorInvalidValue;
+    if (!tiles && !(pl.split || (mfma_gathers(prec, pl) && mode == MODE_SUM && !m0))) return hipErrorInvalidValue;
     if (pl.bigd) return bigd_run(prec, mode, pl, x, st);
     if (pl.wide) return mode == MODE_SUM ? wide_run(prec, pl, x, st) : hipErrorInvalidValue;
     if (pl.split)
-        return mode == MODE_ROWMAX ? split_rowmax_run(pl, x, st)
-               : m0                ? split_gain_run(pl, x, st)
-               : !tiles            ? split_gather_run(pl, x, st)
-                                   : split_sum_run(pl, x, st);
+        return mode == MODE_ROWMAX ? (tiles ? split_rowmax_run(pl, x, st) : split_rowmax_gather_run(pl, x, st))
+               : m0                ? (tiles ? split_gain_run(pl, x, st) : split_gain_gather_run(pl, x, st))
+                                   : (tiles ? split_sum_run(pl, x, st) : split_gather_run(pl, x, st));
     switch (prec) {
     case P_FP32: return eval_run_f32(pl, mode, x, st);
     case P_FP16: return mode == MODE_SUM ? eval_run_f16(pl, mode, x, st) : hipErrorInvalidValue;

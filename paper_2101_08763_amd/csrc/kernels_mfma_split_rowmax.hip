@@ -13,4 +13,14 @@ hipError_t split_rowmax_run(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t s
     return hipErrorInvalidValue;
 }
 
+hipError_t split_rowmax_gather_run(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st) {
+    switch (split_key(pl.nkb, pl.nt)) {
+#define EXEMCL_CASE(NKB, NT) \
+    case split_key(NKB, NT): return split_eval_t<NKB, NT, MODE_ROWMAX, true, true>(pl, x, st);
+        EXEMCL_SPLIT_CASES(EXEMCL_CASE)
+#undef EXEMCL_CASE
+    }
+    return hipErrorInvalidValue;
+}
+
 }  // namespace exemcl

@@ -330,6 +330,8 @@ constexpr int kRowmaxWaves = 4, kRowmaxRt = 2;
 //
 // GATHER: no staged tiles in memory; the workgroup stages every tile into LDS
 // itself, from the set indices, with the same code and so the same bits.
+// `tiles` is then the matrix those indices address (rows of `ld`, like V's),
+// and `live0` its number of rows.
 // ---------------------------------------------------------------------------
 template <int NKB, int NT, int RT, int WAVES, int MODE, bool HAS_M0, bool GATHER>
 __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
@@ -337,7 +339,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
     int64_t ngroups, int64_t nrb, const float *m0, float *partials, int64_t lpad, float *rowmax,
     const int32_t *__restrict__ sets, int64_t l, const int32_t *__restrict__ live, int64_t live0, int m0_stride,
     int32_t *counter, float *__restrict__ out) {
-    if constexpr (HAS_M0 && MODE == MODE_SUM) {
+    if constexpr (HAS_M0 && MODE == MODE_SUM && !GATHER) {
         // scoring a list whose length was counted on the device
         if (live) {
             const int64_t cnt = (int64_t)*live - live0;
@@ -395,7 +397,8 @@ __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
                     const int64_t g = t / kt, q = t - g * kt;
                     const int64_t j = (g0 + g) * kSplitSets + (c & 1) * 16 + lr;
                     const int64_t idx = j < l ? (int64_t)sets[j * kt + q] : -1;
-                    stage_columns<NKB, NT>(V, n, ldv, d, idx, c & 1, lane, buf + (c >> 1) * TB);
+                    stage_columns<NKB, NT>(reinterpret_cast<const float *>(tiles), live0, ldv, d, idx, c & 1, lane,
+                                           buf + (c >> 1) * TB);
                 }
                 return;
             }
@@ -730,7 +733,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
         if (seg > 0) __syncthreads();
         segment(rb, g0, g1);
     }
-    if constexpr (GATHER) {
+    if constexpr (GATHER && MODE == MODE_SUM && !HAS_M0) {
         // `counter`: the workgroup that ends last adds the partial sums, in
         // the second pass's order (reduce_sets_kernel), and saves its launch.
         if (counter && last_workgroup(counter, (int)gridDim.x, reinterpret_cast<int *>(red))) {
@@ -782,8 +785,10 @@ hipError_t split_launch(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st) {
     if (MODE == MODE_SUM && persistent_mode() != kPersistOff) grid = std::min(grid, slots);
     grid = std::min<int64_t>(grid, UINT32_MAX / (WAVES * 64));  // the workgroups share out what there is
     hipExtLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(WAVES * 64), lds, st, x.ev_start, x.ev_stop, 0,
-                          (const float *)x.V, x.n, x.ld, pl.d, (const unsigned char *)x.tiles, x.kt, x.ngroups, nrb,
-                          x.m0, x.partials, x.lpad, x.rowmax, x.sets, x.l, x.live, x.live0, x.m0_stride, x.counter, x.out);
+                          (const float *)x.V, x.n, x.ld, pl.d,
+                          (const unsigned char *)(!GATHER ? x.tiles : x.E ? x.E : x.V), x.kt, x.ngroups, nrb, x.m0,
+                          x.partials, x.lpad, x.rowmax, x.sets, x.l, x.live, !GATHER ? x.live0 : x.E ? x.ne : x.n,
+                          x.m0_stride, x.counter, x.out);
     return hipGetLastError();
 }
 

@@ -9,6 +9,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <map>
 #include <set>
 #include <string>
@@ -226,11 +227,117 @@ static void check_counter() {
     expect(fake::allocs.size() == before + 1 && fake::launches.size() == 1, "the kept block, one launch");
 }
 
+// EXEMCL_WORKSPACE_LIMIT.  A call that is accepted never holds more than the
+// limit (the 256 bytes behind a block, where a count is kept, aside), and
+// every limit under which fp32 tiles of 4 bytes per coordinate fit is
+// accepted, whatever the present tiles need.
+struct Call {
+    enum Kind { EVAL, GAIN, GREEDY, STREAMED } kind;
+    int64_t n, d, l, k;
+    int prec;
+    std::string text() const {
+        static const char *names[] = {"eval", "gain", "greedy", "streamed"};
+        return std::string(names[kind]) + " n " + std::to_string(n) + " d " + std::to_string(d) + " l " +
+               std::to_string(l) + " k " + std::to_string(k) + " precision " + std::to_string(prec);
+    }
+};
+
+static int run(const Call &c, int64_t limit, int64_t *held) {
+    static std::vector<float> V, out;
+    static std::vector<int32_t> sets;
+    setenv("EXEMCL_WORKSPACE_LIMIT", std::to_string(limit).c_str(), 1);
+    fake::allocs.clear();
+    fake::launches.clear();
+    int rc = -1;
+    void *st = fresh_stream();
+    if (c.kind == Call::EVAL) rc = exemplar_eval(kV, c.n, c.d, kI, c.l, c.k, c.prec, kF, st);
+    if (c.kind == Call::GAIN) rc = exemplar_gain((float *)kV, c.n, c.d, kI, c.k, kI, c.l, kF, st);
+    if (c.kind == Call::GREEDY) rc = exemplar_greedy((float *)kV, c.n, c.d, c.k, kI, kF, st);
+    if (c.kind == Call::STREAMED) {  // reads host memory
+        V.resize(std::max<size_t>(V.size(), (size_t)(c.n * c.d)));
+        out.resize(std::max<size_t>(out.size(), (size_t)c.l));
+        sets.assign((size_t)(c.l * c.k), 0);
+        rc = exemplar_eval_streamed(V.data(), c.n, c.d, sets.data(), c.l, c.k, c.prec, 0, out.data(), st);
+    }
+    unsetenv("EXEMCL_WORKSPACE_LIMIT");
+    *held = 0;
+    for (size_t b : fake::allocs) *held += (int64_t)b - 256;
+    return rc;
+}
+
+// What a call needs with fp32 tiles of 4 bytes per coordinate: blocks of 8
+// coordinates and 32 sets up to d = 256, of 16 and 16 above, whole counts of
+// blocks of which some are rounded up, a partial sum per wavefront.
+static int64_t up(int64_t x) { return (x + 255) / 256 * 256; }
+static int64_t need(const Call &c) {
+    const int64_t n = c.n, d = c.d, k = c.k, tm = d <= 256 ? 32 : 16;
+    int64_t blocks = tm == 32 ? (d + 7) / 8 : (d + 15) / 16;
+    for (int64_t b : {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 13, 14, 16, 20, 24, 28, 32})
+        if (b >= blocks) {
+            blocks = b;
+            break;
+        }
+    const int64_t tile = (blocks <= 4 && tm == 32 ? 256 : 128) + blocks * 1024;
+    const int64_t waves = blocks <= 8 && tm == 32 ? 4 : 8, rows = waves * (tm == 16 ? 16 : blocks <= 16 ? 64 : 32);
+    const int64_t ld = d > 8 ? (d + 3) / 4 * 4 : d, copy = ld == d ? 0 : up(n * ld * 4);
+    auto work = [&](int64_t points, int64_t groups, int64_t members) {
+        return up(up((points + rows - 1) / rows * waves * groups * tm * 4) + groups * members * tile);
+    };
+    if (c.kind == Call::EVAL) return copy + work(n, 1, k);
+    if (c.kind == Call::GAIN) return copy + up(up(n * 4) + (k + tm - 1) / tm * tile) + work(n, 1, 1);
+    if (c.kind == Call::GREEDY) {
+        const int64_t nb = std::min<int64_t>(1024, (n + 4095) / 4096);
+        return copy + up(n * 4) + up(n) + 3 * up(n * 4) + up(tile) + 2 * up(nb * 4) + work(n, 1, 1);
+    }
+    const int64_t R = (std::min(n, (int64_t(64) << 20) / (ld * 4)) + rows - 1) / rows * rows, ne = c.l * k;
+    const int64_t lds = (d + 3) / 4 * 4;
+    return 2 * up(R * lds * 4) + up(ne * lds * 4) + up(ne * 4) + up(c.l * 8) + up(c.l) + up(c.l * 4) +
+           work(R, (c.l + tm - 1) / tm, k);
+}
+
+static void check_limits() {
+    std::vector<Call> calls;
+    for (int64_t d : {3, 8, 20, 21, 52, 100, 129, 170, 197, 256, 257, 300, 353, 449, 512})
+        for (int64_t n : {1, 60, 1000, 10000, 40000}) {
+            for (int64_t k : {1, 40, 900}) {
+                calls.push_back({Call::EVAL, n, d, 200, k, EXEMCL_FP32});
+                calls.push_back({Call::GAIN, n, d, 300, k, EXEMCL_FP32});
+                if (n <= 1000) calls.push_back({Call::STREAMED, n, d, 33, k, EXEMCL_FP32});
+            }
+            calls.push_back({Call::GREEDY, n, d, 0, std::min<int64_t>(n, 3), EXEMCL_FP32});
+        }
+    for (const Call &c : calls) {
+        int64_t held = 0;
+        const int64_t least = need(c);
+        expect(run(c, least, &held) == EXEMCL_OK, "accepted under the limit it needs", c.text() + " limit " + std::to_string(least));
+        for (double f : {0.5, 0.9, 1.0, 1.01, 1.1, 1.3, 1.7, 2.0, 3.0, 10.0}) {
+            const int64_t limit = (int64_t)(f * (double)least);
+            const int rc = run(c, limit, &held);
+            expect(rc == EXEMCL_OK || rc == EXEMCL_ENOMEM, "status", c.text());
+            expect(held <= limit, "held at most the limit", c.text() + " limit " + std::to_string(limit) + " held " + std::to_string(held));
+            expect(rc == EXEMCL_OK || fake::launches.empty(), "nothing queued when refused", c.text());
+        }
+    }
+    // the other plans, and what is reported
+    for (int prec : {EXEMCL_FP32, EXEMCL_FP16, EXEMCL_BF16})
+        for (int64_t d : {1, 2, 3, 16, 17, 100, 128, 256, 512, 513, 1000, 1536})
+            for (int64_t n : {1, 1000, 7000, 100000})
+                for (int64_t l : {1, 40, 4096})
+                    for (int64_t k : {1, 8, 32}) {
+                        const Call c{Call::EVAL, n, d, l, k, prec};
+                        int64_t held = 0, ws = 0;
+                        expect(exemplar_plan(n, d, l, k, prec, nullptr, &ws) == EXEMCL_OK, "plan");
+                        expect(run(c, INT64_MAX, &held) == EXEMCL_OK && held <= ws, "the plan's bytes hold the call", c.text());
+                        expect(run(c, ws, &held) == EXEMCL_OK && held <= ws, "the plan's bytes suffice as a limit", c.text());
+                    }
+}
+
 int main(int argc, char **argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "grids") check_grids();
     else if (what == "devices") check_devices();
     else if (what == "counter") check_counter();
+    else if (what == "limits") check_limits();
     else expect(false, "no such check", what);
     if (failures) fprintf(stderr, "%d checks failed\n", failures);
     else printf("%s: checks passed\n", what.c_str());

@@ -31,7 +31,7 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("check", ["grids", "devices", "counter"])
+@pytest.mark.parametrize("check", ["grids", "devices", "counter", "limits"])
 def test_host_runtime(driver, check):
     env = {k: v for k, v in os.environ.items() if not k.startswith("EXEMCL_")}
     r = subprocess.run([driver, check], capture_output=True, text=True, timeout=300, env=env)

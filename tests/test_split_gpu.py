@@ -105,6 +105,70 @@ def test_tiles_staged_in_lds(torch_gpu, monkeypatch, n, d, k):
     assert ei.value.status == api.EXEMCL_ENOMEM
 
 
+def least_limit(monkeypatch, call):
+    """The smallest EXEMCL_WORKSPACE_LIMIT under which `call` runs, in steps
+    of 256 bytes."""
+    lo, hi = 0, 1 << 22
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        monkeypatch.setenv("EXEMCL_WORKSPACE_LIMIT", str(256 * mid))
+        try:
+            call()
+            hi = mid
+        except api.ExemclError as e:
+            assert e.status == api.EXEMCL_ENOMEM
+            lo = mid
+    return 256 * hi
+
+
+@pytest.mark.parametrize("n,d,k,l", [(1000, 100, 19, 70), (10_000, 512, 3, 40), (300, 8, 70, 33), (5000, 301, 40, 33),
+                                     (513, 52, 1, 1)])
+def test_gain_and_greedy_under_tight_limits(torch_gpu, monkeypatch, n, d, k, l):
+    """From the smallest limit that is accepted up: tiles of S, of the
+    candidates, or both staged by the kernels, or S in several passes -- the
+    same bits."""
+    torch = torch_gpu
+    p = synth.random_problem(n, d, 1, 1, seed=9750 + d, clusters=3)
+    Vg, _ = to_gpu(torch, p.X, "fp32")
+    rng = np.random.default_rng(d)
+    S = torch.from_numpy(rng.choice(n, k, replace=False).astype(np.int32)).cuda()
+    C = torch.from_numpy(rng.choice(n, l, replace=False).astype(np.int32)).cuda()
+
+    def gain():
+        return api.exemplar_gain(Vg, S, C).cpu().numpy()
+
+    def greedy():
+        return np.concatenate([x.cpu().numpy() for x in api.exemplar_greedy(Vg, 3)])
+
+    for name, call in (("gain", gain), ("greedy", greedy)):
+        monkeypatch.delenv("EXEMCL_WORKSPACE_LIMIT", raising=False)
+        full = call()
+        least = least_limit(monkeypatch, call)
+        say(f"{name} n={n} d={d} |S|={k}: accepted from {least} bytes")
+        for limit in (least, int(1.2 * least), int(1.5 * least), 2 * least, 4 * least):
+            monkeypatch.setenv("EXEMCL_WORKSPACE_LIMIT", str(limit))
+            assert np.array_equal(full, call()), f"{name} limit {limit}"
+
+
+@pytest.mark.parametrize("n,d,l,k,rows", [(3000, 20, 40, 30, 0), (2500, 100, 33, 3, 700), (4001, 512, 10, 40, 1000)])
+def test_streamed_under_tight_limits(torch_gpu, orc, monkeypatch, n, d, l, k, rows):
+    """The smallest accepted limit: the kernel stages the exemplar matrix's
+    rows itself."""
+    torch = torch_gpu
+    p = synth.random_problem(n, d, l, k, seed=9770 + d, clusters=3)
+    sets = p.sets.copy()
+    sets[2, 1:] = -1
+    sets[3, 0] = n
+    V, S = torch.from_numpy(np.ascontiguousarray(p.X, np.float32)), torch.from_numpy(sets)
+    call = lambda: api.exemplar_eval_streamed(V, S, rows_per_block=rows).numpy()   # noqa: E731
+    least = least_limit(monkeypatch, call)
+    say(f"streamed n={n} d={d} k={k}: accepted from {least} bytes")
+    want = orc.eval(p.X.astype(np.float64), sets, 4)
+    for limit in (least, 2 * least):
+        monkeypatch.setenv("EXEMCL_WORKSPACE_LIMIT", str(limit))
+        exact(call(), want, f"streamed limit {limit}")
+
+
 @pytest.mark.parametrize("scale", [2.0 ** -30, 1.0, 2.0 ** 30])
 def test_error_against_64_bits(torch_gpu, orc, scale):
     """Single-member sets of one point's worth of averaging: the error of
