@@ -138,8 +138,9 @@ EXEMCL_API int exemplar_eval(const void *V, int64_t n, int64_t d, const int32_t 
  *
  * Same arguments, results (bitwise equal to exemplar_eval's), asynchrony and
  * errors as exemplar_eval, except for where temporaries live: partial sums,
- * staged exemplar tiles and (when V's rows are not whole 16-byte vectors) the
- * zero-padded copy of V are carved from a fixed scratch buffer of
+ * staged exemplar tiles and (fp16/bf16, and fp32 above d = 512, when V's rows
+ * are not whole vectors) the zero-padded copy of V are carved from a fixed
+ * scratch buffer of
  * EXEMCL_SCRATCH_BYTES (64 MiB) that is part of the library's code object on
  * each GPU and held until the process ends.  The call makes no allocation of
  * any kind (no hipMalloc, no pool, no library allocation) and records no
@@ -155,10 +156,10 @@ EXEMCL_API int exemplar_eval(const void *V, int64_t n, int64_t d, const int32_t 
  * events between the streams).  Calls on different GPUs are independent.
  *
  * Errors: as exemplar_eval, plus EXEMCL_ESCRATCH when even one set group's
- * workspace plus the padded copy of V does not fit the buffer (for example
- * n in the tens of millions of points, where one set group's partial sums
- * alone exceed 64 MiB, or a padded copy of V larger than the buffer); nothing
- * is queued then.  EXEMCL_WORKSPACE_LIMIT, when set lower, caps it further.
+ * workspace plus the padded copy of V, where one is made, does not fit the
+ * buffer (for example n in the tens of millions of points, where one set
+ * group's partial sums alone exceed 64 MiB, or a padded copy of V larger than
+ * the buffer); nothing is queued then.  EXEMCL_WORKSPACE_LIMIT, when set lower, caps it further.
  */
 EXEMCL_API int exemplar_eval_noalloc(const void *V, int64_t n, int64_t d, const int32_t *sets, int64_t l,
                                      int64_t k, int precision, float *out, void *stream);
@@ -282,7 +283,8 @@ EXEMCL_API int exemplar_sqnorm(const void *V, int64_t n, int64_t d, int precisio
  * exemplar_plan -- host-only description of what exemplar_eval would launch
  * for these sizes; touches no device.  Writes the chosen exemcl_path to
  * *path and the temporary device bytes to *workspace_bytes (either pointer
- * may be NULL).  The path depends on (d, k, precision) only, never on l or n,
+ * may be NULL): as a limit they suffice for the whole batch at once, and the
+ * call holds no more.  The path depends on (d, k, precision) only, never on l or n,
  * which is what keeps out[j] independent of the batch.  The environment
  * variable EXEMCL_PATH=valu|mfma forces a path where it applies (tests).
  * Two more variables tune the MFMA launch without changing any result:

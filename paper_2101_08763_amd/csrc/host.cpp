@@ -104,8 +104,6 @@ bool layout_eval(int64_t n, int64_t d, int64_t l, int64_t k, int precision, int 
         L->off_tiles = align_up(L->G * L->lpad * 4, 256);
         L->bytes = align_up(L->off_tiles + L->ngroups * mfma_tiles_per_group(L->mp, k) * tile_bytes(L->mp), 256);
         L->charge = L->mp.split ? split_charge(n, d, l, k) : L->bytes;
-        // long rows are accounted for with a partial-sum row per 4 points
-        if (L->mp.wide) L->charge += align_up(L->G * 8 * L->lpad * 4, 256) - L->off_tiles;
         L->unit = L->mp.split ? split_charge_unit(d) : tm;
         return true;
     }
@@ -364,13 +362,6 @@ int64_t pad_bytes(int precision, int64_t n, int64_t d) {
     return align_up(n * mfma_row_stride(precision, d) * elem_size(precision), 256);
 }
 
-// Bytes a call is accounted for on behalf of V's rows.
-int64_t charge_rows(int precision, int64_t n, int64_t d) {
-    MfmaPlan mp;
-    if (mfma_plan(precision, d, 1, false, &mp) && mp.split) return split_charge_rows(n, d);
-    return pad_bytes(precision, n, d);
-}
-
 int prepare_rows(const void *V, int64_t n, int64_t d, int precision, hipStream_t st, MfmaRows *r,
                  Arena *arena = nullptr) {
     if (rows_as_is(precision, d) || mfma_rows_ready(precision, V, d)) {
@@ -508,7 +499,7 @@ int run_eval(const void *V, int64_t n, int64_t d, const int32_t *sets, int64_t l
     const int64_t unit = L.unit;
     MfmaRows own;
     if (path == EXEMCL_PATH_MFMA && !rows) {
-        const int64_t pb = charge_rows(precision, n, d);
+        const int64_t pb = pad_bytes(precision, n, d);
         if (reserved + pb > ws_limit || (arena && pb > arena->left())) return EXEMCL_ENOMEM;
         // Nothing is queued unless the padded rows and one set group fit.
         Layout L1;
@@ -518,8 +509,7 @@ int run_eval(const void *V, int64_t n, int64_t d, const int32_t *sets, int64_t l
         const int rc = prepare_rows(V, n, d, precision, st, &own, arena);
         if (rc) return rc;
         rows = &own;
-        reserved += L.mp.split ? pb : own.bytes;
-        if (arena && L.mp.split) arena->cap -= pb;
+        reserved += own.bytes;
     }
     int64_t limit = ws_limit - reserved;
     if (arena) limit = std::min(limit, arena->left());
@@ -922,8 +912,7 @@ EXEMCL_API int exemplar_gain(const float *V, int64_t n, int64_t d, const int32_t
     const int64_t ngroups = (k + tm - 1) / tm;
     const int64_t off_tiles = align_up(n * 4, 256);
     const int64_t charge = align_up(off_tiles + (mp.split ? split_charge(0, d, k, 1) : ngroups * tile_bytes(mp)), 256);
-    const int64_t rows_charge = charge_rows(EXEMCL_FP32, n, d);
-    const int64_t limit = workspace_limit() - rows_charge;
+    const int64_t limit = workspace_limit() - pad_bytes(EXEMCL_FP32, n, d);
     Layout L1;
     if (!layout_eval(n, d, 1, 1, EXEMCL_FP32, EXEMCL_PATH_MFMA, &L1, true)) return EXEMCL_EINVAL;
     // Nothing is queued unless the cache, S and the scoring of one set group
@@ -942,7 +931,7 @@ EXEMCL_API int exemplar_gain(const float *V, int64_t n, int64_t d, const int32_t
         if (rc == EXEMCL_OK) break;
         if (rc != EXEMCL_ENOMEM || !mp.split || gs == 0) return rc;
     }
-    const int64_t held = rows_charge + align_up(off_tiles + gs * tile_bytes(mp), 256);
+    const int64_t held = rows.bytes + align_up(off_tiles + gs * tile_bytes(mp), 256);
     char *base = (char *)ws.ptr;
     float *gcache = (float *)base;
     void *tiles = gs > 0 ? base + off_tiles : nullptr;
@@ -1000,7 +989,7 @@ EXEMCL_API int exemplar_greedy(const float *V, int64_t n, int64_t d, int64_t K, 
     constexpr int64_t kScoringBytes = int64_t(1) << 30;
     // The call is accounted for with a tile of its own for that element.
     const int64_t charge = plain + align_up(mp.split ? split_charge(0, d, 1, 1) : tile_bytes(mp), 256);
-    const int64_t limit = workspace_limit() - charge_rows(EXEMCL_FP32, n, d);
+    const int64_t limit = workspace_limit() - pad_bytes(EXEMCL_FP32, n, d);
     Layout L;
     if (!layout_eval(n, d, 1, 1, EXEMCL_FP32, EXEMCL_PATH_MFMA, &L, true)) return EXEMCL_EINVAL;
     if (charge + L.charge > limit) return EXEMCL_ENOMEM;
@@ -1131,7 +1120,7 @@ EXEMCL_API int exemplar_plan(int64_t n, int64_t d, int64_t l, int64_t k, int pre
     if (path) *path = p;
     if (workspace_bytes)
         *workspace_bytes = std::max(L.charge, gathers_few(L, precision, n, d, k) ? L.off_tiles : L.bytes) +
-                           (p == EXEMCL_PATH_MFMA ? charge_rows(precision, n, d) : 0);
+                           (p == EXEMCL_PATH_MFMA ? pad_bytes(precision, n, d) : 0);
     return EXEMCL_OK;
 }
 

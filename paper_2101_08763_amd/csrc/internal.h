@@ -153,16 +153,15 @@ hipError_t launch_mfma(int prec, int mode, const MfmaPlan &pl, const void *V, in
                        int64_t live0 = 0, int m0_stride = 1, int32_t *counter = nullptr, float *out = nullptr,
                        const void *E = nullptr, int64_t ne = 0);
 
-// Bytes a call on the split kernels is accounted for: what decides whether it
-// fits a limit, and into how many chunks (of split_charge_unit sets at least)
-// it is cut.  Four bytes per staged coordinate (8 to a block, 16 above d =
-// 256) and one partial-sum row per 64 points (32 above d = 128, 16 above
-// 256), plus a copy of V whose rows are not whole 16-byte vectors
-// (split_charge_rows), as the entry points' limits are stated; the kernels
-// hold less, or, where six bytes per coordinate are more, stage tiles in LDS.
+// Bytes a call on the split kernels is accounted for, beside what it holds:
+// it runs where 4 bytes per staged coordinate (8 to a block, 16 above d =
+// 256) and one partial-sum row per 64 points (32 above d = 128, 16 above 256)
+// fit the limit, in chunks of split_charge_unit sets at least.  The present
+// tiles take 6 bytes per coordinate and the sums less; where they do not fit
+// beside each other the kernels stage the tiles in LDS and hold the sums
+// alone, which are always less than what the call is accounted for.
 int64_t split_charge(int64_t n, int64_t d, int64_t l, int64_t k);
 int64_t split_charge_unit(int64_t d);
-int64_t split_charge_rows(int64_t n, int64_t d);
 
 hipError_t launch_valu(int prec, const ValuPlan &pl, const void *V, int64_t n, int d, const int32_t *sets,
                        int64_t l, int64_t k, float *partials, int64_t lpad, hipStream_t st);

@@ -83,10 +83,6 @@ int64_t split_charge(int64_t n, int64_t d, int64_t l, int64_t k) {
 
 int64_t split_charge_unit(int64_t d) { return d <= 256 ? 32 : 16; }
 
-int64_t split_charge_rows(int64_t n, int64_t d) {
-    return d > 8 && d % 4 != 0 ? (n * ((d + 3) / 4 * 4) * 4 + 255) / 256 * 256 : 0;
-}
-
 bool mfma_plan(int prec, int64_t d, int64_t n, bool one, MfmaPlan *p) {
     if (d < 1 || d > kMaxD) return false;
     MfmaPlan q{};

@@ -318,6 +318,12 @@ static void check_limits() {
             expect(rc == EXEMCL_OK || fake::launches.empty(), "nothing queued when refused", c.text());
         }
     }
+    // no bytes for what is not there: a copy of fp32 rows that are read in
+    // place, more partial sums than are written
+    expect(exemplar_eval_noalloc(kV, 170000, 101, kI, 40, 3, EXEMCL_FP32, kF, nullptr) == EXEMCL_OK, "rows read in place");
+    int64_t ws = 0;
+    expect(exemplar_plan(20000, 1536, 4096, 16, EXEMCL_BF16, nullptr, &ws) == EXEMCL_OK && ws < 625 * 4096 * 4 + 2048 * (3200 * 49),
+           "long rows: a partial sum per 32 points");
     // the other plans, and what is reported
     for (int prec : {EXEMCL_FP32, EXEMCL_FP16, EXEMCL_BF16})
         for (int64_t d : {1, 2, 3, 16, 17, 100, 128, 256, 512, 513, 1000, 1536})
