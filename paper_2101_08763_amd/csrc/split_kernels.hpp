@@ -146,9 +146,10 @@ __device__ __forceinline__ bf16x8 tail_fragment(const Quad *q, int grp, int t, b
 // ||s||^2 in fp64 (the lane's blocks and tail in order, then the four groups
 // of lanes with a fixed xor tree), but for a block's eight coordinates where
 // there are many blocks: its error is the same for every point and does not
-// average out in f.  An invalid index is a zero column with bias -FLT_MAX, which never
-// wins the running max.
-template <int NKB, int NT>
+// average out in f.  An invalid index is a zero column with bias -FLT_MAX,
+// which never wins the running max.  Four whole blocks are loaded before any
+// is stored; one at a time with few registers to spare (LEAN).
+template <int NKB, int NT, bool LEAN = false>
 __device__ __forceinline__ void stage_columns(const float *__restrict__ V, int64_t n, int ld, int d, int64_t idx,
                                               int h, int lane, unsigned char *tile) {
     const int grp = lane >> 4;
@@ -171,8 +172,8 @@ __device__ __forceinline__ void stage_columns(const float *__restrict__ V, int64
             }
         }
     }
-    constexpr int BATCH = 4;  // whole blocks loaded before any is stored
-#pragma unroll
+    constexpr int BATCH = LEAN ? 1 : 4, UNROLL = LEAN ? 1 : 16;
+#pragma unroll UNROLL
     for (int k0 = 0; k0 < NKB; k0 += BATCH) {
         float x[BATCH][8];
 #pragma unroll
@@ -287,8 +288,11 @@ constexpr int split_stage_bytes(int nkb, int nt, int waves, bool gather) {
                                                                : split_tps(nkb, nt, waves) * split_tile_bytes(nkb, nt),
                        waves);
 }
+// The points' parts leave no registers to stage in beside them: `gather` then
+// has one buffer, and reads the points again for every stage.
+constexpr bool split_reload(int nkb, bool gather) { return gather && nkb > 4; }
 constexpr int split_buffers(int nkb, int nt, int waves, bool gather) {
-    return gather && split_halves(nkb, nt, waves) ? 1 : 2;
+    return gather && (split_halves(nkb, nt, waves) || split_reload(nkb, gather)) ? 1 : 2;
 }
 constexpr int split_lds(int nkb, int nt, int waves, bool gather) {
     return split_buffers(nkb, nt, waves, gather) * split_stage_bytes(nkb, nt, waves, gather) +
@@ -352,6 +356,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
     constexpr int TPS = split_tps(NKB, NT, WAVES);
     constexpr int NTHR = WAVES * 64;
     constexpr int NBUF = split_buffers(NKB, NT, WAVES, GATHER);
+    constexpr bool RELOAD = split_reload(NKB, GATHER);
     constexpr int SB = split_stage_bytes(NKB, NT, WAVES, GATHER);
     constexpr int CNT = SB / (NTHR * 16);
     // HALF: a stage is half a tile (HSTEPS steps, HBYTES bytes, then the rest)
@@ -397,8 +402,8 @@ __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
                     const int64_t g = t / kt, q = t - g * kt;
                     const int64_t j = (g0 + g) * kSplitSets + (c & 1) * 16 + lr;
                     const int64_t idx = j < l ? (int64_t)sets[j * kt + q] : -1;
-                    stage_columns<NKB, NT>(reinterpret_cast<const float *>(tiles), live0, ldv, d, idx, c & 1, lane,
-                                           buf + (c >> 1) * TB);
+                    stage_columns<NKB, NT, RELOAD>(reinterpret_cast<const float *>(tiles), live0, ldv, d, idx, c & 1,
+                                                      lane, buf + (c >> 1) * TB);
                 }
                 return;
             }
@@ -420,57 +425,62 @@ __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
         const int64_t wrows = min((int64_t)ROWS, n - wrow0);
         const auto vwin = window_rsrc(V + wrow0 * (int64_t)ldv, (uint32_t)(wrows * ldv * 4));
         bf16x8 a[RT][NKB > 0 ? NKB : 1][3], at[RT][NT > 0 ? NT : 1];
+        auto load_points = [&]() {
+            int row = lr;
+            if constexpr (RELOAD) asm volatile("" : "+v"(row));  // loads of its own for every stage
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-            const int rowoff = (wave * RT * 16 + rt * 16 + lr) * ldv;
+            for (int rt = 0; rt < RT; ++rt) {
+                const int rowoff = (wave * RT * 16 + rt * 16 + row) * ldv;
 #pragma unroll
-            for (int kb = 0; kb < NKB; ++kb) {
-                const int d0 = kb * 32 + grp * 8;
-                float x[8];
-                if ((kb + 1) * 32 <= d) {
-                    const f32x4 p = window_load16<f32x4>(vwin, (uint32_t)((rowoff + d0) * 4));
-                    const f32x4 q = window_load16<f32x4>(vwin, (uint32_t)((rowoff + d0 + 4) * 4));
+                for (int kb = 0; kb < NKB; ++kb) {
+                    const int d0 = kb * 32 + grp * 8;
+                    float x[8];
+                    if ((kb + 1) * 32 <= d) {
+                        const f32x4 p = window_load16<f32x4>(vwin, (uint32_t)((rowoff + d0) * 4));
+                        const f32x4 q = window_load16<f32x4>(vwin, (uint32_t)((rowoff + d0 + 4) * 4));
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) x[e] = p[e], x[4 + e] = q[e];
-                } else {
+                        for (int e = 0; e < 4; ++e) x[e] = p[e], x[4 + e] = q[e];
+                    } else {
 #pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        x[e] = window_load4(vwin, d0 + e < d ? (uint32_t)((rowoff + d0 + e) * 4) : kDeadOffset);
+                        for (int e = 0; e < 8; ++e)
+                            x[e] = window_load4(vwin, d0 + e < d ? (uint32_t)((rowoff + d0 + e) * 4) : kDeadOffset);
+                    }
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        __bf16 hi, mid, lo;
+                        split3(x[e], hi, mid, lo);
+                        a[rt][kb][0][e] = lo;
+                        a[rt][kb][1][e] = mid;
+                        a[rt][kb][2][e] = hi;
+                    }
                 }
+                if constexpr (NT > 0) {
+                    constexpr int NQ = NT == 4 ? 2 : 1;
+                    const int r = d - 32 * NKB;
+                    Quad q[NQ];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    __bf16 hi, mid, lo;
-                    split3(x[e], hi, mid, lo);
-                    a[rt][kb][0][e] = lo;
-                    a[rt][kb][1][e] = mid;
-                    a[rt][kb][2][e] = hi;
+                    for (int i = 0; i < NQ; ++i) {
+                        // a whole quad in one load; a partial one, or the one
+                        // past the last, coordinate by coordinate
+                        const int c0 = i == 0 ? Tail<NT>::own(grp) : 16;
+                        const bool whole = c0 + 4 <= r;
+                        const uint32_t off = (uint32_t)((rowoff + 32 * NKB + c0) * 4);
+                        const f32x4 v = window_load16<f32x4>(vwin, whole ? off : kDeadOffset);
+                        float x[4] = {v[0], v[1], v[2], v[3]};
+                        if ((r & 3) != 0)
+#pragma unroll
+                            for (int e = 0; e < 3; ++e) {
+                                const float y = window_load4(vwin, !whole && c0 + e < r ? off + 4 * e : kDeadOffset);
+                                x[e] = whole ? x[e] : y;
+                            }
+                        q[i] = split_quad(x);
+                    }
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) at[rt][t] = tail_fragment<NT>(q, grp, t, true);
                 }
             }
-            if constexpr (NT > 0) {
-                constexpr int NQ = NT == 4 ? 2 : 1;
-                const int r = d - 32 * NKB;
-                Quad q[NQ];
-#pragma unroll
-                for (int i = 0; i < NQ; ++i) {
-                    // a whole quad in one load; a partial one, or the one
-                    // past the last, coordinate by coordinate
-                    const int c0 = i == 0 ? Tail<NT>::own(grp) : 16;
-                    const bool whole = c0 + 4 <= r;
-                    const uint32_t off = (uint32_t)((rowoff + 32 * NKB + c0) * 4);
-                    const f32x4 v = window_load16<f32x4>(vwin, whole ? off : kDeadOffset);
-                    float x[4] = {v[0], v[1], v[2], v[3]};
-                    if ((r & 3) != 0)
-#pragma unroll
-                        for (int e = 0; e < 3; ++e) {
-                            const float y = window_load4(vwin, !whole && c0 + e < r ? off + 4 * e : kDeadOffset);
-                            x[e] = whole ? x[e] : y;
-                        }
-                    q[i] = split_quad(x);
-                }
-#pragma unroll
-                for (int t = 0; t < NT; ++t) at[rt][t] = tail_fragment<NT>(q, grp, t, true);
-            }
-        }
+        };
+        if constexpr (!RELOAD) load_points();
 
         // Initial running max: e0's 0, or the cached per-point value.
         float minit[HAS_M0 ? RT : 1][4];
@@ -655,6 +665,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
             __syncthreads();
             const unsigned char *buf = smem + (HALF || NBUF == 1 ? 0 : s & 1) * SB;
             const int tn = (int)min((int64_t)TPS, ntiles - (int64_t)s * TPS);
+            if constexpr (RELOAD) load_points();
             head(buf);
             if (NBUF > 1 && s > 0 && (HALF || s + 1 < nst)) issue(HALF ? 2 * s + 1 : s + 1);
             auto mid = [&]() {
