@@ -314,8 +314,13 @@ constexpr int split_rt(int nkb, int nt, int64_t n, bool one) {
     if (nkb == 0) return n < 1024 ? 1 : n < 32768 ? 2 : top;
     return n < 8192 ? 1 : top == 4 ? (n < 100000 ? 2 : top) : (!one && n < 32768 ? 2 : top);
 }
-// The cache g(v) reads V once against a few tiles: small workgroups.
-constexpr int kRowmaxWaves = 4, kRowmaxRt = 2;
+// The cache g(v) reads V once against a few tiles: small workgroups, of two
+// row tiles; one row tile and eight wavefronts where the registers hold one,
+// since a tile's LDS then leaves room for a single workgroup on the CU
+// (20 000 x 512, 7 points: 20.6 us; two row tiles, which spill, and four
+// wavefronts 45.6).
+constexpr int split_rowmax_rt(int nkb, int nt) { return std::min(2, split_rt_max(nkb, nt)); }
+constexpr int split_rowmax_waves(int nkb, int nt) { return split_rt_max(nkb, nt) == 1 ? 8 : 4; }
 
 // ---------------------------------------------------------------------------
 // Evaluation.  A workgroup owns WAVES*RT*16 consecutive points; units of work
@@ -771,6 +776,7 @@ hipError_t split_launch(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st) {
     auto kern = eval_split_kernel<NKB, NT, RT, WAVES, MODE, HAS_M0, GATHER>;
     constexpr int lds = split_lds(NKB, NT, WAVES, GATHER);
     constexpr int rows = WAVES * RT * 16;
+    static_assert(RT <= split_rt_max(NKB, NT), "the points' parts are held in registers");
     if (MODE == MODE_SUM && pl.rows != rows) return hipErrorInvalidValue;
     // Resident workgroups per CU, queried once per instantiation and device
     // (the LDS attribute holds for one device).
@@ -807,7 +813,7 @@ template <int NKB, int NT, int MODE, bool HAS_M0, bool GATHER>
 hipError_t split_eval_t(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st) {
     constexpr int TOP = split_rt_max(NKB, NT);
     if constexpr (MODE == MODE_ROWMAX) {
-        return split_launch<NKB, NT, kRowmaxRt, kRowmaxWaves, MODE, HAS_M0, GATHER>(pl, x, st);
+        return split_launch<NKB, NT, split_rowmax_rt(NKB, NT), split_rowmax_waves(NKB, NT), MODE, HAS_M0, GATHER>(pl, x, st);
     } else {
         if constexpr (TOP > 1)
             if (pl.rt == 1) return split_launch<NKB, NT, 1, kSplitWaves, MODE, HAS_M0, GATHER>(pl, x, st);
