@@ -57,7 +57,7 @@ int64_t wg_target() {
 int choose_path(int64_t d, int64_t k, int precision) {
     MfmaPlan mp;
     ValuPlan vp;
-    const bool can_mfma = mfma_plan(precision, d, 1, false, &mp);
+    const bool can_mfma = mfma_plan(precision, d, 1, &mp);
     const bool can_valu = valu_plan(precision, d, k, &vp);
     const int f = forced_path();
     if (f == EXEMCL_PATH_VALU && can_valu) return EXEMCL_PATH_VALU;
@@ -79,14 +79,14 @@ struct Layout {
 
 int64_t tile_bytes(const MfmaPlan &mp) { return mfma_tile_bytes(mp); }
 
-// Workspace of one exemplar_eval call (or, `one`, of the scoring of S u {c}).
+// Workspace of one exemplar_eval call, or of the scoring half of a gain call.
 // plan_n: the number of points the launch geometry is chosen for, when that
 // is not n (blocks of a streamed V).
-bool layout_eval(int64_t n, int64_t d, int64_t l, int64_t k, int precision, int path, Layout *L, bool one = false,
+bool layout_eval(int64_t n, int64_t d, int64_t l, int64_t k, int precision, int path, Layout *L,
                  int64_t plan_n = 0) {
     L->path = path;
     if (path == EXEMCL_PATH_MFMA) {
-        if (!mfma_plan(precision, d, plan_n > 0 ? plan_n : n, one, &L->mp)) return false;
+        if (!mfma_plan(precision, d, plan_n > 0 ? plan_n : n, &L->mp)) return false;
         const int64_t tm = L->mp.tile;
         L->ngroups = (l + tm - 1) / tm;
         L->lpad = L->ngroups * tm;
@@ -352,7 +352,7 @@ struct MfmaRows {
 // takes V as it is.
 bool rows_as_is(int precision, int64_t d) {
     MfmaPlan mp;
-    return mfma_plan(precision, d, 1, false, &mp) && (mp.split || (mp.il && mp.nkb == 1));
+    return mfma_plan(precision, d, 1, &mp) && (mp.split || (mp.il && mp.nkb == 1));
 }
 
 // Temporary bytes of the padded copy of V (0 when rows of this d are read in
@@ -481,21 +481,20 @@ bool gathers_few(const Layout &L, int precision, int64_t n, int64_t d, int64_t k
 // batch it is evaluated in, so chunked results are bitwise the same.  ENOMEM
 // only when not even one set group fits -- the paper's chunk size 0.
 //
-// `one`: scoring S u {c} (the launch geometry of exemplar_greedy's rounds).
 // `rows` (nullable) is V already prepared for the MFMA kernels by the caller,
 // which also holds `reserved` bytes of temporary memory that count against
 // EXEMCL_WORKSPACE_LIMIT.  With `arena` every temporary is carved from it
 // (and the chunks are sized to what is left of it); nothing is allocated.
 int run_eval(const void *V, int64_t n, int64_t d, const int32_t *sets, int64_t l, int64_t k, int precision,
              const float *m0, const int32_t *common, int64_t kcommon, float *out, hipStream_t st,
-             const MfmaRows *rows = nullptr, int64_t reserved = 0, Arena *arena = nullptr, bool one = false) {
+             const MfmaRows *rows = nullptr, int64_t reserved = 0, Arena *arena = nullptr) {
     if (l == 0) return EXEMCL_OK;
     const int64_t ws_limit = workspace_limit();
     int path = k == 0 ? EXEMCL_PATH_NONE : choose_path(d, k, precision);
     if (m0 && path == EXEMCL_PATH_VALU) path = EXEMCL_PATH_MFMA;
     if (k > 0 && path == EXEMCL_PATH_NONE) return EXEMCL_EINVAL;
     Layout L;
-    if (!layout_eval(n, d, l, k, precision, path, &L, one)) return EXEMCL_EINVAL;
+    if (!layout_eval(n, d, l, k, precision, path, &L)) return EXEMCL_EINVAL;
     const int64_t unit = L.unit;
     MfmaRows own;
     if (path == EXEMCL_PATH_MFMA && !rows) {
@@ -503,7 +502,7 @@ int run_eval(const void *V, int64_t n, int64_t d, const int32_t *sets, int64_t l
         if (reserved + pb > ws_limit || (arena && pb > arena->left())) return EXEMCL_ENOMEM;
         // Nothing is queued unless the padded rows and one set group fit.
         Layout L1;
-        if (!layout_eval(n, d, std::min<int64_t>(l, unit), k, precision, path, &L1, one)) return EXEMCL_EINVAL;
+        if (!layout_eval(n, d, std::min<int64_t>(l, unit), k, precision, path, &L1)) return EXEMCL_EINVAL;
         if (reserved + pb + L1.charge > ws_limit || (arena && pb + L1.charge > arena->left()))
             return EXEMCL_ENOMEM;
         const int rc = prepare_rows(V, n, d, precision, st, &own, arena);
@@ -523,7 +522,7 @@ int run_eval(const void *V, int64_t n, int64_t d, const int32_t *sets, int64_t l
         gather = true;
     }
     while (!few) {
-        if (!layout_eval(n, d, lc, k, precision, path, &L, one)) return EXEMCL_EINVAL;
+        if (!layout_eval(n, d, lc, k, precision, path, &L)) return EXEMCL_EINVAL;
         if (L.charge <= limit && L.bytes <= limit) {
             const int rc = alloc_scratch(&ws, L.bytes, st, arena);
             if (rc == EXEMCL_OK) break;
@@ -550,7 +549,7 @@ int run_eval(const void *V, int64_t n, int64_t d, const int32_t *sets, int64_t l
     for (int64_t j0 = 0; j0 < l; j0 += lc) {
         const int64_t lj = l - j0 < lc ? l - j0 : lc;
         Layout Lj;
-        if (!layout_eval(n, d, lj, k, precision, path, &Lj, one)) return EXEMCL_EINVAL;
+        if (!layout_eval(n, d, lj, k, precision, path, &Lj)) return EXEMCL_EINVAL;
         const hipError_t e = run_chunk(Lj, base, V, n, d, rows, sets + j0 * k, lj, k, precision, m0, common,
                                        kcommon, out + j0, st, arena == nullptr, gather, nullptr, 0, counter);
         if (e != hipSuccess) return EXEMCL_EDEVICE;
@@ -672,9 +671,9 @@ int run_streamed(const void *V, int64_t n, int64_t d, const int32_t *sets, int64
     MfmaPlan mp;
     Layout L;
     for (;;) {
-        if (!mfma_plan(precision, d, plan_n, false, &mp)) return EXEMCL_EINVAL;
+        if (!mfma_plan(precision, d, plan_n, &mp)) return EXEMCL_EINVAL;
         R = (R0 + mp.rows - 1) / mp.rows * mp.rows;  // whole row blocks of the kernel
-        if (!layout_eval(R, d, l, k, precision, EXEMCL_PATH_MFMA, &L, false, plan_n)) return EXEMCL_EINVAL;
+        if (!layout_eval(R, d, l, k, precision, EXEMCL_PATH_MFMA, &L, plan_n)) return EXEMCL_EINVAL;
         off_exem = 2 * align_up(R * ld * es, 256);
         off_idx = off_exem + align_up(ne * ld * es, 256);
         off_acc = off_idx + align_up(ne * 4, 256);
@@ -790,7 +789,7 @@ int run_streamed(const void *V, int64_t n, int64_t d, const int32_t *sets, int64
         const int64_t rows = std::min(R, n - b * R);
         e = hipStreamWaitEvent(st, ss->copied[i], 0);
         Layout Lb;
-        if (e == hipSuccess && !layout_eval(rows, d, l, k, precision, EXEMCL_PATH_MFMA, &Lb, false, plan_n))
+        if (e == hipSuccess && !layout_eval(rows, d, l, k, precision, EXEMCL_PATH_MFMA, &Lb, plan_n))
             e = hipErrorInvalidValue;
         if (e == hipSuccess) {
             ProfRange pr(st);
@@ -885,7 +884,7 @@ EXEMCL_API int exemplar_eval_streamed(const void *V, int64_t n, int64_t d, const
     if (l > 0 && k > 0 && !sets) return EXEMCL_EINVAL;
     if (rows_per_block < 0) return EXEMCL_EINVAL;
     MfmaPlan mp;
-    if (!mfma_plan(precision, d, n, false, &mp)) return EXEMCL_EINVAL;
+    if (!mfma_plan(precision, d, n, &mp)) return EXEMCL_EINVAL;
     if (l == 0) return EXEMCL_OK;
     if (k == 0) {  // f(empty) = 0 for every set
         memset(out, 0, (size_t)l * sizeof(float));
@@ -901,10 +900,10 @@ EXEMCL_API int exemplar_gain(const float *V, int64_t n, int64_t d, const int32_t
     if (k > 0 && !S) return EXEMCL_EINVAL;
     if (l > 0 && !cands) return EXEMCL_EINVAL;
     MfmaPlan mp;
-    if (!mfma_plan(EXEMCL_FP32, d, n, true, &mp)) return EXEMCL_EINVAL;
+    if (!mfma_plan(EXEMCL_FP32, d, n, &mp)) return EXEMCL_EINVAL;
     if (l == 0) return EXEMCL_OK;
     hipStream_t st = (hipStream_t)stream;
-    if (k == 0) return run_eval(V, n, d, cands, l, 1, EXEMCL_FP32, nullptr, nullptr, 0, out, st, nullptr, 0, nullptr, true);
+    if (k == 0) return run_eval(V, n, d, cands, l, 1, EXEMCL_FP32, nullptr, nullptr, 0, out, st);
 
     // Cache g(v) = max(0, max_{s in S} h_s(v)): S's members as single-member
     // "sets" staged side by side, reduced by max over columns per point.
@@ -914,7 +913,7 @@ EXEMCL_API int exemplar_gain(const float *V, int64_t n, int64_t d, const int32_t
     const int64_t charge = align_up(off_tiles + (mp.split ? split_charge(0, d, k, 1) : ngroups * tile_bytes(mp)), 256);
     const int64_t limit = workspace_limit() - pad_bytes(EXEMCL_FP32, n, d);
     Layout L1;
-    if (!layout_eval(n, d, 1, 1, EXEMCL_FP32, EXEMCL_PATH_MFMA, &L1, true)) return EXEMCL_EINVAL;
+    if (!layout_eval(n, d, 1, 1, EXEMCL_FP32, EXEMCL_PATH_MFMA, &L1)) return EXEMCL_EINVAL;
     // Nothing is queued unless the cache, S and the scoring of one set group
     // fit.
     if (charge + L1.charge > limit) return EXEMCL_ENOMEM;
@@ -946,7 +945,7 @@ EXEMCL_API int exemplar_gain(const float *V, int64_t n, int64_t d, const int32_t
     if (e != hipSuccess) return EXEMCL_EDEVICE;
     // Score every S u {c}: single-member sets {c} with the running max
     // started at g(v) instead of e0's 0.
-    return run_eval(V, n, d, cands, l, 1, EXEMCL_FP32, gcache, S, k, out, st, &rows, held, nullptr, true);
+    return run_eval(V, n, d, cands, l, 1, EXEMCL_FP32, gcache, S, k, out, st, &rows, held);
 }
 
 EXEMCL_API int exemplar_greedy(const float *V, int64_t n, int64_t d, int64_t K, int32_t *S_out, float *f_out,
@@ -955,7 +954,7 @@ EXEMCL_API int exemplar_greedy(const float *V, int64_t n, int64_t d, int64_t K, 
     if (K < 0 || K > n) return EXEMCL_EINVAL;
     if (K > 0 && (!S_out || !f_out)) return EXEMCL_EINVAL;
     MfmaPlan mp;
-    if (!mfma_plan(EXEMCL_FP32, d, n, true, &mp)) return EXEMCL_EINVAL;
+    if (!mfma_plan(EXEMCL_FP32, d, n, &mp)) return EXEMCL_EINVAL;
     if (K == 0) return EXEMCL_OK;
     hipStream_t st = (hipStream_t)stream;
 
@@ -991,7 +990,7 @@ EXEMCL_API int exemplar_greedy(const float *V, int64_t n, int64_t d, int64_t K, 
     const int64_t charge = plain + align_up(mp.split ? split_charge(0, d, 1, 1) : tile_bytes(mp), 256);
     const int64_t limit = workspace_limit() - pad_bytes(EXEMCL_FP32, n, d);
     Layout L;
-    if (!layout_eval(n, d, 1, 1, EXEMCL_FP32, EXEMCL_PATH_MFMA, &L, true)) return EXEMCL_EINVAL;
+    if (!layout_eval(n, d, 1, 1, EXEMCL_FP32, EXEMCL_PATH_MFMA, &L)) return EXEMCL_EINVAL;
     if (charge + L.charge > limit) return EXEMCL_ENOMEM;
     MfmaRows rows;
     int rc = prepare_rows(V, n, d, EXEMCL_FP32, st, &rows);
@@ -1000,7 +999,7 @@ EXEMCL_API int exemplar_greedy(const float *V, int64_t n, int64_t d, int64_t K, 
     bool gather = false;  // not even one set group's tiles fit: staged by the kernels
     Scratch ws;
     for (;;) {
-        if (!layout_eval(n, d, lc, 1, EXEMCL_FP32, EXEMCL_PATH_MFMA, &L, true)) return EXEMCL_EINVAL;
+        if (!layout_eval(n, d, lc, 1, EXEMCL_FP32, EXEMCL_PATH_MFMA, &L)) return EXEMCL_EINVAL;
         const bool small = std::max(L.bytes, L.charge) <= kScoringBytes || lc <= L.unit;
         if (lazy && small && fixed + L.bytes > limit) {  // no room for the list
             lazy = false;
@@ -1053,7 +1052,7 @@ EXEMCL_API int exemplar_greedy(const float *V, int64_t n, int64_t d, int64_t K, 
             for (int64_t j0 = 0; e == hipSuccess && j0 < n; j0 += lc) {
                 const int64_t lj = n - j0 < lc ? n - j0 : lc;
                 Layout Ls;
-                if (!layout_eval(ns, d, lj, 1, EXEMCL_FP32, EXEMCL_PATH_MFMA, &Ls, true, n)) return EXEMCL_EINVAL;
+                if (!layout_eval(ns, d, lj, 1, EXEMCL_FP32, EXEMCL_PATH_MFMA, &Ls, n)) return EXEMCL_EINVAL;
                 float *partials = (float *)(work + Ls.off_partials);
                 void *tiles = work + Ls.off_tiles;
                 e = launch_pack(EXEMCL_FP32, mp, rows.V, n, (int)rows.ld, cands + j0, lj, 1, tiles, st);
@@ -1066,7 +1065,7 @@ EXEMCL_API int exemplar_greedy(const float *V, int64_t n, int64_t d, int64_t K, 
             }
             if (e == hipSuccess) e = launch_greedy_probe(lscores, taken, n, probes, st);
             Layout Lp;
-            if (!layout_eval(n, d, kGreedyProbes, 1, EXEMCL_FP32, EXEMCL_PATH_MFMA, &Lp, true)) return EXEMCL_EINVAL;
+            if (!layout_eval(n, d, kGreedyProbes, 1, EXEMCL_FP32, EXEMCL_PATH_MFMA, &Lp)) return EXEMCL_EINVAL;
             if (e == hipSuccess)
                 e = run_chunk(Lp, work, V, n, d, &rows, probes, kGreedyProbes, 1, EXEMCL_FP32, g_cur, nullptr, 0,
                               pscores, st, false);
@@ -1078,7 +1077,7 @@ EXEMCL_API int exemplar_greedy(const float *V, int64_t n, int64_t d, int64_t K, 
         for (int64_t j0 = 0; e == hipSuccess && j0 < n; j0 += lc) {
             const int64_t lj = n - j0 < lc ? n - j0 : lc;
             Layout Lj;
-            if (!layout_eval(n, d, lj, 1, EXEMCL_FP32, EXEMCL_PATH_MFMA, &Lj, true)) return EXEMCL_EINVAL;
+            if (!layout_eval(n, d, lj, 1, EXEMCL_FP32, EXEMCL_PATH_MFMA, &Lj)) return EXEMCL_EINVAL;
             if (lazy && i > 0)
                 e = run_chunk(Lj, work, V, n, d, &rows, list + j0, lj, 1, EXEMCL_FP32, g_cur, nullptr, 0, lscores + j0,
                               st, true, false, &state->count, j0);

@@ -13,9 +13,9 @@ enum Prec { P_FP32 = 0, P_FP16 = 1, P_BF16 = 2 };
 constexpr int32_t kEmptySlot = -1;
 
 // Geometry of one MFMA evaluation launch; a pure function of d, the
-// precision, n (the points per workgroup) and whether it scores S u {c},
-// never of l or k, so that the partial-sum layout seen by one set does not
-// depend on the batch it arrives in.
+// precision and n (the points per workgroup), never of l or k, so that the
+// partial-sum layout seen by one set does not depend on the batch it arrives
+// in.
 struct MfmaPlan {
     int tile;       // TM: sets per column tile (32 or 16)
     int nkb;        // k-blocks per tile: ceil(d / kb_dims) rounded up to a compiled bucket
@@ -38,9 +38,8 @@ struct MfmaPlan {
     int d;          // split: the data's dimension
 };
 
-// `one`: the launch scores S u {c} (m0 set).  The staged tiles' layout does
-// not depend on n or `one`.
-bool mfma_plan(int prec, int64_t d, int64_t n, bool one, MfmaPlan *p);
+// The staged tiles' layout does not depend on n.
+bool mfma_plan(int prec, int64_t d, int64_t n, MfmaPlan *p);
 
 // Arguments of one launch of the MFMA evaluation kernel.
 struct MfmaArgs {

@@ -250,7 +250,7 @@ hipError_t launch_reduce(const float *partials, int64_t G, int64_t lpad, int64_t
 // ---------------------------------------------------------------------------
 int64_t mfma_row_stride(int prec, int64_t d) {
     MfmaPlan pl;
-    if (mfma_plan(prec, d, 1, false, &pl) && pl.split) return d;  // rows are read as they are
+    if (mfma_plan(prec, d, 1, &pl) && pl.split) return d;  // rows are read as they are
     const int64_t vec = prec == P_FP32 ? 4 : 8;
     return (d + vec - 1) / vec * vec;
 }
@@ -266,7 +266,7 @@ int64_t mfma_row_stride(int prec, int64_t d) {
 // at an 8-byte aligned address; the loads need 4-byte alignment).
 bool mfma_rows_in_place(int prec, int64_t d) {
     MfmaPlan pl;
-    if (!mfma_plan(prec, d, 1, false, &pl)) return false;
+    if (!mfma_plan(prec, d, 1, &pl)) return false;
     if (prec == P_FP32) return d % 4 == 0;
     return d % 8 == 0 || (pl.half && d % 4 == 0);
 }

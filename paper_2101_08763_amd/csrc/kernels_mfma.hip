@@ -49,7 +49,7 @@ constexpr int64_t kMaxD = int64_t(1) << 24;
 // is not compiled, is a zero-padded whole block).  d <= 2 stays on the fp32
 // MFMA: one instruction holds all of it (10^5 points, 1 024 sets of 16: d = 2
 // 90 us against 105 here; d = 4 137 against 104).
-static bool split_plan(int64_t d, int64_t n, bool one, MfmaPlan *q) {
+static bool split_plan(int64_t d, int64_t n, MfmaPlan *q) {
     if (d <= 2) return false;
     int nkb = (int)(d / 32), r4 = (int)(d % 32 + 3) / 4;
     int nt = (6 * r4 + 7) / 8;
@@ -64,7 +64,7 @@ static bool split_plan(int64_t d, int64_t n, bool one, MfmaPlan *q) {
     q->kb_dims = 32;
     q->nkb = nkb;
     q->nt = nt;
-    q->rt = split_rt(nkb, nt, n, one);
+    q->rt = split_rt(nkb, nt, n);
     q->waves = kSplitWaves;
     q->rows = q->waves * q->rt * 16;
     q->wgsum = 1;
@@ -83,10 +83,10 @@ int64_t split_charge(int64_t n, int64_t d, int64_t l, int64_t k) {
 
 int64_t split_charge_unit(int64_t d) { return d <= 256 ? 32 : 16; }
 
-bool mfma_plan(int prec, int64_t d, int64_t n, bool one, MfmaPlan *p) {
+bool mfma_plan(int prec, int64_t d, int64_t n, MfmaPlan *p) {
     if (d < 1 || d > kMaxD) return false;
     MfmaPlan q{};
-    if (prec == P_FP32 && split_plan(d, n, one, &q)) {
+    if (prec == P_FP32 && split_plan(d, n, &q)) {
         *p = q;
         return true;
     }

@@ -125,6 +125,21 @@ __device__ __forceinline__ u32x2 pick(int prod, const bf16x4 &p0, const bf16x4 &
            : prod == 5 ? b(p5)
                        : zero;
 }
+// Coordinates c .. c + 3 of the row at element `row` of a window, c a multiple
+// of 4, zero from d on, in one load: the last quad of rows with d % 4 != 0 is
+// read from its end and shifted (d >= 4).
+__device__ __forceinline__ f32x4 window_quad(__amdgpu_buffer_rsrc_t rsrc, int row, int c, int d) {
+    const int part = d & 3;
+    const bool whole = c + 4 <= d;
+    const f32x4 v = window_load16<f32x4>(rsrc, c < d ? (uint32_t)((row + (whole ? c : d - 4)) * 4) : kDeadOffset);
+    if (part == 0) return v;
+    f32x4 x = {part == 3 ? v[1] : part == 2 ? v[2] : v[3], part == 3 ? v[2] : part == 2 ? v[3] : 0.0f,
+               part == 3 ? v[3] : 0.0f, 0.0f};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] = whole ? v[e] : x[e];
+    return x;
+}
+
 // One lane's tail fragment t, of a point or of an exemplar.
 template <int NT>
 __device__ __forceinline__ bf16x8 tail_fragment(const Quad *q, int grp, int t, bool point) {
@@ -301,18 +316,35 @@ constexpr int split_lds(int nkb, int nt, int waves, bool gather) {
 
 // Row tiles per wavefront: as many as the registers hold without spilling in
 // the main loop (3 operand fragments per whole block and row tile).  A
-// smaller ground set takes fewer, so that there are row blocks for all CUs;
-// the rule looks at n and never at l or k, which must not change a result.
+// smaller ground set takes fewer: row blocks for all CUs, and less to load
+// and split before the first product.  The rule looks at n and never at l or
+// k, which must not change a result; so each line is a mean of long and short
+// calls (256 sets of 10, 64 of 4, microseconds):
+//   d = 8    700 points   1 or 2: 11.5, 11.5    4: 12.6, 11.4
+//          7 000          1: 14.0, 11.4         2: 11.7, 11.5    4: 12.9, 11.5
+//         20 000          2: 17.4, 11.4         4: 17.6, 11.4
+//         40 000          2: 23.5, 14.1         4: 21.7, 11.4
+//   d = 40   4 000        1: 15.8, 12.7         2: 17.5, 12.8
+//         12 000          1: 26.0, 12.8         2: 25.1, 13.0    4: 23.5, 16.3
+//         30 000          2: 40.0, 13.3         4: 36.6, 17.2
+//         64 000          2: 68.2, 17.9         4: 62.2, 18.0
+//         80 000          2: 88.0, 22.7         4: 79.9, 22.4
+//   d = 100  4 000        1: 21.0, 15.2         2: 26.7, 18.5
+//         12 000          1: 42.9, 16.4         2: 42.8, 19.2    3: 38.4, 24.0
+//         30 000          2: 73.7, 19.7         3: 77.8, 26.7
+//         40 000          2: 96.8, 24.7         3: 94.0, 27.6
+//         80 000          2: 178, 37.1          3: 172, 32.1
+// Up to 65 536 points two row tiles are one round of workgroups.
 constexpr int kSplitWaves = 8;
 constexpr int split_rt_max(int nkb, int nt) {
     const int steps = split_steps(nkb, nt);
     return steps <= 5 ? 4 : steps <= 10 ? 3 : steps <= 19 ? 2 : 1;
 }
-constexpr int split_rt(int nkb, int nt, int64_t n, bool one) {
+constexpr int split_rt(int nkb, int nt, int64_t n) {
     const int top = split_rt_max(nkb, nt);
     if (top == 1) return 1;
     if (nkb == 0) return n < 1024 ? 1 : n < 32768 ? 2 : top;
-    return n < 8192 ? 1 : top == 4 ? (n < 100000 ? 2 : top) : (!one && n < 32768 ? 2 : top);
+    return n < 8192 ? 1 : n < (top == 4 ? 65537 : 32768) ? 2 : top;
 }
 // The cache g(v) reads V once against a few tiles: small workgroups, of two
 // row tiles; one row tile and eight wavefronts where the registers hold one,
@@ -439,21 +471,18 @@ __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
 #pragma unroll
                 for (int kb = 0; kb < NKB; ++kb) {
                     const int d0 = kb * 32 + grp * 8;
-                    float x[8];
+                    f32x4 p, q;
                     if ((kb + 1) * 32 <= d) {
-                        const f32x4 p = window_load16<f32x4>(vwin, (uint32_t)((rowoff + d0) * 4));
-                        const f32x4 q = window_load16<f32x4>(vwin, (uint32_t)((rowoff + d0 + 4) * 4));
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) x[e] = p[e], x[4 + e] = q[e];
+                        p = window_load16<f32x4>(vwin, (uint32_t)((rowoff + d0) * 4));
+                        q = window_load16<f32x4>(vwin, (uint32_t)((rowoff + d0 + 4) * 4));
                     } else {
-#pragma unroll
-                        for (int e = 0; e < 8; ++e)
-                            x[e] = window_load4(vwin, d0 + e < d ? (uint32_t)((rowoff + d0 + e) * 4) : kDeadOffset);
+                        p = window_quad(vwin, rowoff, d0, d);
+                        q = window_quad(vwin, rowoff, d0 + 4, d);
                     }
 #pragma unroll
                     for (int e = 0; e < 8; ++e) {
                         __bf16 hi, mid, lo;
-                        split3(x[e], hi, mid, lo);
+                        split3(e < 4 ? p[e & 3] : q[e & 3], hi, mid, lo);
                         a[rt][kb][0][e] = lo;
                         a[rt][kb][1][e] = mid;
                         a[rt][kb][2][e] = hi;
@@ -461,23 +490,20 @@ __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
                 }
                 if constexpr (NT > 0) {
                     constexpr int NQ = NT == 4 ? 2 : 1;
-                    const int r = d - 32 * NKB;
                     Quad q[NQ];
 #pragma unroll
                     for (int i = 0; i < NQ; ++i) {
-                        // a whole quad in one load; a partial one, or the one
-                        // past the last, coordinate by coordinate
-                        const int c0 = i == 0 ? Tail<NT>::own(grp) : 16;
-                        const bool whole = c0 + 4 <= r;
-                        const uint32_t off = (uint32_t)((rowoff + 32 * NKB + c0) * 4);
-                        const f32x4 v = window_load16<f32x4>(vwin, whole ? off : kDeadOffset);
-                        float x[4] = {v[0], v[1], v[2], v[3]};
-                        if ((r & 3) != 0)
+                        const int c0 = 32 * NKB + (i == 0 ? Tail<NT>::own(grp) : 16);
+                        float x[4];
+                        if (NKB == 0 && NT == 1 && d < 4) {  // d = 3
 #pragma unroll
-                            for (int e = 0; e < 3; ++e) {
-                                const float y = window_load4(vwin, !whole && c0 + e < r ? off + 4 * e : kDeadOffset);
-                                x[e] = whole ? x[e] : y;
-                            }
+                            for (int e = 0; e < 4; ++e)
+                                x[e] = window_load4(vwin, e < d ? (uint32_t)((rowoff + e) * 4) : kDeadOffset);
+                        } else {
+                            const f32x4 v = window_quad(vwin, rowoff, c0, d);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) x[e] = v[e];
+                        }
                         q[i] = split_quad(x);
                     }
 #pragma unroll
@@ -493,11 +519,21 @@ __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
             // m0 may be null in MODE_ROWMAX (an empty window reads as zeros)
             const auto mwin = window_rsrc(m0 ? m0 + wrow0 * m0_stride : V,
                                           m0 ? (uint32_t)(((wrows - 1) * m0_stride + 1) * 4) : 0u);
+            if (m0_stride == 1 && wrows == ROWS) {  // whole quads
 #pragma unroll
-            for (int rt = 0; rt < RT; ++rt)
+                for (int rt = 0; rt < RT; ++rt) {
+                    const f32x4 v = window_load16<f32x4>(mwin, (uint32_t)((wave * RT * 16 + rt * 16 + 4 * grp) * 4));
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    minit[rt][i] = window_load4(mwin, (uint32_t)((wave * RT * 16 + rt * 16 + 4 * grp + i) * m0_stride * 4));
+                    for (int i = 0; i < 4; ++i) minit[rt][i] = v[i];
+                }
+            } else {
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        minit[rt][i] =
+                            window_load4(mwin, (uint32_t)((wave * RT * 16 + rt * 16 + 4 * grp + i) * m0_stride * 4));
+            }
         }
         auto m_init = [&](int rt, int i) -> float {
             if constexpr (HAS_M0) return minit[rt][i];
@@ -771,6 +807,21 @@ hipError_t split_pack_t(const void *V, int64_t n, int ld, int d, const int32_t *
     return hipGetLastError();
 }
 
+// Workgroups of a persistent launch: one per slot, sharing the units out
+// evenly, or a whole number per row block, so that none crosses into another
+// one and loads and splits points twice.  Whichever ends first: tiles of the
+// longest share, and kSplitStart instructions' worth of them per row block.
+constexpr int kSplitStart = 200;
+inline int64_t split_grid(int64_t nrb, int64_t ngroups, int64_t kt, int64_t slots, int mfmas_per_tile) {
+    const int64_t even = std::min(nrb * ngroups, slots);
+    if (nrb > slots || even % nrb == 0) return even;
+    const int64_t per = std::min(ngroups, slots / nrb);
+    const int64_t start = kSplitStart / mfmas_per_tile;
+    const int64_t whole = (ngroups + per - 1) / per * kt + start;
+    const int64_t shared = (nrb * ngroups + slots - 1) / slots * kt + 2 * start;
+    return whole <= shared ? nrb * per : even;
+}
+
 template <int NKB, int NT, int RT, int WAVES, int MODE, bool HAS_M0, bool GATHER>
 hipError_t split_launch(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st) {
     auto kern = eval_split_kernel<NKB, NT, RT, WAVES, MODE, HAS_M0, GATHER>;
@@ -799,7 +850,7 @@ hipError_t split_launch(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st) {
     if (slots < 1) return hipErrorInvalidDevice;
     // MODE_ROWMAX: a workgroup sees every set group of its row block.
     int64_t grid = MODE == MODE_ROWMAX ? nrb : nrb * x.ngroups;
-    if (MODE == MODE_SUM && persistent_mode() != kPersistOff) grid = std::min(grid, slots);
+    if (MODE == MODE_SUM && persistent_mode() != kPersistOff) grid = split_grid(nrb, x.ngroups, x.kt, slots, 2 * RT * (6 * NKB + NT));
     grid = std::min<int64_t>(grid, UINT32_MAX / (WAVES * 64));  // the workgroups share out what there is
     hipExtLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(WAVES * 64), lds, st, x.ev_start, x.ev_stop, 0,
                           (const float *)x.V, x.n, x.ld, pl.d,

@@ -60,7 +60,7 @@ def test_every_tail(torch_gpu, orc, d):
 
 
 @pytest.mark.parametrize("d", [3, 20, 32, 100, 170])
-@pytest.mark.parametrize("n", [127, 2047, 2048, 8191, 8192, 32767, 32768, 99_999, 100_000])
+@pytest.mark.parametrize("n", [127, 1023, 1024, 2047, 2048, 8191, 8192, 32767, 32768, 65_536, 65_537, 99_999, 100_000])
 def test_row_tile_rule(torch_gpu, orc, n, d):
     """Both sides of every n at which the row tiles per wavefront change; a
     batch of one set has the bits of the same set in a larger batch."""
