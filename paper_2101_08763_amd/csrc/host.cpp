@@ -426,18 +426,19 @@ struct ProfRange {
 
 // Queue the evaluation of sets [0, l) with a workspace laid out by L;
 // `gather`: without its staged tiles, and with `counter` in one launch;
-// `live`: *live - live0 of the sets.
+// `live`: *live - live0 of the sets; `staged`: their tiles are there already.
 hipError_t run_chunk(const Layout &L, char *base, const void *V, int64_t n, int64_t d, const MfmaRows *rows,
                      const int32_t *sets, int64_t l, int64_t k, int precision, const float *m0,
                      const int32_t *common, int64_t kcommon, float *out, hipStream_t st, bool prof = true,
                      bool gather = false, const int32_t *live = nullptr, int64_t live0 = 0,
-                     int32_t *counter = nullptr) {
+                     int32_t *counter = nullptr, bool staged = false) {
     if (L.path == EXEMCL_PATH_NONE) return launch_zero(out, l, st);  // k = 0: every set is empty
     float *partials = (float *)(base + L.off_partials);
     hipError_t e = hipSuccess;
     if (L.path == EXEMCL_PATH_MFMA) {
         void *tiles = gather ? nullptr : base + L.off_tiles;
-        if (!gather) e = launch_pack(precision, L.mp, rows->V, n, (int)rows->ld, sets, l, k, tiles, st, live, live0);
+        if (!gather && !staged)
+            e = launch_pack(precision, L.mp, rows->V, n, (int)rows->ld, sets, l, k, tiles, st, live, live0);
         if (e == hipSuccess) {
             ProfRange pr(st, prof);
             e = launch_mfma(precision, MODE_SUM, L.mp, rows->V, n, (int)rows->ld, tiles, mfma_tiles_per_group(L.mp, k),
@@ -921,6 +922,34 @@ EXEMCL_API int exemplar_gain(const float *V, int64_t n, int64_t d, const int32_t
     // limit leaves beside the scoring; none, if not even one fits (the kernel
     // then stages them itself).
     int64_t gs = std::min(ngroups, (limit - off_tiles - L1.charge) / tile_bytes(mp));
+    if (mp.split) {
+        // Where everything fits side by side, one launch stages S and the
+        // candidates (20 000 x 400, 7 points, 16 candidates: 33.6 us a call,
+        // with two 39.1; 9 000 x 20: 16.9 and 22.4, the host's launches).
+        Layout L;
+        if (!layout_eval(n, d, l, 1, EXEMCL_FP32, EXEMCL_PATH_MFMA, &L)) return EXEMCL_EINVAL;
+        const int64_t off_work = align_up(off_tiles + ngroups * tile_bytes(mp), 256);
+        Scratch all;
+        rc = EXEMCL_ENOMEM;
+        if (off_work + std::max(L.charge, L.bytes) <= limit) rc = alloc_scratch(&all, off_work + L.bytes, st);
+        if (rc == EXEMCL_OK) {
+            char *base = (char *)all.ptr;
+            float *gcache = (float *)base;
+            MfmaRows in_place;
+            in_place.V = V;
+            in_place.ld = d;
+            hipError_t e = split_pack_run(mp, V, n, (int)d, S, k, 1, base + off_tiles, st, nullptr, 0, cands, l,
+                                          base + off_work + L.off_tiles);
+            if (e == hipSuccess)
+                e = launch_mfma(EXEMCL_FP32, MODE_ROWMAX, mp, V, n, (int)d, base + off_tiles, 1, ngroups, ngroups,
+                                nullptr, nullptr, 0, gcache, st);
+            if (e == hipSuccess)
+                e = run_chunk(L, base + off_work, V, n, d, &in_place, cands, l, 1, EXEMCL_FP32, gcache, S, k, out, st,
+                              true, false, nullptr, 0, nullptr, true);
+            return status_of(e);
+        }
+        if (rc != EXEMCL_ENOMEM) return rc;
+    }
     MfmaRows rows;
     rc = prepare_rows(V, n, d, EXEMCL_FP32, st, &rows);
     if (rc) return rc;
@@ -1033,7 +1062,8 @@ EXEMCL_API int exemplar_greedy(const float *V, int64_t n, int64_t d, int64_t K, 
     float *pval = (float *)(base + off_pval);
     int32_t *pidx = (int32_t *)(base + off_pidx);
     char *work = base + fixed;
-    void *ctile = gather ? nullptr : work + L.off_tiles;
+    // (staged by the kernel where its rows are short)
+    void *ctile = gather || (mp.split && d <= kGatherD) ? nullptr : work + L.off_tiles;
 
     int32_t *list = (int32_t *)(base + off_list), *probes = (int32_t *)(base + off_probes);
     float *lscores = (float *)(base + off_lscores), *pscores = (float *)(base + off_pscores);

@@ -84,7 +84,8 @@ hipError_t eval_run_f16(const MfmaPlan &pl, int mode, const MfmaArgs &x, hipStre
 hipError_t eval_run_bf16(const MfmaPlan &pl, int mode, const MfmaArgs &x, hipStream_t st);
 // The fp32 kernels on the bf16 matrix cores (kernels_mfma_split*.hip).
 hipError_t split_pack_run(const MfmaPlan &pl, const void *V, int64_t n, int ld, const int32_t *sets, int64_t l,
-                          int64_t k, void *tiles, hipStream_t st, const int32_t *live, int64_t live0);
+                          int64_t k, void *tiles, hipStream_t st, const int32_t *live, int64_t live0,
+                          const int32_t *sets2 = nullptr, int64_t l2 = 0, void *tiles2 = nullptr);
 hipError_t split_sum_run(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st);      // MODE_SUM, m0 null
 hipError_t split_gain_run(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st);     // MODE_SUM from m0
 hipError_t split_rowmax_run(const MfmaPlan &pl, const MfmaArgs &x, hipStream_t st);   // MODE_ROWMAX, m0 nullable

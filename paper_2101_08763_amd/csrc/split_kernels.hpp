@@ -260,12 +260,19 @@ __device__ __forceinline__ void stage_columns(const float *__restrict__ V, int64
 // Staging: one workgroup of two wavefronts per tile (set group g, member p),
 // one column group each; tile g*k + p at tiles + (g*k + p) * tile bytes.
 // `live`: only *live - live0 of the l sets are there (counted on the device).
+// `sets2`: after those, l2 sets of one member to tiles2.
 template <int NKB, int NT>
 __global__ __launch_bounds__(128) void pack_split_kernel(const float *__restrict__ V, int64_t n, int ld, int d,
                                                          const int32_t *__restrict__ sets, int64_t l, int64_t k,
                                                          unsigned char *__restrict__ tiles,
-                                                         const int32_t *__restrict__ live, int64_t live0) {
-    const int64_t t = flat_block();
+                                                         const int32_t *__restrict__ live, int64_t live0,
+                                                         const int32_t *__restrict__ sets2, int64_t l2,
+                                                         unsigned char *__restrict__ tiles2) {
+    int64_t t = flat_block();
+    if (sets2) {
+        const int64_t first = (l + kSplitSets - 1) / kSplitSets * k;
+        if (t >= first) t -= first, sets = sets2, l = l2, k = 1, tiles = tiles2;
+    }
     const int64_t g = t / k, p = t - (t / k) * k;
     if (g * kSplitSets >= l) return;
     if (live) {
@@ -800,10 +807,11 @@ __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
 // ---------------------------------------------------------------------------
 template <int NKB, int NT>
 hipError_t split_pack_t(const void *V, int64_t n, int ld, int d, const int32_t *sets, int64_t l, int64_t k,
-                        void *tiles, hipStream_t st, const int32_t *live, int64_t live0) {
-    const int64_t ngroups = (l + kSplitSets - 1) / kSplitSets;
-    hipLaunchKernelGGL((pack_split_kernel<NKB, NT>), flat_grid(ngroups * k, 128), dim3(128), 0, st, (const float *)V,
-                       n, ld, d, sets, l, k, (unsigned char *)tiles, live, live0);
+                        void *tiles, hipStream_t st, const int32_t *live, int64_t live0, const int32_t *sets2, int64_t l2,
+                        void *tiles2) {
+    const int64_t count = (l + kSplitSets - 1) / kSplitSets * k + (l2 + kSplitSets - 1) / kSplitSets;
+    hipLaunchKernelGGL((pack_split_kernel<NKB, NT>), flat_grid(count, 128), dim3(128), 0, st, (const float *)V, n, ld, d,
+                       sets, l, k, (unsigned char *)tiles, live, live0, sets2, l2, (unsigned char *)tiles2);
     return hipGetLastError();
 }
 
