@@ -30,6 +30,7 @@
 #pragma once
 
 #include <atomic>
+#include <type_traits>
 #include <float.h>
 #include <stdlib.h>
 
@@ -108,12 +109,16 @@ constexpr int tile_bytes_of(int hdr, int nff, int nhalf) { return hdr + nff * 10
 // elements in order, then the K-groups of the column with a fixed xor tree).
 // ---------------------------------------------------------------------------
 
-// The workgroup's number in a flat_grid.
-__device__ __forceinline__ int64_t flat_block() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
+// The workgroup's number in a flat_grid, whose rows have a fixed length: the
+// grid's own extents are one more line of kernel arguments to wait for (0.3 us
+// of a 3 us kernel).
+constexpr int64_t kFlatRow = 1 << 20;
+__device__ __forceinline__ int64_t flat_block() { return (int64_t)blockIdx.y * kFlatRow + blockIdx.x; }
 
 // One column group of one tile: a wavefront stages column group h of `tile`
 // (in memory or LDS); `idx` is the row of the lane's column, any value.
-template <typename T, int TILE>
+// LONG: more than 32 k-blocks.
+template <typename T, int TILE, bool LONG>
 __device__ __forceinline__ void stage_tile_columns(const T *__restrict__ V, int64_t n, int ld, int64_t idx, int h,
                                                    int lane, int nkb, int half, int splat, int il,
                                                    unsigned char *tile) {
@@ -125,13 +130,11 @@ __device__ __forceinline__ void stage_tile_columns(const T *__restrict__ V, int6
     typename M::vec_t *dst = reinterpret_cast<typename M::vec_t *>(tile + HDR);
     const bool valid = idx >= 0 && idx < n;
     const int64_t r = valid ? idx : n;  // row n reads as zeros
-    // ||s||^2 of long 16-bit rows in fp64: a chain of hundreds of fp32 sums
+    // ||s||^2, of long 16-bit rows in fp64: a chain of hundreds of fp32 sums
     // is up to 12 units of the last place off, the same for every point.
-    float sq = 0.0f;
-    double sq64 = 0.0;
-    const bool long_row = sizeof(T) == 2 && nkb > 32;
+    std::conditional_t<LONG && sizeof(T) == 2, double, float> sq = 0;
     auto add = [&](float x) {
-        if (long_row) sq64 = fma((double)x, (double)x, sq64);
+        if constexpr (sizeof(sq) == 8) sq = fma((double)x, (double)x, sq);
         else sq = fmaf(x, x, sq);
     };
     // Up to KBATCH k-blocks are loaded before any is stored, so the loads
@@ -171,10 +174,7 @@ __device__ __forceinline__ void stage_tile_columns(const T *__restrict__ V, int6
         }
         dst[(kb * NB + h) * 64 + lane] = v;
 #pragma unroll
-        for (int e = 0; e < M::VEC; ++e) {
-            const float x = to_f32(v[e]);
-            sq = fmaf(x, x, sq);
-        }
+        for (int e = 0; e < M::VEC; ++e) add(to_f32(v[e]));
     }
     if constexpr (M::HAS_HALF) {
         if (half) {
@@ -188,18 +188,12 @@ __device__ __forceinline__ void stage_tile_columns(const T *__restrict__ V, int6
             for (int e = 0; e < M::HVEC; ++e) v[e] = live ? v[e] : (typename M::elem_t)0.0f;
             reinterpret_cast<hvec_t *>(tile + HDR + nfull * NB * 1024)[h * 64 + lane] = v;
 #pragma unroll
-            for (int e = 0; e < M::HVEC; ++e) {
-                const float x = to_f32(v[e]);
-                sq = fmaf(x, x, sq);
-            }
+            for (int e = 0; e < M::HVEC; ++e) add(to_f32(v[e]));
         }
     }
 #pragma unroll
-    for (int off = M::TM; off < 64; off <<= 1) {
-        sq += __shfl_xor(sq, off);
-        if (long_row) sq64 += __shfl_xor(sq64, off);
-    }
-    const float b = !valid ? -FLT_MAX : long_row ? (float)(-0.5 * sq64) : -0.5f * sq;
+    for (int off = M::TM; off < 64; off <<= 1) sq += __shfl_xor(sq, off);
+    const float b = valid ? (float)(sq * -0.5f) : -FLT_MAX;
     if (grp == 0) {
         if (splat) {
             // Exact three-way split: hi is b rounded to bf16, mid the
@@ -223,7 +217,7 @@ __device__ __forceinline__ void stage_tile_columns(const T *__restrict__ V, int6
     }
 }
 
-template <typename T, int TILE>
+template <typename T, int TILE, bool LONG>
 __global__ __launch_bounds__((64 * Mfma<T, TILE>::NB)) void pack_tiles_kernel(const T *__restrict__ V, int64_t n, int ld,
                                                         const int32_t *__restrict__ sets, int64_t l,
                                                         int64_t k, int nkb, int half, int splat, int il,
@@ -240,8 +234,8 @@ __global__ __launch_bounds__((64 * Mfma<T, TILE>::NB)) void pack_tiles_kernel(co
     // The member index is read from an address clamped into the set matrix
     // (l, k >= 1 whenever this kernel runs).
     const int32_t raw = sets[(j < l ? j : l - 1) * k + (p < k ? p : k - 1)];
-    stage_tile_columns<T, TILE>(V, n, ld, j < l && p < k ? (int64_t)raw : -1, h, lane, nkb, half, splat, il,
-                                tiles + t * bytes);
+    stage_tile_columns<T, TILE, LONG>(V, n, ld, j < l && p < k ? (int64_t)raw : -1, h, lane, nkb, half, splat, il,
+                                      tiles + t * bytes);
 }
 
 // Stage geometry, fixed at compile time per k-block bucket.  Workgroups of
@@ -619,8 +613,8 @@ __global__ __launch_bounds__(WAVES * 64, PERSIST ? 2 : 1) void eval_mfma_kernel(
                 const int64_t t = s * TPS + c / NB;
                 const int64_t j = (g0 + t / kt) * TM + lr, p = (t % kt) * NB + c % NB;
                 const int64_t idx = j < l && p < k ? (int64_t)sets[j * k + p] : -1;
-                stage_tile_columns<T, TILE>(V, n, ldv, idx, c % NB, lane, NKB, HALF ? 1 : 0, SPLAT ? 1 : 0, 0,
-                                            buf + c / NB * TB);
+                stage_tile_columns<T, TILE, false>(V, n, ldv, idx, c % NB, lane, NKB, HALF ? 1 : 0, SPLAT ? 1 : 0, 0,
+                                                   buf + c / NB * TB);
             }
             return;
         }
@@ -1075,12 +1069,11 @@ inline int64_t device_cu_count() {
 }
 
 // `blocks` workgroups of `threads` as a grid (flat_block() numbers them): an
-// extent holds 32 bits of work-items, so larger counts take several rows, of
-// whole multiples of the 8 XCDs.  The last row may reach past `blocks`.
+// extent holds 32 bits of work-items, so larger counts take rows of kFlatRow,
+// a multiple of the 8 XCDs.  The last one may reach past `blocks`.
 inline dim3 flat_grid(int64_t blocks, int threads) {
-    const int64_t most = UINT32_MAX / threads / 8 * 8;
-    const int64_t rows = (blocks + most - 1) / most;
-    return rows <= 1 ? dim3((unsigned)blocks) : dim3((unsigned)(((blocks + rows - 1) / rows + 7) / 8 * 8), (unsigned)rows);
+    if (blocks <= UINT32_MAX / threads) return dim3((unsigned)blocks);
+    return dim3((unsigned)kFlatRow, (unsigned)((blocks + kFlatRow - 1) / kFlatRow));
 }
 
 template <typename T, int TILE>
@@ -1093,8 +1086,11 @@ hipError_t pack_launch(const MfmaPlan &pl, const void *V, int64_t n, int ld, con
     const int64_t ngroups = (l + TILE - 1) / TILE;
     const int64_t kt = (k + Mfma<T, TILE>::NB - 1) / Mfma<T, TILE>::NB;
     constexpr int threads = 64 * Mfma<T, TILE>::NB;
-    hipLaunchKernelGGL((pack_tiles_kernel<T, TILE>), flat_grid(ngroups * kt, threads), dim3(threads), 0, st,
-                       (const T *)V, n, ld, sets, l, k, pl.nkb, pl.half, pl.splat, pl.il, (unsigned char *)tiles);
+    auto kern = pack_tiles_kernel<T, TILE, false>;
+    if constexpr (TILE == 16 && sizeof(T) == 2)
+        if (pl.nkb > 32) kern = pack_tiles_kernel<T, TILE, true>;
+    hipLaunchKernelGGL(kern, flat_grid(ngroups * kt, threads), dim3(threads), 0, st, (const T *)V, n, ld, sets, l, k,
+                       pl.nkb, pl.half, pl.splat, pl.il, (unsigned char *)tiles);
     return hipGetLastError();
 }
 
