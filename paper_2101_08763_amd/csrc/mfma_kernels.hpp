@@ -58,20 +58,11 @@ constexpr bool splat_bias(int elem_bytes, int tile, int nkb) {
     return EXEMCL_SPLAT_MFMA && (elem_bytes == 2 || EXEMCL_SPLAT_F32) && tile == 32 && nkb <= EXEMCL_SPLAT_MAX_NKB;
 }
 
-// fp32 32x32x2 tiles whose last k-block holds r <= 4 coordinates pair them
-// per instruction: in that k-block element e of lane group g holds
-// coordinate 2e + g, so instruction e covers coordinates 2e and 2e + 1 and
-// ceil(r / 2) instructions cover it (the contiguous layout, e and 4 + e per
-// instruction, needs all 4 once r > 2).  With a single k-block (d <= 8)
-// every row is read one coordinate at a time, so V needs no 16-byte
-// alignment or padding.  A kernel uses the paired last block when it has
-// one k-block or fewer than 4 instructions in the last one.
-#ifndef EXEMCL_IL
-#define EXEMCL_IL 1
-#endif
-constexpr bool il_layout(int elem_bytes, int tile, int nkb, int nks_last) {
-    return EXEMCL_IL && elem_bytes == 4 && tile == 32 && (nkb == 1 || nks_last < 4);
-}
+// fp32 32x32x2 tiles (d <= 2, one k-block) pair their coordinates: element e of
+// lane group g holds coordinate 2e + g, so one instruction covers both.  Their
+// rows are read one coordinate at a time, so V needs no 16-byte alignment or
+// padding.
+constexpr bool il_layout(int elem_bytes, int tile) { return elem_bytes == 4 && tile == 32; }
 __device__ __forceinline__ int il_dim(int grp, int e) { return 2 * e + grp; }
 
 // Largest finite bf16 (0x7F7F).
@@ -140,9 +131,9 @@ __device__ __forceinline__ void stage_tile_columns(const T *__restrict__ V, int6
     // Up to KBATCH k-blocks are loaded before any is stored, so the loads
     // overlap (indices past the last block re-read it and are not
     // stored); ||s||^2 still runs over k-blocks and elements in order.
-    // A paired last k-block (fp32) follows the others.
+    // (A paired k-block, fp32 d <= 2, is the only one.)
     const bool paired = sizeof(T) == 4 && il;
-    const int nreg = paired ? nfull - 1 : nfull;
+    const int nreg = paired ? 0 : nfull;
     constexpr int KBATCH = 8;
     for (int kb0 = 0; kb0 < nreg; kb0 += KBATCH) {
         typename M::vec_t vb[KBATCH];
@@ -163,16 +154,14 @@ __device__ __forceinline__ void stage_tile_columns(const T *__restrict__ V, int6
         }
     }
     if (paired) {
-        // last k-block: coordinate kb*8 + 2e + grp, read one at a time
-        // (single-block rows may be unpadded)
-        const int kb = nfull - 1;
+        // coordinate 2e + grp, read one at a time (the rows may be unpadded)
         typename M::vec_t v;
 #pragma unroll
         for (int e = 0; e < M::VEC; ++e) {
-            const int c = kb * M::KB_DIMS + il_dim(grp, e);
+            const int c = il_dim(grp, e);
             v[e] = (r < n && c < ld) ? V[r * (int64_t)ld + c] : (typename M::elem_t)0.0f;
         }
-        dst[(kb * NB + h) * 64 + lane] = v;
+        dst[h * 64 + lane] = v;
 #pragma unroll
         for (int e = 0; e < M::VEC; ++e) add(to_f32(v[e]));
     }
@@ -491,7 +480,7 @@ __device__ void finish_sets(const float *partials, int64_t G, int64_t lpad, int6
 // s+NBUF-1.
 //
 // NKS_LAST = MFMA instructions fed by the last k-block (fp32 packs KS_PER_KB
-// instructions per k-block; tiny d uses fewer, see il_layout).
+// instructions per k-block; d <= 2 uses one, see il_layout).
 //
 // Per tile: the accumulators start at the column's bias (a splat, or one
 // bf16 MFMA for SPLAT tiles), the MFMA chain adds <v, s>, and the running max
@@ -539,7 +528,7 @@ __global__ __launch_bounds__(WAVES * 64, PERSIST ? 2 : 1) void eval_mfma_kernel(
     // the matrix cores, in the 32x32 accumulator layout all these shapes
     // share; the VALU only folds.
     constexpr bool SPLAT = splat_bias((int)sizeof(T), TILE, NKB);
-    constexpr bool IL = il_layout((int)sizeof(T), TILE, NKB, NKS_LAST);
+    constexpr bool IL = il_layout((int)sizeof(T), TILE);
     constexpr int NBIAS = SPLAT ? 2 : NB;  // bias registers per tile (SPLAT: the 8 header bytes)
     constexpr int HDR = hdr_bytes(TM, NB, SPLAT);
     constexpr int TB = tile_bytes_of(HDR, NFF, HALF ? NB : 0);
@@ -651,10 +640,11 @@ __global__ __launch_bounds__(WAVES * 64, PERSIST ? 2 : 1) void eval_mfma_kernel(
         const int lrow = wave * RT * TM + rt * TM + lr;
 #pragma unroll
         for (int kb = 0; kb < NKF; ++kb) {
-            if (IL && kb == NKF - 1) {
+            if constexpr (IL) {
+                static_assert(NKB == 1, "one paired k-block");
 #pragma unroll
                 for (int e = 0; e < M::VEC; ++e) {
-                    const int c = kb * M::KB_DIMS + il_dim(grp, e);
+                    const int c = il_dim(grp, e);
                     a[rt][kb][e] = window_load4(vwin, c < ldv ? (uint32_t)((lrow * ldv + c) * 4) : kDeadOffset);
                 }
             } else {
@@ -1081,7 +1071,7 @@ hipError_t pack_launch(const MfmaPlan &pl, const void *V, int64_t n, int ld, con
                        int64_t k, void *tiles, hipStream_t st) {
     if (pl.half && !Mfma<T, TILE>::HAS_HALF) return hipErrorInvalidValue;
     if ((pl.splat != 0) != splat_bias((int)sizeof(T), TILE, pl.nkb)) return hipErrorInvalidValue;
-    if ((pl.il != 0) != il_layout((int)sizeof(T), TILE, pl.nkb, pl.nks_last)) return hipErrorInvalidValue;
+    if ((pl.il != 0) != il_layout((int)sizeof(T), TILE)) return hipErrorInvalidValue;
     if (l < 1 || k < 1) return hipErrorInvalidValue;  // the kernel reads sets[0] at least
     const int64_t ngroups = (l + TILE - 1) / TILE;
     const int64_t kt = (k + Mfma<T, TILE>::NB - 1) / Mfma<T, TILE>::NB;
