@@ -408,6 +408,10 @@ __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
     constexpr int HSTEPS = HALF ? (STEPS + 1) / 2 : STEPS, HBYTES = split_first(NKB, NT);
     static_assert(NBUF * SB + split_red_bytes(TPS, WAVES) <= kSplitLds, "LDS");
     constexpr int PF = STEPS == 1 || STEPS > 42 ? 1 : 2;  // steps of B fragments read ahead
+    // Above 36 steps every register counts: the copies' offsets are computed
+    // for every stage (kept, they spilled points' parts, whose reloads wait
+    // for the copies: 100 000 x 512, 1 024 sets of 16 10.1 ms, 6.8 now).
+    constexpr bool TIGHT = STEPS > 36;
     constexpr int ROWS = WAVES * RT * 16;
     // An accumulator for the small products; the few of a tail alone go onto
     // the bias one after the other (error above), which saves the additions.
@@ -454,11 +458,13 @@ __global__ __launch_bounds__(WAVES * 64, 2) void eval_split_kernel(
             const int64_t base = HALF ? (s >> 1) * (int64_t)TB + (s & 1) * HBYTES : s * (int64_t)(TPS * TB);
             const int64_t most = HALF ? (s & 1 ? TB - HBYTES : HBYTES) : TPS * TB;
             const auto win = window_rsrc(chunk + base, (uint32_t)min(most, chunk_bytes - base));
+            int at = tid * 16;
+            if constexpr (TIGHT) asm volatile("" : "+v"(at));
 #pragma unroll
             for (int r = 0; r < CNT; ++r)
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(
                     win, (__attribute__((address_space(3))) void *)(buf + (r * NTHR + wave * 64) * 16), 16,
-                    (r * NTHR + tid) * 16, 0, 0, 0);
+                    at + r * NTHR * 16, 0, 0, 0);
         };
         if (nst > 0) issue(0);
         if (NBUF > 1 && (HALF || nst > 1)) issue(1);
