@@ -140,13 +140,12 @@ EXEMCL_API int exemplar_eval(const void *V, int64_t n, int64_t d, const int32_t 
  * errors as exemplar_eval, except for where temporaries live: partial sums,
  * staged exemplar tiles and (fp16/bf16, and fp32 above d = 512, when V's rows
  * are not whole vectors) the zero-padded copy of V are carved from a fixed
- * scratch buffer of
- * EXEMCL_SCRATCH_BYTES (64 MiB) that is part of the library's code object on
- * each GPU and held until the process ends.  The call makes no allocation of
- * any kind (no hipMalloc, no pool, no library allocation) and records no
- * profiling events.  A batch whose workspace exceeds the buffer is processed
- * in chunks of whole set groups, as exemplar_eval does under a workspace
- * limit, with bitwise the same results.
+ * scratch buffer of EXEMCL_SCRATCH_BYTES (64 MiB) that is part of the
+ * library's code object on each GPU and held until the process ends.  The
+ * call makes no allocation of any kind (no hipMalloc, no pool, no library
+ * allocation) and records no profiling events.  A batch whose workspace
+ * exceeds the buffer is processed in chunks of whole set groups, as
+ * exemplar_eval does under a workspace limit, with bitwise the same results.
  *
  * Every call on one GPU uses that GPU's one buffer, and the buffer keeps the
  * last call's contents (nothing in it needs to start at zero: every byte a
@@ -159,7 +158,8 @@ EXEMCL_API int exemplar_eval(const void *V, int64_t n, int64_t d, const int32_t 
  * workspace plus the padded copy of V, where one is made, does not fit the
  * buffer (for example n in the tens of millions of points, where one set
  * group's partial sums alone exceed 64 MiB, or a padded copy of V larger than
- * the buffer); nothing is queued then.  EXEMCL_WORKSPACE_LIMIT, when set lower, caps it further.
+ * the buffer); nothing is queued then.  EXEMCL_WORKSPACE_LIMIT, when set
+ * lower, caps it further.
  */
 EXEMCL_API int exemplar_eval_noalloc(const void *V, int64_t n, int64_t d, const int32_t *sets, int64_t l,
                                      int64_t k, int precision, float *out, void *stream);
@@ -240,9 +240,10 @@ EXEMCL_API int exemplar_gain(const float *V, int64_t n, int64_t d, const int32_t
  * f(S u {c}) (the same computation as exemplar_gain, with the cache g(v) kept
  * on the device and updated as g <- max(g, <v,c*> - ||c*||^2/2) after each
  * round).  Candidates whose gain in an earlier round already rules them out
- * (f is submodular, Definition 2) need not be scored again.  Ties go to the lowest index (Algorithm 1
- * leaves the choice open); a NaN score ranks below every number.  The
- * rounds are queued back to back on the stream: no host synchronisation.
+ * (f is submodular, Definition 2) need not be scored again.  Ties go to the
+ * lowest index (Algorithm 1 leaves the choice open); a NaN score ranks below
+ * every number.  The rounds are queued back to back on the stream: no host
+ * synchronisation.
  *
  *   V      device, n x d fp32 row-major; read only
  *   n, d   as for exemplar_eval
@@ -284,8 +285,8 @@ EXEMCL_API int exemplar_sqnorm(const void *V, int64_t n, int64_t d, int precisio
  * for these sizes; touches no device.  Writes the chosen exemcl_path to
  * *path and the temporary device bytes to *workspace_bytes (either pointer
  * may be NULL): as a limit they suffice for the whole batch at once, and the
- * call holds no more.  The path depends on (d, k, precision) only, never on l or n,
- * which is what keeps out[j] independent of the batch.  The environment
+ * call holds no more.  The path depends on (d, k, precision) only, never on l
+ * or n, which is what keeps out[j] independent of the batch.  The environment
  * variable EXEMCL_PATH=valu|mfma forces a path where it applies (tests).
  * Two more variables tune the MFMA launch without changing any result:
  * EXEMCL_PERSIST=0|2 forces the plain or the persistent grid (default: a

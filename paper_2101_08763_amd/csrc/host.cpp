@@ -1000,10 +1000,11 @@ EXEMCL_API int exemplar_greedy(const float *V, int64_t n, int64_t d, int64_t K, 
     const int64_t off_pidx = align_up(off_pval + nb * 4, 256);
     const int64_t plain = align_up(off_pidx + nb * 4, 256);
     // Lazy rounds keep the scores as gains, and a list of the candidates that
-    // can still win.  They take 9 more launches a round, about 60 us, and
+    // can still win.  They take 7 more launches a round, about 50 us, and
     // save most of its n^2 d products: worth it from about 100 us of those
     // on.  16 rounds over 20 000 points of d = 100: 5.5 ms scoring everything,
-    // 2.7 ms lazily; 6 rounds over 60 000: 15.7 and 4.8 ms.
+    // 2.6 to 3.3 ms lazily (13 dependent launches a round, so it depends on
+    // the box); 6 rounds over 60 000: 15.7 and 4.8 ms.
     bool lazy = mp.split && K > 1 && (double)n * (double)n * (double)d >= 1.2e10;
     const int64_t off_list = plain;
     const int64_t off_lscores = align_up(off_list + n * 4, 256);

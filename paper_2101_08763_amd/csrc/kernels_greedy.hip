@@ -101,14 +101,17 @@ __global__ __launch_bounds__(kThreads) void argmax_final_kernel(const float *__r
 }
 
 // ---------------------------------------------------------------------------
-// Lazy rounds (see internal.h).  Bounds compare fp32 scores, whose error
-// against exact arithmetic is at most the mean over the points of the error
-// of h_s(v) where it is positive -- there |s| <= 2 |v|, so |v||s| + |s|^2/2 <=
-// 4 |v|^2 -- and of the fp32 sums: 2 (4 e + 2^-20) L({e0}) with e the error of
-// a dot product relative to |v||s|.  e = sqrt(d) 2^-24 is the largest one
-// measured for a single dot product (5e-7 = 0.84 sqrt(100) 2^-24 at d = 100);
-// its mean over the points, which is what a score holds, is a hundredth of
-// that.  A bound uses two scores: tol = (16 sqrt(d) + 64) 2^-24 L({e0}).
+// Lazy rounds (see internal.h).  The filter combines four rounded scores --
+// the candidate's in an earlier round, f then, f now, the best score now --
+// and stands for a fifth, the candidate's now.  Their h_s(v) have the same
+// bits in every round, kernel and launch shape (one order of the same
+// instructions: scoring and cache must keep it), and of fixed numbers the sum
+// of maxima is exactly submodular, so only the rounding of the sums counts.
+// All terms are >= 0 and a score passes 8 roundings: 6 fp32 additions in a
+// wavefront, its workgroup's sum, the result.  Scores are at most L({e0}), so
+// five of them and the three operations in between stay below
+// (5 * 8 + 3) 2^-24 L({e0}) < 64 * 2^-24 L({e0}), for any data.  The filter's
+// tol, (16 sqrt(d) + 64) 2^-24 L({e0}), leaves four times that at d = 100.
 // ---------------------------------------------------------------------------
 constexpr int kPickThreads = 1024;
 

@@ -4,8 +4,10 @@
 // The fp32 MFMA runs at a sixteenth of the bf16 rate and never overlaps VALU
 // work.  An fp32 value is exactly the sum of three bf16 ones,
 //     x = hi + mid + lo   (hi = bf16(x), mid = bf16(x - hi), lo = the rest),
-// and of the nine products of two such sums six matter: the other three are
-// below 2^-26 of |x||y|, under the rounding of one fp32 addition.  So
+// and of the nine products of two such sums six matter: each of the other
+// three is at most 2^-25 of |x||y| (parts round to nearest, so |mid| <= 2^-8
+// |x| and |lo| <= 2^-17 |x|), their sum at most 2^-24, one rounding of fp32,
+// and of either sign.  So
 //     <v, s> = sum  lo*hi + hi*lo + mid*mid + mid*hi + hi*mid + hi*hi
 // on v_mfma_f32_16x16x32_bf16 (products exact, fp32 accumulation), six
 // instructions of 32 coordinates where fp32 needs sixteen times their time.
@@ -14,14 +16,20 @@
 // against 64 bits, random and clustered points, h_s(v) of d = 8 / 32 / 100 /
 // 256 / 512 coordinates: rms error 3.6 / 4.8 / 8.3 / 15 / 21 e-8 of the
 // values' rms, fp32 MFMA 6.7 / 14 / 24 / 43 / 60 e-8 (one accumulator for
-// all six products: 5.3 / 12 / 20 / 36 / 46 e-8 and a mean of -4e-8).
+// all six products: 5.3 / 12 / 20 / 36 / 46 e-8 and a mean of -4e-8).  f
+// averages those errors away; what is left are the exemplars' norms and the
+// sums over points, both summed in fp64 beyond short runs: rms error of f, 34
+// values of d from 3 to 512, eval and gain, 0.38 to 1.00 times that of the
+// fp32 MFMA kernels.
 //
-// Bound by the matrix cores (a sixth of the bf16 peak is 419 TFLOP/s) up to
-// about 200 coordinates, by LDS reads where one row tile is all the registers
-// hold.  A call, fp32 MFMA -> here: 50 000 x 100, 5 000 sets of 10 3 515 ->
-// 1 833 us; 50 000 x 32, 256 sets of 10 77.7 -> 50.0; 30 011 x 301, 333 sets
-// of 7 386 -> 211; the kernel at 10^5 points, 1 024 sets of 16: d = 16 132 ->
-// 263 TFLOP/s, d = 128 142 -> 290, d = 512 133 -> 191.
+// Bound by the matrix cores (a sixth of the bf16 peak is 419 TFLOP/s; busy
+// 83 % of the time at 50 000 x 100, 5 000 sets of 10) up to about 200
+// coordinates.  Where one row tile is all the registers hold, a (half) tile is
+// little work between two barriers (d = 512: matrix cores busy 68 % of the
+// time, LDS reads 34 %).  A call, fp32 MFMA -> here: 50 000 x 100, 5 000 sets
+// of 10 3 539 -> 1 809 us; 50 000 x 32, 256 sets of 10 78.3 -> 48.9; 30 011 x
+// 301, 333 sets of 7 389 -> 194; the kernel at 10^5 points, 1 024 sets of 16:
+// d = 16 132 -> 261 TFLOP/s, d = 128 142 -> 289, d = 512 133 -> 247.
 //
 // Everything else follows mfma_kernels.hpp: the clamp form, points resident
 // in registers, exemplar tiles streamed through LDS, a running max per
@@ -299,7 +307,7 @@ constexpr int split_tps(int nkb, int nt, int waves) {
         --tps;
     return tps;
 }
-// Tiles of which two do not fit (d above 384) are staged in two halves, each
+// Tiles of which two do not fit (d above 352) are staged in two halves, each
 // with a buffer of its own; `gather` stages such a tile whole in one buffer.
 constexpr bool split_halves(int nkb, int nt, int waves) {
     return 2 * split_round(split_tile_bytes(nkb, nt), waves) + split_red_bytes(1, waves) > kSplitLds;

@@ -338,12 +338,26 @@ static void check_limits() {
                     }
 }
 
+// "precision n d kernel" of exemplar_eval's contraction kernel, a line each.
+static void print_kernels() {
+    for (int prec : {EXEMCL_FP32, EXEMCL_FP16, EXEMCL_BF16})
+        for (int64_t n : {1, 6143, 6144, 12000})
+            for (int64_t d : {1, 2, 3, 16, 17, 512, 513, 1024, 1025, 1 << 20, (1 << 20) + 1}) {
+                fake::launches.clear();
+                expect(exemplar_eval(kV, n, d, kI, 40, 3, prec, kF, fresh_stream()) == EXEMCL_OK, "eval");
+                for (const auto &x : fake::launches)
+                    if (x.name.find("eval_") != std::string::npos)
+                        printf("%d %lld %lld %s\n", prec, (long long)n, (long long)d, x.name.c_str());
+            }
+}
+
 int main(int argc, char **argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "grids") check_grids();
     else if (what == "devices") check_devices();
     else if (what == "counter") check_counter();
     else if (what == "limits") check_limits();
+    else if (what == "kernels") print_kernels();
     else expect(false, "no such check", what);
     if (failures) fprintf(stderr, "%d checks failed\n", failures);
     else printf("%s: checks passed\n", what.c_str());

@@ -28,11 +28,17 @@ def points(kind, n, d, seed):
     if kind == "unit":
         X = synth.random_problem(n, d, 1, 1, seed=seed, clusters=20).X
         return X / np.linalg.norm(X, axis=1, keepdims=True)
-    return synth.random_problem(n, d, 1, 1, seed=seed, clusters=15 if kind == "mixture" else 0).X
+    X = synth.random_problem(n, d, 1, 1, seed=seed, clusters=0 if kind == "iid" else 15).X
+    if kind == "heavy":  # norms over five orders of magnitude
+        return X * np.exp(1.5 * np.random.default_rng(seed).standard_normal((n, 1)))
+    if kind == "far":  # clusters far from the origin: gains small beside f
+        return X + 200.0
+    return X
 
 
 @pytest.mark.parametrize("kind,n,d,K", [("mixture", 16_001, 64, 7), ("iid", 16_001, 64, 4), ("iid", 40_000, 8, 4),
-                                        ("twice", 16_000, 64, 6), ("unit", 13_003, 100, 5), ("mixture", 9_001, 300, 4)])
+                                        ("twice", 16_000, 64, 6), ("unit", 13_003, 100, 5), ("mixture", 9_001, 300, 4),
+                                        ("heavy", 16_001, 64, 6), ("far", 16_001, 64, 6)])
 @pytest.mark.parametrize("chunked", [False, True])
 def test_lazy_rounds_score_as_all(torch_gpu, monkeypatch, kind, n, d, K, chunked):
     torch = torch_gpu

@@ -31,6 +31,19 @@ def driver(tmp_path_factory):
     return exe
 
 
+def test_bench_names_the_kernel_that_runs(driver):
+    """bench.dominant_kernel (which prices a workload) against the library's
+    own choice, on both sides of every rule."""
+    import bench
+    env = {k: v for k, v in os.environ.items() if not k.startswith("EXEMCL_")}
+    r = subprocess.run([driver, "kernels"], capture_output=True, text=True, timeout=300, env=env)
+    lines = [ln.split() for ln in r.stdout.splitlines() if "eval_" in ln]
+    assert r.returncode == 0 and len(lines) == 3 * 4 * 11, r.stdout + r.stderr
+    for prec, n, d, name in lines:
+        want = bench.dominant_kernel(["fp32", "fp16", "bf16"][int(prec)], int(n), int(d))
+        assert want in name, (prec, n, d, name, want)
+
+
 @pytest.mark.parametrize("check", ["grids", "devices", "counter", "limits"])
 def test_host_runtime(driver, check):
     env = {k: v for k, v in os.environ.items() if not k.startswith("EXEMCL_")}
