@@ -1004,7 +1004,7 @@ EXEMCL_API int exemplar_greedy(const float *V, int64_t n, int64_t d, int64_t K, 
     // save most of its n^2 d products: worth it from about 100 us of those
     // on.  16 rounds over 20 000 points of d = 100: 5.5 ms scoring everything,
     // 2.6 to 3.3 ms lazily (13 dependent launches a round, so it depends on
-    // the box); 6 rounds over 60 000: 15.7 and 4.8 ms.
+    // the host); 6 rounds over 60 000: 15.7 and 4.8 ms.
     bool lazy = mp.split && K > 1 && (double)n * (double)n * (double)d >= 1.2e10;
     const int64_t off_list = plain;
     const int64_t off_lscores = align_up(off_list + n * 4, 256);
